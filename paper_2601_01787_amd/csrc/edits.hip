@@ -12,7 +12,7 @@
 //            unsigned LEB128 varint; key() maps values to integers in value
 //            order, so steps counts the representable values in (g_i, fhat_i].
 // Encoding is a chain of data-parallel passes (count, scan, compact, sizes,
-// scan, write); decoding runs one thread per chunk of the table.
+// scan, write); decoding runs one block per chunk of the table.
 #include <string.h>
 
 #include "launch.hpp"
@@ -222,46 +222,181 @@ __global__ __launch_bounds__(256) void k_edit_write(const T* fhat, const T* g,
 }
 
 // ---- decoder -------------------------------------------------------------------
-// One thread per chunk: walks its entries and lowers g (holding fhat) at each
-// edited vertex by `steps` representable values.  Reads past the payload or
-// indices past the field set *err and stop the chunk.
+// One block per chunk.  The payload is read in tiles of kDecTile bytes: every
+// thread holds 16 of them, counts the varints that end there, and a block scan
+// gives each varint its number in the chunk (even: a gap, odd: a step count of
+// entry number / 2).  A varint belongs to the thread that holds its last byte,
+// which reads the bytes before its own from LDS (the last 16 bytes of the tile
+// before are kept).  A second scan turns the chunk's gaps into vertex indices,
+// and all threads then lower their entries of g at once.
+// The serial part of a chunk is thus two block scans per 8 KiB of payload and
+// one scan of its entries, where one thread per chunk walked 4096 entries with
+// a dependent byte load per byte and a dependent read of g per entry: bound by
+// latency at 443 threads on the whole chip.  1.8 M edits of a 512^3 binary32
+// field (5.9 MB of stream): 10.6 ms before, 77 us now; the whole call with its
+// copy of the field 10.8 ms before, 0.33 ms now.
+// Reads past the payload or indices outside the field set *err; the chunk's
+// entries in range may still be written.
+constexpr int kDecThreads = 512;
+constexpr int kDecBytes = 16;                        // payload bytes per thread and tile
+constexpr int kDecTile = kDecThreads * kDecBytes;    // 8 KiB
+constexpr int kDecPer = kEditChunk / kDecThreads;    // entries per thread
+
+// Exclusive sum over the kDecThreads threads of a block; *total (all threads).
+template <class V>
+__device__ __forceinline__ V dec_excl(V v, V* sh, V* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  V x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const V y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) sh[wave] = x;
+  __syncthreads();
+  V before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < kDecThreads / 64; ++w) {
+    const V t = sh[w];
+    before += w < wave ? t : V(0);
+    all += t;
+  }
+  __syncthreads();
+  *total = all;
+  return before + x - v;
+}
+
 template <class T>
-__global__ __launch_bounds__(256) void k_edit_decode(const uint8_t* table, const uint8_t* payload,
-                                                     int64_t payload_bytes, int64_t ne,
-                                                     int64_t n, T* g, int* err) {
-  const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t nch = (ne + kEditChunk - 1) / kEditChunk;
-  if (c >= nch) return;
+__global__ __launch_bounds__(kDecThreads) void k_edit_decode(const uint8_t* table,
+                                                             const uint8_t* payload,
+                                                             int64_t payload_bytes, int64_t ne,
+                                                             int64_t n, T* g, int* err) {
+  // [the 16 bytes before the tile][tile], as 8-byte words
+  __shared__ unsigned long long s_raw[(kDecBytes + kDecTile) / 8];
+  __shared__ uint32_t s_at[kEditChunk];             // gaps, then vertex indices
+  __shared__ unsigned long long s_steps[kEditChunk];
+  __shared__ unsigned long long s_sum[kDecThreads / 64];
+  __shared__ int s_cnt[kDecThreads / 64];
+  constexpr uint32_t kBad = 0xFFFFFFFFu;
+  const int tid = threadIdx.x;
+  const int64_t c = blockIdx.x;
   const unsigned long long* t = (const unsigned long long*)(table + 16 * c);
-  int64_t pos = (int64_t)t[0];
-  int64_t prev = t[1] == ~0ull ? -1 : (int64_t)t[1];
-  const int64_t cnt = (ne - c * kEditChunk) < kEditChunk ? ne - c * kEditChunk : kEditChunk;
-  for (int64_t e = 0; e < cnt; ++e) {
-    unsigned long long v[2];
-    for (int w = 0; w < 2; ++w) {
-      unsigned long long x = 0;
-      int shift = 0;
-      for (;;) {
-        if (pos >= payload_bytes || shift > 63) {
-          *err = 1;
-          return;
-        }
-        const uint8_t b = payload[pos++];
-        x |= (unsigned long long)(b & 0x7f) << shift;
-        shift += 7;
-        if (!(b & 0x80)) break;
+  const int64_t start = (int64_t)t[0];
+  const unsigned long long first = t[1] + 1ull;  // (all ones: none before)
+  const int cnt = (int)((ne - c * kEditChunk) < kEditChunk ? ne - c * kEditChunk : kEditChunk);
+  if (start < 0 || start >= payload_bytes) {
+    if (tid == 0) *err = 1;
+    return;
+  }
+  const uint8_t* bytes = (const uint8_t*)s_raw;
+  bool bad = false;
+  if (tid < kDecBytes / 8) s_raw[tid] = 0ull;  // no varint runs into the chunk's first byte
+  int found = 0;                               // varints that ended before this tile
+  // the payload is 8-byte aligned, and so is every tile
+  for (int64_t at = start & ~int64_t(7); found < 2 * cnt; at += kDecTile) {
+    if (at >= payload_bytes) {  // the payload ends inside the chunk
+      bad = true;
+      break;
+    }
+    __syncthreads();  // the tile before has been read (and its tail copied)
+    unsigned long long w[kDecBytes / 8];
+#pragma unroll
+    for (int k = 0; k < kDecBytes / 8; ++k) {
+      const int64_t b = at + tid * kDecBytes + 8 * k;
+      w[k] = 0ull;
+      if (b + 8 <= payload_bytes) {
+        w[k] = *(const unsigned long long*)(payload + b);
+      } else {
+        for (int j = 0; b + j < payload_bytes; ++j)
+          w[k] |= (unsigned long long)payload[b + j] << (8 * j);
       }
-      v[w] = x;
+      // bytes before the chunk's first one read as ends of other varints
+      if (b < start)
+        w[k] = start - b >= 8 ? 0ull : w[k] & (~0ull << (8 * (start - b)));
+      s_raw[(kDecBytes + tid * kDecBytes) / 8 + k] = w[k];
     }
-    const int64_t i = prev + 1 + (int64_t)v[0];
-    if (v[0] >= (unsigned long long)n || i >= n || v[1] == 0) {
-      *err = 1;
-      return;
+    int mine = 0;
+#pragma unroll
+    for (int k = 0; k < kDecBytes / 8; ++k) {
+      const int64_t b = at + tid * kDecBytes + 8 * k;
+      unsigned long long ends = ~w[k] & 0x8080808080808080ull;
+      if (b < start) ends &= start - b >= 8 ? 0ull : ~0ull << (8 * (start - b));
+      if (b + 8 > payload_bytes)
+        ends &= b >= payload_bytes ? 0ull : ~0ull >> (8 * (8 - (payload_bytes - b)));
+      mine += __popcll(ends);
     }
+    int all;
+    int v = found + dec_excl<int>(mine, s_cnt, &all);  // (its barriers publish s_raw)
+    if (mine && v < 2 * cnt) {
+      // the part of this thread's first varint that lies before its bytes
+      int p = kDecBytes + tid * kDecBytes;
+      int q = p;
+      while (p - q < 11 && q > 0 && (bytes[q - 1] & 0x80)) --q;
+      unsigned long long x = 0;
+      int len = 0;
+      for (; q < p; ++q, ++len)
+        if (len < 10) x |= (unsigned long long)(bytes[q] & 0x7f) << (7 * len);
+      for (int k = 0; k < kDecBytes && mine > 0 && v < 2 * cnt; ++k) {
+        const int64_t b = at + tid * kDecBytes + k;
+        if (b < start) continue;
+        const uint8_t y = bytes[p + k];
+        if (len < 10) x |= (unsigned long long)(y & 0x7f) << (7 * len);
+        ++len;
+        if (y & 0x80) continue;
+        bad |= len > 10;
+        if (v & 1) {
+          s_steps[v >> 1] = x;
+          bad |= x == 0ull;
+        } else {
+          const bool in = x < (unsigned long long)n;
+          s_at[v >> 1] = in ? (uint32_t)x : kBad;
+          bad |= !in;
+        }
+        ++v;
+        --mine;
+        x = 0;
+        len = 0;
+      }
+    }
+    found += all;
+    __syncthreads();  // every thread has read the bytes before its own
+    if (tid == kDecThreads - 1)
+      for (int k = 0; k < kDecBytes / 8; ++k) s_raw[k] = w[k];
+  }
+  if (__syncthreads_or(bad)) {
+    if (tid == 0) *err = 1;
+    return;
+  }
+  // gaps to vertex indices: entry e edits the vertex after `first` and e + 1
+  // gaps and e earlier edits
+  unsigned long long sum = 0;
+#pragma unroll
+  for (int k = 0; k < kDecPer; ++k) {
+    const int e = tid * kDecPer + k;
+    if (e < cnt) sum += (unsigned long long)s_at[e] + 1ull;
+  }
+  unsigned long long all;
+  unsigned long long i = first + dec_excl<unsigned long long>(sum, s_sum, &all);
+#pragma unroll
+  for (int k = 0; k < kDecPer; ++k) {
+    const int e = tid * kDecPer + k;
+    if (e >= cnt) break;
+    i += s_at[e];
+    const bool in = i < (unsigned long long)n;
+    s_at[e] = in ? (uint32_t)i : kBad;
+    bad |= !in;
+    ++i;
+  }
+  if (bad) *err = 1;
+  __syncthreads();
+  const gptr<T> gg = as_global(g);
+#pragma unroll
+  for (int k = 0; k < kDecPer; ++k) {
+    const int e = tid + k * kDecThreads;
+    if (e >= cnt || s_at[e] == kBad) continue;
     T out;
-    from_order_key(order_key(g[i]) - v[1], &out);
-    g[i] = out;
-    prev = i;
+    from_order_key(order_key(gg[s_at[e]]) - s_steps[e], &out);
+    gg[s_at[e]] = out;
   }
 }
 
@@ -399,13 +534,12 @@ hipError_t edits_decode(int dtype, const uint8_t* table, const uint8_t* payload,
                         hipStream_t s) {
   const int64_t nch = (ne + kEditChunk - 1) / kEditChunk;
   if (nch == 0) return hipSuccess;
-  const unsigned grid = (unsigned)((nch + 255) / 256);
   if (dtype == PMSZ_F32)
-    hipLaunchKernelGGL(k_edit_decode<float>, dim3(grid), dim3(256), 0, s, table, payload,
-                       payload_bytes, ne, n, (float*)g, err);
+    hipLaunchKernelGGL(k_edit_decode<float>, dim3((unsigned)nch), dim3(kDecThreads), 0, s, table,
+                       payload, payload_bytes, ne, n, (float*)g, err);
   else
-    hipLaunchKernelGGL(k_edit_decode<double>, dim3(grid), dim3(256), 0, s, table, payload,
-                       payload_bytes, ne, n, (double*)g, err);
+    hipLaunchKernelGGL(k_edit_decode<double>, dim3((unsigned)nch), dim3(kDecThreads), 0, s, table,
+                       payload, payload_bytes, ne, n, (double*)g, err);
   return hipGetLastError();
 }
 
