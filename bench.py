@@ -339,9 +339,7 @@ def bench_labels_verify(f, fhat, g, xi, reps):
     """Segmentation labels (pmsz_labels) of f's and of the corrected field's
     directions, and the evaluation counts (pmsz_verify), on the resident 512^3
     workload.  Labels: device time from the library's events; algorithmic
-    bytes = per vertex 1 (direction byte) + 8 (two labels written) once, then
-    per pointer-jumping pass 12 (own label and the label it points at read,
-    own label written; 8 on the last pass, which writes nothing)."""
+    bytes = per vertex 1 (direction byte read) + 8 (two labels written)."""
     import torch
 
     import paper_2601_01787_amd as pmsz
@@ -355,8 +353,7 @@ def bench_labels_verify(f, fhat, g, xi, reps):
             pmsz.labels(d)
             info = pmsz.last_labels()
             ms.append(info["ms"])
-        passes = info["passes_max"] + info["passes_min"]
-        alg = n * 9 + n * 12 * max(passes - 2, 0) + n * 8 * min(passes, 2)
+        alg = n * 9
         dev_ms = sorted(ms)[len(ms) // 2]
         out[name] = {"ms": round(dev_ms, 4), "passes_max": info["passes_max"],
                      "passes_min": info["passes_min"], "algorithmic_bytes": alg,

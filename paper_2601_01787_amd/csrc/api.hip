@@ -742,35 +742,10 @@ static size_t session_ctl_bytes(int32_t cap) {
          align_up(sizeof(FieldIter) * (size_t)cap);
 }
 
-// Pointer jumping to the fixed point on the device: passes are queued a
-// batch at a time (each returns at once when its predecessor changed
-// nothing) and only the batch's changed flags are read back.  *passes
-// receives the passes that ran, the last being the one that found nothing to
-// change.  Direction bytes that do not form a forest (possible only for
-// caller-supplied bytes) either never settle (PMSZ_ERR_INVALID_ARG here) or
-// are counted in *bad by the passes (see k_labels_jump).
-int label_pass(int32_t* lab, int64_t n, const uint8_t* dirs, int shift, unsigned int* flags,
-               unsigned long long* bad, hipStream_t s, int64_t* passes) {
-  HIP_TRY(engine_zero(flags, 4 * kLabelMaxPasses, s));
-  unsigned int h[kLabelBatch];
-  for (int b = 0; b < kLabelMaxPasses; b += kLabelBatch) {
-    for (int p = b; p < b + kLabelBatch; ++p)
-      HIP_TRY(launch_labels_jump(lab, n, dirs, shift, flags, bad, p, s));
-    HIP_TRY(hipMemcpyAsync(h, flags + b, sizeof(h), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    for (int p = 0; p < kLabelBatch; ++p)
-      if (!h[p]) {
-        *passes = b + p + 1;
-        return PMSZ_OK;
-      }
-  }
-  return fail(PMSZ_ERR_INVALID_ARG,
-              "label propagation did not settle in %d passes: the direction bytes do not form "
-              "a forest", kLabelMaxPasses);
-}
-
-// ws: kLabelsWsBytes of device workspace.  Invalid direction codes are
-// reported as PMSZ_ERR_INVALID_ARG (the label arrays are then unspecified).
+// Labels by tiles, then pointer jumping over those left open (see labels.hip).
+// ws: kLabelsWsBytes of device workspace.  Invalid direction codes and cycles
+// of pointers (possible only for caller-supplied bytes) are reported as
+// PMSZ_ERR_INVALID_ARG (the label arrays are then unspecified).
 int labels_impl(const Geo& G, const uint8_t* dirs, int32_t* lmax, int32_t* lmin, void* ws,
                 hipStream_t s) {
   unsigned long long* bad = (unsigned long long*)ws;
@@ -778,21 +753,35 @@ int labels_impl(const Geo& G, const uint8_t* dirs, int32_t* lmax, int32_t* lmin,
   Timing& tm = t_timing;
   int r = timing_events(tm);
   if (r) return r;
+  void* stage;
+  if ((r = staging(t_stage, kLabelsWsBytes, &stage))) return r;
+  const unsigned long long* nbad = (const unsigned long long*)stage;
+  const unsigned int* open = (const unsigned int*)((const char*)stage + 256);
   memset(&tm.labels, 0, sizeof(tm.labels));
-  HIP_TRY(engine_zero(bad, 8, s));
+  HIP_TRY(engine_zero(ws, kLabelsWsBytes, s));
   HIP_TRY(hipEventRecord(tm.ev[0], s));
-  HIP_TRY(launch_labels_init(dirs, G, lmax, lmin, bad, s));
-  if (lmax && (r = label_pass(lmax, G.n, dirs, 0, flags, bad, s, &tm.labels.passes_max)))
-    return r;
-  if (lmin && (r = label_pass(lmin, G.n, dirs, 4, flags, bad, s, &tm.labels.passes_min)))
-    return r;
-  HIP_TRY(hipEventRecord(tm.ev[1], s));
-  unsigned long long nbad = 0;
-  HIP_TRY(hipMemcpyAsync(&nbad, bad, sizeof(nbad), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
-  if (nbad)
-    return fail(PMSZ_ERR_INVALID_ARG, "%llu direction bytes hold a code that is not a neighbour "
-                "of their vertex, or lie on a cycle of pointers", nbad);
+  // the tile pass checks the codes of the labels asked for
+  if (!lmax || !lmin) HIP_TRY(launch_check_dirs(dirs, G, bad, s));
+  if (lmax || lmin) HIP_TRY(launch_labels_tile(dirs, G, lmax, lmin, flags, bad, s));
+  for (int pass = 1;; pass += kLabelBatch) {
+    HIP_TRY(hipEventRecord(tm.ev[1], s));
+    HIP_TRY(hipMemcpyAsync(stage, ws, kLabelsWsBytes, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    if (*nbad)
+      return fail(PMSZ_ERR_INVALID_ARG, "%llu direction bytes hold a code that is not a neighbour "
+                  "of their vertex, or lie on a cycle of pointers", *nbad);
+    if (!open[2 * (pass - 1)] && !open[2 * (pass - 1) + 1]) break;
+    if (pass + kLabelBatch > kLabelMaxPasses)
+      return fail(PMSZ_ERR_INVALID_ARG,
+                  "label propagation did not settle in %d passes: the direction bytes do not form "
+                  "a forest", pass);
+    for (int p = pass; p < pass + kLabelBatch; ++p)
+      HIP_TRY(launch_labels_finish(lmax, lmin, G.n, flags, p, s));
+  }
+  for (int p = 0; p < kLabelMaxPasses; ++p) {
+    if (lmax && (p == 0 || open[2 * (p - 1)])) tm.labels.passes_max = p + 1;
+    if (lmin && (p == 0 || open[2 * (p - 1) + 1])) tm.labels.passes_min = p + 1;
+  }
   float ms = 0.f;
   HIP_TRY(hipEventElapsedTime(&ms, tm.ev[0], tm.ev[1]));
   tm.labels.ms = ms;

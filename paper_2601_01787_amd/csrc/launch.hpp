@@ -30,22 +30,22 @@ inline int64_t bitmap_words(int64_t n) { return (n + 31) / 32; }
 hipError_t launch_dirs(int dtype, const void* h, const Geo& G, uint8_t* dirs, hipStream_t s);
 
 // labels.hip
-// Pointer jumping: each pass follows up to kLabelHops links per vertex;
-// passes are queued kLabelBatch at a time between read-backs of their
-// changed flags, at most kLabelMaxPasses per label array.
+// Labels: one pass over tiles (launch_labels_tile), then, when some paths are
+// not finished, pointer-jumping passes over the labels that are not final:
+// each follows up to kLabelHops links, and they are queued kLabelBatch at a
+// time between read-backs of their flags, at most kLabelMaxPasses with the
+// tile pass.  Labels workspace: [bad-code counter (8 bytes), padded to 256][two
+// words per pass: labels of that kind left open by it].
 constexpr int kLabelHops = 8;
-constexpr int kLabelBatch = 8;
-constexpr int kLabelMaxPasses = 64;
-// Labels workspace: [bad-code counter (8 bytes), padded to 256][changed flag
-// per pass (kLabelMaxPasses words)].
-constexpr size_t kLabelsWsBytes = 256 + 4 * kLabelMaxPasses;
+constexpr int kLabelBatch = 4;
+constexpr int kLabelMaxPasses = 32;
+constexpr size_t kLabelsWsBytes = 256 + 8 * kLabelMaxPasses;
 hipError_t launch_check_dirs(const uint8_t* dirs, const Geo& G, unsigned long long* bad,
                              hipStream_t s);
-hipError_t launch_labels_init(const uint8_t* dirs, const Geo& G, int32_t* lmax, int32_t* lmin,
-                              unsigned long long* bad, hipStream_t s);
-hipError_t launch_labels_jump(int32_t* lab, int64_t n, const uint8_t* dirs, int shift,
-                              unsigned int* flags, unsigned long long* bad, int pass,
-                              hipStream_t s);
+hipError_t launch_labels_tile(const uint8_t* dirs, const Geo& G, int32_t* lmax, int32_t* lmin,
+                              unsigned int* flags, unsigned long long* bad, hipStream_t s);
+hipError_t launch_labels_finish(int32_t* lmax, int32_t* lmin, int64_t n, unsigned int* flags,
+                                int pass, hipStream_t s);
 
 // verify.hip
 struct VerifyCounts {
