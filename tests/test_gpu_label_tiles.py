@@ -99,3 +99,16 @@ def test_cycles_are_refused(ring):
     with pytest.raises(pmsz.PmszError) as e:
         pmsz.labels(d)
     assert e.value.status == 1
+
+
+@pytest.mark.parametrize("shape", [(1, 1), (1, 1023), (1, 1024), (5, 205), (70, 90, 100)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_verify_counts_at_block_edges(shape, dtype):
+    """Blocks of 1024 vertices, with remainders and more than one per block."""
+    f, fhat, xi = random_case(shape, dtype, 12)
+    g = fhat.copy()
+    g.reshape(-1)[-1] = f.reshape(-1)[-1] + dtype(3 * xi)  # the last vertex: out of bound
+    rep = pmsz.verify(dev(f), dev(g), dev(fhat), xi)
+    assert rep == oracle.verify(f, g, fhat, xi)
+    assert rep["bound_violations"] == 1
