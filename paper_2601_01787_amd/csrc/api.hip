@@ -442,7 +442,7 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
   // cost more than they save).
   const bool split = voxels >= kSplitVoxels;
   if (timed) HIP_TRY(hipEventRecord(tm.ev[0], s));
-  if (need_dirs) HIP_TRY(engine_dirs(dtype, a.fd, n, P.total_tiles, s));
+  if (need_dirs) HIP_TRY(engine_dirs(dtype, dims, a.fd, n, P.total_tiles, s));
   if (timed) HIP_TRY(hipEventRecord(tm.ev[1], s));
   if (split) {
     a.tiles_swept = 1;

@@ -28,6 +28,7 @@
 #include <mutex>
 
 #include "engine.hpp"
+#include "wave_tiles.hpp"
 
 namespace pmsz {
 
@@ -949,11 +950,9 @@ __device__ __forceinline__ void flush_counts(gptr<CtrSlot> c, unsigned long long
   }
 }
 
-// Tile detection of round E over the grid's share of the tiles.  ONLY < 0:
-// each field by its state (the engine); ONLY = KIND_FIRST_GIVEN: every tile
-// of the fields in their first round, unmarked (engine_sweep); ONLY =
-// KIND_NEXT: the marked tiles of fields in a tile round (engine_sweep).
-template <class T, int SETS, int ONLY = -1, bool PROP = true, int DIM = 0>
+// Tile detection of round E over the grid's share of the tiles, each field by
+// its state.
+template <class T, int SETS>
 __device__ void detect_tiles(const EngineArgs& a, TileLds<T>& sm, unsigned long long* red,
                              uint16_t* s_tiles, int* s_scan, unsigned long long* s_acc,
                              unsigned long long E, unsigned long long E0, int64_t first,
@@ -973,17 +972,10 @@ __device__ void detect_tiles(const EngineArgs& a, TileLds<T>& sm, unsigned long 
     int take = 0;
     if (mine < a.total_tiles) {
       const FieldDesc& d = a.fd[field_of_tile(a.fd, a.nf, mine)];
-      if (DIM != 0 && d.geo.ndim != DIM) {
-        // the other dimension's sweep kernel takes this tile (and its mark)
-      } else if (ONLY == KIND_FIRST_GIVEN) {
-        const FieldIter s = state_at(d, E, E0);
-        take = !s.started && !s.done;
-      } else {
-        const gptr<uint8_t> flag = as_global(d.act) + p * tile_count(d.geo) + (mine - d.tile_base);
-        if (*flag) {
-          *flag = 0;
-          take = 1;
-        }
+      const gptr<uint8_t> flag = as_global(d.act) + p * tile_count(d.geo) + (mine - d.tile_base);
+      if (*flag) {
+        *flag = 0;
+        take = 1;
       }
     }
     int n_act = 0;
@@ -1001,9 +993,8 @@ __device__ void detect_tiles(const EngineArgs& a, TileLds<T>& sm, unsigned long 
                     : s.started ? KIND_NEXT : KIND_FIRST_GIVEN;
       }
       const int kind = cached_kind;
-      if (kind < 0 || (ONLY >= 0 && kind != ONLY)) continue;
+      if (kind < 0) continue;
       const FieldDesc& d = a.fd[fi];
-      if (DIM != 0 && d.geo.ndim != DIM) continue;  // the other dimension's kernel
       if (tid == 0 && fi != cur) {
         if (cur >= 0) {
           flush_counts(&as_global(a.fd[cur].st)->c[q].s[ctr_slot()], acc_m, acc_nf, acc_nb,
@@ -1016,18 +1007,19 @@ __device__ void detect_tiles(const EngineArgs& a, TileLds<T>& sm, unsigned long 
       const T* g = (const T*)d.g;
       const T* f = (const T*)d.f;
       const T xi = (T)d.xi_t;
-      void* const prop = PROP ? d.prop : nullptr;  // proposals of the targeted edit
       TileCounts tc;
-      if (DIM == 3 || (DIM == 0 && d.geo.ndim == 3)) {
-        if (ONLY != KIND_FIRST_GIVEN && kind == KIND_NEXT)
-          tc = tile3<T, KIND_NEXT, SETS>(sm, red, g, f, d.dirs, d.bm, xi, d.geo, tile, prop);
-        else if (ONLY != KIND_NEXT)
-          tc = tile3<T, KIND_FIRST_GIVEN, SETS>(sm, red, g, f, d.dirs, d.bm, xi, d.geo, tile, prop);
-      } else if (DIM != 3) {
-        if (ONLY != KIND_FIRST_GIVEN && kind == KIND_NEXT)
-          tc = tile2<T, KIND_NEXT, SETS>(sm, red, g, f, d.dirs, d.bm, xi, d.geo, tile, prop);
-        else if (ONLY != KIND_NEXT)
-          tc = tile2<T, KIND_FIRST_GIVEN, SETS>(sm, red, g, f, d.dirs, d.bm, xi, d.geo, tile, prop);
+      if (d.geo.ndim == 3) {
+        if (kind == KIND_NEXT)
+          tc = tile3<T, KIND_NEXT, SETS>(sm, red, g, f, d.dirs, d.bm, xi, d.geo, tile, d.prop);
+        else
+          tc = tile3<T, KIND_FIRST_GIVEN, SETS>(sm, red, g, f, d.dirs, d.bm, xi, d.geo, tile,
+                                                d.prop);
+      } else {
+        if (kind == KIND_NEXT)
+          tc = tile2<T, KIND_NEXT, SETS>(sm, red, g, f, d.dirs, d.bm, xi, d.geo, tile, d.prop);
+        else
+          tc = tile2<T, KIND_FIRST_GIVEN, SETS>(sm, red, g, f, d.dirs, d.bm, xi, d.geo, tile,
+                                                d.prop);
       }
       if (tid == 0) {
         acc_m += unpack3(tc, 0);
@@ -1537,59 +1529,144 @@ __global__ __launch_bounds__(256) void k_tail(EngineArgs a) {
 }
 
 // Directions of f for every field of a batch whose caller gave none, before
-// the engine runs: a plain (non-cooperative) grid over the tiles of all
-// fields, at the stencil's own occupancy.
-template <class T>
+// the engine runs: a plain (non-cooperative) grid, one wave per tile.  One kernel
+// per dimension, each taking only its own fields.
+template <class T, int DIM>
 __global__ __launch_bounds__(256) void k_dirs_fields(const FieldDesc* fd, int nf,
                                                      int64_t total_tiles) {
-  __shared__ TileLds<T> sm;
-  for (int64_t tt = blockIdx.x; tt < total_tiles; tt += gridDim.x) {
+  __shared__ WaveLds<T, DIM, false> sm[4];
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int32_t run = xcd_run(total_tiles);
+  const int64_t blocks = tile_blocks(total_tiles);
+  for (int64_t vb = blockIdx.x; vb < blocks; vb += gridDim.x) {
+    const int64_t tt = first_tile(vb, run) + wave;
+    if (tt >= total_tiles) continue;
     const FieldDesc& d = fd[field_of_tile(fd, nf, tt)];
-    if (d.dirs_given) continue;
-    const T* f = (const T*)d.f;
-    if (d.geo.ndim == 3)
-      tile3<T, KIND_DIRS>(sm, nullptr, f, f, d.dirs, nullptr, T(0), d.geo, tt - d.tile_base);
-    else
-      tile2<T, KIND_DIRS>(sm, nullptr, f, f, d.dirs, nullptr, T(0), d.geo, tt - d.tile_base);
+    if (d.dirs_given || d.geo.ndim != DIM) continue;
+    wave_tile<T, KIND_DIRS, false, DIM>(sm[wave], nullptr, (const T*)d.f, (const T*)nullptr, d.dirs,
+                                        nullptr, T(0), d.geo, (int32_t)(tt - d.tile_base), nullptr);
   }
 }
 
-// The sweep kernels' occupancy and prefetch depth (measured on the 512^3
-// binary32 workload: seven waves per SIMD with two plane sets in flight beat
-// five or six waves and four sets, spills included; binary64 keeps the
-// engine's three waves).
-constexpr int kSweepSets = 2;
-constexpr int kSweepWaves32 = 7, kSweepWaves64 = 3;
-
 // Tile detection of the round the workspace's epoch names, as a plain kernel
 // (see engine_sweep in engine.hpp); it adds to the same counters, flag
-// bitmaps and totals as the engine's own tile detection.
-template <class T, int KIND, bool PROP, int DIM, int SETS>
-__global__ __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? kSweepWaves32 : kSweepWaves64)))
-void k_sweep(EngineArgs a) {
-  __shared__ TileLds<T> sm;
-  __shared__ unsigned long long red[4];
-  __shared__ uint16_t s_tiles[256];
-  __shared__ int s_scan[4];
-  __shared__ unsigned long long s_acc[4];
-  for (int k = threadIdx.x; k < kFlagWords; k += 256) sm.flags[k] = 0u;
+// bitmaps and totals as the engine's own tile detection.  One tile per wave: a
+// wave looks at 64 of its tiles at a time, one per lane, and marches those that
+// are its kernel's (every tile of a field in its first round, or the marked tiles of
+// a field in a tile round).
+// Waves per SIMD of the sweeps: the most that spills next to nothing (a march that
+// spills waits for memory in every step: sweeps of a 512^3 binary32 field took
+// 0.66 ms at four waves against 0.56 ms at three, of a 1024 x 1024 x 768
+// binary64 one 5.2 ms at three against 3.3 ms at two).
+template <class T, int DIM>
+constexpr int sweep_waves() {
+  return (sizeof(T) == 4 ? 4 : 3) - (DIM == 3 ? 1 : 0);
+}
+template <class T, int KIND, bool PROP, int DIM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
+    sweep_waves<T, DIM>()))) void k_sweep(EngineArgs a) {
+  __shared__ WaveLds<T, DIM, true> s_w[4];
+  __shared__ int32_t s_delta[16];
+  __shared__ int s_cur[4];
+  __shared__ unsigned long long s_cnt[4][4];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  WaveLds<T, DIM, true>& sm = s_w[wave];
+  for (int k = lane; k < (int)(sizeof(sm.flags) / 4); k += 64) sm.flags[k] = 0u;
+  if (DIM == 3) set_flag_deltas(s_delta, kRowBits3, kRowBits3 * (TY + 2));
+  else set_flag_deltas(s_delta, kRowBits2, 0);
   __syncthreads();
-  const unsigned long long E = a.ctl->epoch;  // written by the previous launch
-  detect_tiles<T, SETS, KIND, PROP, DIM>(a, sm, red, s_tiles, s_scan, s_acc, E, E, blockIdx.x,
-                                         gridDim.x);
+  EngineCtl* ctl = a.ctl;
+  const unsigned long long E = ctl->epoch;  // written by the previous launch
+  const int p = (int)(E & 1), q = (int)(E % 3);
+  auto counters = [&](int f) { return &as_global(a.fd[f].st)->c[q].s[ctr_slot()]; };
+  unsigned long long* const all_sw = &ctl->tot[q][ctr_slot()].swept;
+  const int32_t run = xcd_run(a.total_tiles);
+  const int64_t blocks = tile_blocks(a.total_tiles);
+  const int64_t W = gridDim.x;  // (a multiple of the XCDs)
+  int cur = -1;  // the field whose counts these are
+  unsigned long long m = 0, nf = 0, nb = 0, sw = 0;
+  for (int64_t base = blockIdx.x; base < blocks; base += W * 64) {
+    const int64_t mine =
+        base + lane * W < blocks ? first_tile(base + lane * W, run) + wave : a.total_tiles;
+    int fi = -1;
+    bool take = false;
+    if (mine < a.total_tiles) {
+      fi = field_of_tile(a.fd, a.nf, mine);
+      const FieldDesc& d = a.fd[fi];
+      if (d.geo.ndim == DIM) {  // (the other dimension's kernel takes the others)
+        const FieldIter s = state_at(d, E, E);
+        if (KIND == KIND_FIRST_GIVEN) {
+          take = !s.started && !s.done;
+        } else {
+          const gptr<uint8_t> flag = as_global(d.act) + p * tile_count(d.geo) + (mine - d.tile_base);
+          if (*flag) {
+            *flag = 0;
+            take = s.started && !s.done && sparse_items(d, s, E) < 0;
+          }
+        }
+      }
+    }
+    for (unsigned long long todo = __ballot(take); todo; todo &= todo - 1ull) {
+      const int l = __builtin_ctzll(todo);
+      const int ft = __builtin_amdgcn_readlane(fi, l);
+      const FieldDesc& d = a.fd[ft];
+      if (ft != cur) {
+        if (cur >= 0 && lane == 0) flush_counts(counters(cur), m, nf, nb, sw, all_sw);
+        m = nf = nb = sw = 0;
+        cur = ft;
+      }
+      const int32_t tile =
+          (int32_t)(first_tile(base + (int64_t)l * W, run) + wave - d.tile_base);
+      const LaneCounts c =
+          wave_tile<T, KIND, PROP, DIM>(sm, s_delta, (const T*)d.g, (const T*)d.f, d.dirs, d.bm,
+                                        (T)d.xi_t, d.geo, tile, d.prop);
+      const unsigned long long t = wave_sum(pack3(c.mism, c.nf, c.nb));
+      m += uniform((int32_t)unpack3(t, 0));
+      nf += uniform((int32_t)unpack3(t, 1));
+      nb += uniform((int32_t)unpack3(t, 2));
+      sw += (unsigned long long)uniform(tile_voxels(d.geo, tile));
+    }
+  }
+  // the rest, one set of atomics for the waves that end on the same field
+  if (lane == 0) {
+    s_cur[wave] = cur;
+    s_cnt[wave][0] = m;
+    s_cnt[wave][1] = nf;
+    s_cnt[wave][2] = nb;
+    s_cnt[wave][3] = sw;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int i = 0; i < 4; ++i) {
+      const int f = s_cur[i];
+      if (f < 0) continue;
+      for (int j = i + 1; j < 4; ++j) {
+        if (s_cur[j] != f) continue;
+        for (int k = 0; k < 4; ++k) s_cnt[i][k] += s_cnt[j][k];
+        s_cur[j] = -1;
+      }
+      flush_counts(counters(f), s_cnt[i][0], s_cnt[i][1], s_cnt[i][2], s_cnt[i][3], all_sw);
+    }
+  }
 }
 
-hipError_t engine_dirs(int dtype, const FieldDesc* fd, int nf, int64_t total_tiles,
+template <class T>
+static void dirs_dims(int dims, const FieldDesc* fd, int nf, int64_t total_tiles, hipStream_t s) {
+  int64_t grid = tile_blocks(total_tiles);
+  if (grid > (1 << 20)) grid = 1 << 20;
+  if (dims & 2)
+    hipLaunchKernelGGL((k_dirs_fields<T, 2>), dim3((unsigned)grid), dim3(256), 0, s, fd, nf,
+                       total_tiles);
+  if (dims & 4)
+    hipLaunchKernelGGL((k_dirs_fields<T, 3>), dim3((unsigned)grid), dim3(256), 0, s, fd, nf,
+                       total_tiles);
+}
+
+hipError_t engine_dirs(int dtype, int dims, const FieldDesc* fd, int nf, int64_t total_tiles,
                        hipStream_t s) {
-  int64_t grid = total_tiles < 65536 ? total_tiles : 65536;
-  if (grid < 1) grid = 1;
-  if (dtype == PMSZ_F32)
-    hipLaunchKernelGGL(k_dirs_fields<float>, dim3((unsigned)grid), dim3(256), 0, s, fd, nf,
-                       total_tiles);
-  else
-    hipLaunchKernelGGL(k_dirs_fields<double>, dim3((unsigned)grid), dim3(256), 0, s, fd, nf,
-                       total_tiles);
+  if (dtype == PMSZ_F32) dirs_dims<float>(dims, fd, nf, total_tiles, s);
+  else dirs_dims<double>(dims, fd, nf, total_tiles, s);
   return hipGetLastError();
 }
 
@@ -1640,22 +1717,20 @@ static hipError_t occupancy(int dev, Occupancy& out) {
   return occupancy_of((const void*)k_engine<T>, dev, out);
 }
 
-// One block per resident slot of the chip (every block resident at once),
-// at most one per tile.
+// Waves enough to fill the chip kSweepFill times over, at most one per tile.
+constexpr int64_t kSweepFill = 4;
 template <class T, int KIND, bool PROP, int DIM>
 static hipError_t sweep_t(const EngineArgs& a, hipStream_t s) {
-  constexpr int SETS = kSweepSets;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   Occupancy occ;
-  if ((e = occupancy_of((const void*)k_sweep<T, KIND, PROP, DIM, SETS>, dev, occ)) != hipSuccess)
+  if ((e = occupancy_of((const void*)k_sweep<T, KIND, PROP, DIM>, dev, occ)) != hipSuccess)
     return e;
-  int64_t grid = (int64_t)(occ.per_cu > 0 ? occ.per_cu : 1) * (occ.cus > 0 ? occ.cus : 1);
-  if (grid > a.total_tiles) grid = a.total_tiles;
-  if (grid < 1) grid = 1;
-  hipLaunchKernelGGL((k_sweep<T, KIND, PROP, DIM, SETS>), dim3((unsigned)grid), dim3(256), 0, s,
-                     a);
+  int64_t grid = kSweepFill * (occ.per_cu > 0 ? occ.per_cu : 1) * (occ.cus > 0 ? occ.cus : 1);
+  grid = (grid + kXcds - 1) / kXcds * kXcds;
+  if (grid > tile_blocks(a.total_tiles)) grid = tile_blocks(a.total_tiles);
+  hipLaunchKernelGGL((k_sweep<T, KIND, PROP, DIM>), dim3((unsigned)grid), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -190,8 +190,8 @@ hipError_t engine_launch(int dtype, const EngineArgs& a, hipStream_t s, int* gri
 hipError_t engine_tail(int dtype, const EngineArgs& a, hipStream_t s);
 // Directions of f, before the engine, for every field of the device table fd
 // whose dirs_given is 0 (into its dirs); the engine then starts every field
-// from given directions.
-hipError_t engine_dirs(int dtype, const FieldDesc* fd, int nf, int64_t total_tiles,
+// from given directions.  dims as for engine_sweep.
+hipError_t engine_dirs(int dtype, int dims, const FieldDesc* fd, int nf, int64_t total_tiles,
                        hipStream_t s);
 // Tile detection of one round as a plain kernel (no grid barrier, so it runs
 // at the march's own occupancy instead of the persistent engine's), for the

@@ -1,40 +1,50 @@
 // stencil.hip -- standalone steepest-direction pass (pmsz_directions and the
-// directions used by verification): one block per tile of the shared tile
-// code, writing one direction byte per vertex.
+// directions used by verification): one wave per tile (wave_tiles.hpp), writing
+// one direction byte per vertex.
 #include "launch.hpp"
-#include "tiles.hpp"
+#include "wave_tiles.hpp"
 
 namespace pmsz {
 
-template <class T>
-__global__ __launch_bounds__(256) void k_dirs(const T* __restrict__ h, TileGeo G,
-                                              uint8_t* __restrict__ dirs) {
-  __shared__ TileLds<T> sm;
-  __shared__ unsigned long long red[4];
-  if (G.ndim == 3)
-    tile3<T, KIND_DIRS>(sm, red, h, nullptr, dirs, nullptr, T(0), G, blockIdx.x);
-  else
-    tile2<T, KIND_DIRS>(sm, red, h, nullptr, dirs, nullptr, T(0), G, blockIdx.x);
+template <class T, int DIM>
+__global__ __launch_bounds__(256) void k_dirs(const T* h, TileGeo G, uint8_t* dirs,
+                                              int32_t run) {
+  __shared__ WaveLds<T, DIM, false> sm[4];
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int32_t tile = (int32_t)first_tile(blockIdx.x, run) + wave;
+  if (tile >= (int32_t)tile_count(G)) return;
+  wave_tile<T, KIND_DIRS, false, DIM>(sm[wave], nullptr, h, (const T*)nullptr, dirs, nullptr, T(0),
+                                      G, tile, nullptr);
 }
 
-// Longer marches than the correction engine uses (no frontier to keep fine),
-// while still giving the chip several blocks per compute unit.
+// Longer marches than the correction engine's on small fields (no frontier to
+// keep fine), while still giving the chip several waves per compute unit.
 static int dirs_chunk(int ndim, int64_t nx, int64_t ny, int64_t nz) {
   const int64_t cols = ndim == 3 ? ((nx + TX - 1) / TX) * ((ny + TY - 1) / TY) : (nx + RX - 1) / RX;
   const int64_t depth = ndim == 3 ? nz : ny;
   int64_t c = depth * cols / 4096;
   if (c < 2) c = 2;
-  if (c > 64) c = 64;
+  const int most = ndim == 3 ? kMaxChunk : kMaxChunk / 2;
+  if (c > most) c = most;
   return (int)c;
+}
+
+template <class T>
+static void launch_dirs_t(const void* h, const TileGeo& G, uint8_t* dirs, hipStream_t s) {
+  const dim3 grid((unsigned)tile_blocks(tile_count(G)));
+  const int32_t run = xcd_run(tile_count(G));
+  if (G.ndim == 3)
+    hipLaunchKernelGGL((k_dirs<T, 3>), grid, dim3(256), 0, s, (const T*)h, G, dirs, run);
+  else
+    hipLaunchKernelGGL((k_dirs<T, 2>), grid, dim3(256), 0, s, (const T*)h, G, dirs, run);
 }
 
 hipError_t launch_dirs(int dtype, const void* h, const Geo& g, uint8_t* dirs, hipStream_t s) {
   const TileGeo G = make_tile_geo(g.ndim, g.nx, g.ny, g.nz, dirs_chunk(g.ndim, g.nx, g.ny, g.nz));
-  const unsigned grid = (unsigned)tile_count(G);
   if (dtype == PMSZ_F32)
-    hipLaunchKernelGGL(k_dirs<float>, dim3(grid), dim3(256), 0, s, (const float*)h, G, dirs);
+    launch_dirs_t<float>(h, G, dirs, s);
   else
-    hipLaunchKernelGGL(k_dirs<double>, dim3(grid), dim3(256), 0, s, (const double*)h, G, dirs);
+    launch_dirs_t<double>(h, G, dirs, s);
   return hipGetLastError();
 }
 

@@ -164,7 +164,7 @@ inline TileGeo make_tile_geo(int ndim, int64_t nx, int64_t ny, int64_t nz, int c
 
 // What a tile pass does with the directions it computes.
 enum TileKind {
-  KIND_DIRS = 0,        // write the direction bytes of h
+  KIND_DIRS = 0,        // write the direction bytes of h (wave_tiles.hpp only)
   KIND_FIRST_GIVEN = 2, // first round: validation of g against f, mismatch
                         // detection of g against the given directions of f
   KIND_NEXT = 3         // later rounds: mismatch detection of g
@@ -355,11 +355,10 @@ __device__ __forceinline__ T fast_margin(T xi) {
   return m < xi ? m : next_down<T>(xi);  // strictly below xi (xi > 0)
 }
 
-// One 3D tile.  h: field whose directions are evaluated (g, or f for
-// KIND_DIRS).  f: original field (its values for the first round's
-// validation).  dirs: direction bytes of f, read (NEXT, FIRST_GIVEN) or
-// written (DIRS).  bm: the field's flag bitmap.  Returns the packed counts in
-// thread 0.
+// One 3D tile of the engine's own rounds.  h: field whose directions are
+// evaluated (g).  f: original field (its values for the first round's
+// validation).  dirs: direction bytes of f.  bm: the field's flag bitmap.
+// Returns the packed counts in thread 0.
 //
 // The march visits planes p = z0-1 .. z1 (z1 = end of the tile), two per
 // step.  For each plane p it reduces the thread's upper square (x..x+1,
@@ -378,7 +377,7 @@ __device__ __forceinline__ T fast_margin(T xi) {
 // only its own pair.
 template <class T, int KIND, int SETS = sets_for<T, KIND>()>
 __device__ TileCounts tile3(TileLds<T>& sm, unsigned long long* red, const T* h_in,
-                            const T* f_in, uint8_t* dirs_in, uint32_t* bm_in, T xi,
+                            const T* f_in, const uint8_t* dirs_in, uint32_t* bm_in, T xi,
                             const TileGeo G_in, int64_t tile_in, void* prop_in = nullptr) {
   // every argument is uniform over the block (one tile of one field)
   const TileGeo G = uniform_geo(G_in);
@@ -386,11 +385,10 @@ __device__ TileCounts tile3(TileLds<T>& sm, unsigned long long* red, const T* h_
   void* const prop = uniform_ptr(prop_in);
   const gptr<const T> h = as_global(uniform_ptr(h_in));
   const gptr<const T> f = as_global(uniform_ptr(f_in));
-  const gptr<uint8_t> dirs = as_global(uniform_ptr(dirs_in));
+  const gptr<const uint8_t> dirs = as_global(uniform_ptr(dirs_in));
   const gptr<uint32_t> bm = as_global(uniform_ptr(bm_in));
   const T xi_in = fast_margin<T>(xi);  // validation's fast test (bound_class)
   constexpr int PER = (PLANE + 255) / 256;
-  constexpr bool kReadDirs = (KIND == KIND_NEXT || KIND == KIND_FIRST_GIVEN);
   constexpr bool kGivenF = (KIND == KIND_FIRST_GIVEN);
   constexpr int kSets = SETS;
   const int tid = threadIdx.x, tx = tid & (TX - 1), ty = tid / TX;
@@ -444,10 +442,8 @@ __device__ TileCounts tile3(TileLds<T>& sm, unsigned long long* red, const T* h_
   };
   auto fetch_own = [&](int32_t v, Set& S) {
     const int64_t pl = (int64_t)G.sxy * (v >= 0 && v < G.nz ? v : 0) + corner;
-    if (kReadDirs) {
-      opaque_off(rel);
-      S.d = (dirs + pl)[rel];
-    }
+    opaque_off(rel);
+    S.d = (dirs + pl)[rel];
     if (kGivenF) {
       opaque_off(relb);
       S.fv = *(gptr<const T>)((gptr<const char>)(f + pl) + relb);
@@ -476,7 +472,7 @@ __device__ TileCounts tile3(TileLds<T>& sm, unsigned long long* red, const T* h_
   // flag bit of this column's vertex in the halo box's first plane
   constexpr int32_t kPlaneBits3 = kRowBits3 * (TY + 2);
   const int32_t bit0 = (ty + 1) * kRowBits3 + (tx + 1) - (z0 - 1) * kPlaneBits3;
-  if (KIND != KIND_DIRS) set_flag_deltas(sm.fdelta, kRowBits3, kPlaneBits3);
+  set_flag_deltas(sm.fdelta, kRowBits3, kPlaneBits3);
   unsigned mism = 0, nf = 0, nb = 0;
   // carried from plane p-1: its squares, the lower box of vertex p-1 and the
   // centre value (for validation)
@@ -488,19 +484,15 @@ __device__ TileCounts tile3(TileLds<T>& sm, unsigned long long* red, const T* h_
                     T fv, T centre) {
     const Ext<T> e = merge_up(lob, merge_up(up, with_bits(upn, 4)));
     const int ca = e.ca, cd = e.cd;
-    if (KIND == KIND_DIRS) {
-      (dirs + ((int64_t)G.sxy * v + corner))[rel] = (uint8_t)(ca | (cd << 4));
-    } else {
-      const int fa = d & 15, fd = d >> 4;
-      if (kGivenF) {
-        const int bc = bound_class<T>(fv, centre, xi, xi_in);
-        nf += bc == 1;
-        nb += bc == 2;
-      }
-      if (core_col && v >= G.cz0 && v < G.cz1)
-        mism += flag_targets<T>(bit0 + v * kPlaneBits3, X + G.nx * Y + G.sxy * v, ca, cd, fa, fd,
-                                G, sm.flags, sm.fdelta, prop, h, e.lo);
+    const int fa = d & 15, fd = d >> 4;
+    if (kGivenF) {
+      const int bc = bound_class<T>(fv, centre, xi, xi_in);
+      nf += bc == 1;
+      nb += bc == 2;
     }
+    if (core_col && v >= G.cz0 && v < G.cz1)
+      mism += flag_targets<T>(bit0 + v * kPlaneBits3, X + G.nx * Y + G.sxy * v, ca, cd, fa, fd, G,
+                              sm.flags, sm.fdelta, prop, h, e.lo);
   };
   // Two planes per barrier: step p stages planes p and p+1 in one pair of LDS
   // slots, reduces both planes' squares (two independent chains), and
@@ -550,7 +542,6 @@ __device__ TileCounts tile3(TileLds<T>& sm, unsigned long long* red, const T* h_
       step(p + k, Q[(k + 2) % kSets], Q[(k + 3) % kSets], p + k <= z1, p + k + 1 <= z1);
   }
   lds_barrier();  // the next tile of this block reuses the LDS buffers
-  if (KIND == KIND_DIRS) return 0;
   flush_rows<kFlagW3>(sm.flags, (z1 - z0 + 2) * (TY + 2), [&](int32_t r) {
     const int32_t lz = r / (TY + 2), ly = r - lz * (TY + 2);
     return G.nx * (y0 - 1 + ly) + G.sxy * (z0 - 1 + lz) + (x0 - 1);
@@ -563,7 +554,7 @@ __device__ TileCounts tile3(TileLds<T>& sm, unsigned long long* red, const T* h_
 // pair (x-1..x) and finishes vertex r-1.
 template <class T, int KIND, int SETS = sets_for<T, KIND>()>
 __device__ TileCounts tile2(TileLds<T>& sm, unsigned long long* red, const T* h_in,
-                            const T* f_in, uint8_t* dirs_in, uint32_t* bm_in, T xi,
+                            const T* f_in, const uint8_t* dirs_in, uint32_t* bm_in, T xi,
                             const TileGeo G_in, int64_t tile_in, void* prop_in = nullptr) {
   // every argument is uniform over the block (one tile of one field)
   const TileGeo G = uniform_geo(G_in);
@@ -571,11 +562,10 @@ __device__ TileCounts tile2(TileLds<T>& sm, unsigned long long* red, const T* h_
   void* const prop = uniform_ptr(prop_in);
   const gptr<const T> h = as_global(uniform_ptr(h_in));
   const gptr<const T> f = as_global(uniform_ptr(f_in));
-  const gptr<uint8_t> dirs = as_global(uniform_ptr(dirs_in));
+  const gptr<const uint8_t> dirs = as_global(uniform_ptr(dirs_in));
   const gptr<uint32_t> bm = as_global(uniform_ptr(bm_in));
   const T xi_in = fast_margin<T>(xi);  // validation's fast test (bound_class)
   constexpr int PER = (RW + 255) / 256;
-  constexpr bool kReadDirs = (KIND == KIND_NEXT || KIND == KIND_FIRST_GIVEN);
   constexpr bool kGivenF = (KIND == KIND_FIRST_GIVEN);
   constexpr int kSets = SETS;
   const int tid = threadIdx.x;
@@ -620,10 +610,8 @@ __device__ TileCounts tile2(TileLds<T>& sm, unsigned long long* red, const T* h_
   };
   auto fetch_own = [&](int32_t v, Set& S) {
     const int64_t pl = (int64_t)G.nx * (v >= 0 && v < G.ny ? v : 0) + corner;
-    if (kReadDirs) {
-      opaque_off(rel);
-      S.d = (dirs + pl)[rel];
-    }
+    opaque_off(rel);
+    S.d = (dirs + pl)[rel];
     if (kGivenF) {
       opaque_off(relb);
       S.fv = *(gptr<const T>)((gptr<const char>)(f + pl) + relb);
@@ -646,7 +634,7 @@ __device__ TileCounts tile2(TileLds<T>& sm, unsigned long long* red, const T* h_
   };
   // flag rows are the strip's rows y0-1 .. y1; this column's bit in the first
   const int32_t bit0 = tid + 1 - (y0 - 1) * kRowBits2;
-  if (KIND != KIND_DIRS) set_flag_deltas(sm.fdelta, kRowBits2, 0);
+  set_flag_deltas(sm.fdelta, kRowBits2, 0);
   unsigned mism = 0, nf = 0, nb = 0;
   Ext<T> gu{}, gl{}, gbox{};
   T gc = T(0);
@@ -664,34 +652,30 @@ __device__ TileCounts tile2(TileLds<T>& sm, unsigned long long* red, const T* h_
       const int32_t v = r - 1;
       const Ext<T> e = merge_up(gbox, merge_up(gu, with_bits(su, 2)));
       const int ca = e.ca, cd = e.cd;
-      if (KIND == KIND_DIRS) {
-        (dirs + ((int64_t)G.nx * v + corner))[rel] = (uint8_t)(ca | (cd << 4));
-      } else {
-        const int fa = d_cur & 15, fd = d_cur >> 4;
-        if (kGivenF) {
-          const int bc = bound_class<T>(f_cur, gc, xi, xi_in);
-          nf += bc == 1;
-          nb += bc == 2;
+      const int fa = d_cur & 15, fd = d_cur >> 4;
+      if (kGivenF) {
+        const int bc = bound_class<T>(f_cur, gc, xi, xi_in);
+        nf += bc == 1;
+        nb += bc == 2;
+      }
+      // 2D codes only use the x and y bits; rows are indexed by y
+      const int32_t vi = X + G.nx * v;
+      const bool core = core_col && v >= G.cy0 && v < G.cy1;
+      const int32_t bi = bit0 + v * kRowBits2;
+      if (core && ca != fa) {
+        flag_bit(sm.flags, bi + sm.fdelta[ca]);
+        if (prop) {
+          const int32_t c = vi + code_delta32(fa, G.nx, G.sxy);
+          propose<T>(prop, vi + code_delta32(ca, G.nx, G.sxy), c, h[c]);
         }
-        // 2D codes only use the x and y bits; rows are indexed by y
-        const int32_t vi = X + G.nx * v;
-        const bool core = core_col && v >= G.cy0 && v < G.cy1;
-        const int32_t bi = bit0 + v * kRowBits2;
-        if (core && ca != fa) {
-          flag_bit(sm.flags, bi + sm.fdelta[ca]);
-          if (prop) {
-            const int32_t c = vi + code_delta32(fa, G.nx, G.sxy);
-            propose<T>(prop, vi + code_delta32(ca, G.nx, G.sxy), c, h[c]);
-          }
-          ++mism;
-        }
-        if (core && cd != fd) {
-          flag_bit(sm.flags, bi + sm.fdelta[fd]);
-          if (prop)
-            propose<T>(prop, vi + code_delta32(fd, G.nx, G.sxy),
-                       vi + code_delta32(cd, G.nx, G.sxy), e.lo);
-          ++mism;
-        }
+        ++mism;
+      }
+      if (core && cd != fd) {
+        flag_bit(sm.flags, bi + sm.fdelta[fd]);
+        if (prop)
+          propose<T>(prop, vi + code_delta32(fd, G.nx, G.sxy), vi + code_delta32(cd, G.nx, G.sxy),
+                     e.lo);
+        ++mism;
       }
     }
     gu = su;
@@ -716,7 +700,6 @@ __device__ TileCounts tile2(TileLds<T>& sm, unsigned long long* red, const T* h_
     for (int k = 0; k < kSets; ++k) step(r + k, Q[(k + 2) % kSets], r + k <= y1);
   }
   lds_barrier();  // the next tile of this block reuses the LDS buffers
-  if (KIND == KIND_DIRS) return 0;
   flush_rows<kFlagW2>(sm.flags, y1 - y0 + 2,
                       [&](int32_t r) { return G.nx * (y0 - 1 + r) + (x0 - 1); }, bm);
   return block_sum(pack3(mism, nf, nb), red);
