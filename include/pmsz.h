@@ -257,7 +257,7 @@ typedef struct {
   int64_t lowered;         /* block copies lowered by the exchanges             */
   int64_t steps_applied;   /* value changes made by the local corrections      */
   double compute_ms;       /* device time of the local corrections, all phases */
-  double exchange_ms;      /* device time of the exchanges, all phases         */
+  double exchange_ms;      /* device time of the exchanges and of the copy back */
   int32_t status;          /* pmsz_status of the run                            */
   int32_t reserved;
 } pmsz_blocks_stats;

@@ -395,7 +395,9 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
     d.list = (uint32_t*)(fb + L.list);
     d.marks = (uint8_t*)(fb + L.marks);
     d.list_cap = list_capacity(d.geo);
-    d.dirs = d.dirs_given ? (uint8_t*)dirs_given[i] : (uint8_t*)(base + P.dirs + P.dirs_off[i]);
+    // (an array given with dirs_given 0 is filled first: pmsz_correct_blocks)
+    d.dirs = dirs_given && dirs_given[i] ? (uint8_t*)dirs_given[i]
+                                         : (uint8_t*)(base + P.dirs + P.dirs_off[i]);
     d.prop = P.edit_mode ? (void*)(base + P.prop + P.prop_off[i]) : nullptr;
   }
   const size_t up = sizeof(FieldDesc) * (size_t)n;
@@ -1316,16 +1318,21 @@ int pmsz_correct_blocks(const pmsz_grid* grid, const void* f, void* g, double xi
   hipStream_t s = (hipStream_t)stream;
   char* base = (char*)ws;
   const Geo G = make_geo(*grid);
-  // block table for the exchange
+  const BlockCopy* const tab_dev = (const BlockCopy*)(base + B.tab);
+  int64_t max_rows = 0;
+  // block table for the copies and the exchange
   {
     std::vector<BlockCopy> tab((size_t)B.R);
     for (int64_t id = 0; id < B.R; ++id) {
-      tab[id].ox = B.org[3 * id];
-      tab[id].oy = B.org[3 * id + 1];
-      tab[id].oz = B.org[3 * id + 2];
-      tab[id].lnx = B.ext[3 * id];
-      tab[id].lny = B.ext[3 * id + 1];
+      tab[id].ox = (int32_t)B.org[3 * id];
+      tab[id].oy = (int32_t)B.org[3 * id + 1];
+      tab[id].oz = (int32_t)B.org[3 * id + 2];
+      tab[id].lnx = (int32_t)B.ext[3 * id];
+      tab[id].lny = (int32_t)B.ext[3 * id + 1];
+      tab[id].lnz = (int32_t)B.ext[3 * id + 2];
+      tab[id].f = base + B.off_f[id];
       tab[id].g = base + B.off_g[id];
+      max_rows = std::max(max_rows, B.ext[3 * id + 1] * B.ext[3 * id + 2]);
     }
     void* stage;
     const size_t tb = sizeof(BlockCopy) * tab.size(), hb = sizeof(int32_t) * B.holders.size(),
@@ -1341,13 +1348,9 @@ int pmsz_correct_blocks(const pmsz_grid* grid, const void* f, void* g, double xi
                              hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));  // the staging buffer is reused below
   }
-  // copies of f and fhat, and the directions of each copy of f
-  for (int64_t id = 0; id < B.R; ++id) {
-    HIP_TRY(blocks_gather(grid->dtype, f, G, &B.org[3 * id], &B.ext[3 * id], base + B.off_f[id], s));
-    HIP_TRY(blocks_gather(grid->dtype, g, G, &B.org[3 * id], &B.ext[3 * id], base + B.off_g[id], s));
-    HIP_TRY(launch_dirs(grid->dtype, base + B.off_f[id], make_geo(B.fields[id].grid),
-                        (uint8_t*)(base + B.off_d[id]), s));
-  }
+  // copies of f and fhat; the first phase makes the directions of each copy of f
+  HIP_TRY(blocks_gather(grid->dtype, f, g, G, tab_dev, (int32_t)B.R, max_rows, s));
+  for (int64_t id = 0; id < B.R; ++id) B.P.fd[id].dirs_given = 0;
   hipEvent_t ev[2];
   HIP_TRY(hipEventCreate(&ev[0]));
   HIP_TRY(hipEventCreate(&ev[1]));
@@ -1371,18 +1374,14 @@ int pmsz_correct_blocks(const pmsz_grid* grid, const void* f, void* g, double xi
         r = fail(st[id].status, "block %lld: %s", (long long)id,
                  pmsz_status_string(st[id].status));
     if (r != PMSZ_OK) break;
+    for (int64_t id = 0; id < B.R; ++id) B.P.fd[id].dirs_given = 1;
     stats->compute_ms += t_timing.last.dirs_ms + t_timing.last.sweep_ms + t_timing.last.engine_ms;
     // ghost-layer exchange
     unsigned long long lowered = 0;
     if ((r = hip_check(engine_fill(ctr, sizeof(unsigned long long), 0u, s)))) break;
     if ((r = hip_check(hipEventRecord(ev[0], s)))) break;
-    // owners' cores into g, then the shared vertices take their minimum
-    for (int64_t id = 0; id < B.R && r == PMSZ_OK; ++id)
-      r = hip_check(blocks_scatter_core(grid->dtype, base + B.off_g[id], &B.ext[3 * id],
-                                        &B.core[6 * id], &B.org[3 * id], g, G, s));
-    if (r != PMSZ_OK) break;
-    if ((r = hip_check(blocks_exchange(grid->dtype, g, G, B.nb,
-                                       (const BlockCopy*)(base + B.tab),
+    // the shared vertices take their minimum
+    if ((r = hip_check(blocks_exchange(grid->dtype, G, B.nb, tab_dev,
                                        (const int32_t*)(base + B.hold),
                                        (const int32_t*)(base + B.planes_off),
                                        (int32_t)(B.planes.size() / 2), B.max_plane, ctr, s))))
@@ -1412,6 +1411,18 @@ int pmsz_correct_blocks(const pmsz_grid* grid, const void* f, void* g, double xi
       status = any_stalled ? PMSZ_ERR_STALLED : PMSZ_ERR_NOT_CONVERGED;
       break;
     }
+  }
+  // the owners' cores into g, once
+  if (r == PMSZ_OK) {
+    float ms = 0.f;
+    r = hip_check(hipEventRecord(ev[0], s));
+    if (r == PMSZ_OK)
+      r = hip_check(
+          blocks_scatter_cores(grid->dtype, tab_dev, (int32_t)B.R, max_rows, g, G, s));
+    if (r == PMSZ_OK) r = hip_check(hipEventRecord(ev[1], s));
+    if (r == PMSZ_OK) r = hip_check(hipStreamSynchronize(s));
+    if (r == PMSZ_OK) r = hip_check(hipEventElapsedTime(&ms, ev[0], ev[1]));
+    stats->exchange_ms += ms;
   }
   (void)hipEventDestroy(ev[0]);
   (void)hipEventDestroy(ev[1]);

@@ -57,19 +57,23 @@ hipError_t launch_verify(int dtype, const void* f, const void* g, const void* fh
                          const int32_t* lf_min, const int32_t* lg_max, const int32_t* lg_min,
                          VerifyCounts* out, hipStream_t s);
 
-// blocks.hip: one block of a decomposed domain as the exchange sees it --
-// the origin of its copy in the global grid, the copy's x and y extents and
-// the copy's values (dense, x fastest).
+// blocks.hip: one block of a decomposed domain -- the origin of its copy in
+// the global grid, the copy's extents and its values of f and g (dense, x
+// fastest).  Its core is the copy without the ghost layer, which it has on
+// every side that does not end at the grid's.
 struct BlockCopy {
-  int64_t ox, oy, oz;
-  int64_t lnx, lny;
+  int32_t ox, oy, oz;
+  int32_t lnx, lny, lnz;
+  void* f;
   void* g;
 };
-hipError_t blocks_gather(int dtype, const void* src, const Geo& G, const int64_t o[3],
-                         const int64_t l[3], void* dst, hipStream_t s);
-hipError_t blocks_scatter_core(int dtype, const void* src, const int64_t l[3], const int64_t c[6],
-                               const int64_t o[3], void* dst, const Geo& G, hipStream_t s);
-hipError_t blocks_exchange(int dtype, void* g, const Geo& G, const int32_t nb[3],
+// f and g of the grid into the copies of every block.
+hipError_t blocks_gather(int dtype, const void* f, const void* g, const Geo& G,
+                         const BlockCopy* tab, int32_t blocks, int64_t max_rows, hipStream_t s);
+// The cores of every block's g into g.
+hipError_t blocks_scatter_cores(int dtype, const BlockCopy* tab, int32_t blocks, int64_t max_rows,
+                                void* g, const Geo& G, hipStream_t s);
+hipError_t blocks_exchange(int dtype, const Geo& G, const int32_t nb[3],
                            const BlockCopy* tab, const int32_t* hold, const int32_t* planes,
                            int32_t n_planes, int64_t max_plane, unsigned long long* lowered,
                            hipStream_t s);
