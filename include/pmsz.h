@@ -185,6 +185,14 @@ int pmsz_correct_mode(const pmsz_grid* grid, const void* f, void* g, double xi,
                       const uint8_t* dirs_f, int edit_mode, void* ws, size_t ws_bytes,
                       int64_t max_iters, pmsz_stats* stats, void* stream);
 
+/* pmsz_correct_mode with fhat in an array of its own: g receives fhat, then the
+ * edits, in one pass less over both than a copy before the call.  fhat must be
+ * g itself or not overlap it.  After a validation failure g holds fhat; after an
+ * argument error it is unchanged, after a device error unspecified. */
+int pmsz_correct_from(const pmsz_grid* grid, const void* f, const void* fhat, void* g, double xi,
+                      const uint8_t* dirs_f, int edit_mode, void* ws, size_t ws_bytes,
+                      int64_t max_iters, pmsz_stats* stats, void* stream);
+
 /* Batched correction of n independent fields in one persistent launch.  Each
  * field follows exactly the iteration of pmsz_correct (bit-identical results
  * and statistics); fields retire independently.  fields, stats: host arrays

@@ -33,7 +33,7 @@ STEP_STOP_ON_DONE = 1
 # the last two return strings, the others a status code
 EXPORTS = ("pmsz_workspace_size", "pmsz_directions", "pmsz_correct",
            "pmsz_batched_workspace_size", "pmsz_correct_batched", "pmsz_labels",
-           "pmsz_correct_mode", "pmsz_verify", "pmsz_last_timing", "pmsz_last_rounds",
+           "pmsz_correct_mode", "pmsz_correct_from", "pmsz_verify", "pmsz_last_timing", "pmsz_last_rounds",
            "pmsz_session_workspace_size", "pmsz_field_workspace_size", "pmsz_session_create",
            "pmsz_session_add", "pmsz_session_step", "pmsz_session_sync", "pmsz_session_result",
            "pmsz_session_remove", "pmsz_session_destroy", "pmsz_session_step_ex",
@@ -149,6 +149,8 @@ def load():
     L.pmsz_directions.argtypes = [G, vp, vp, vp]
     L.pmsz_correct.argtypes = [G, vp, vp, dbl, vp, vp, sz, i64, ctypes.POINTER(Stats), vp]
     L.pmsz_correct_mode.argtypes = [G, vp, vp, dbl, vp, ctypes.c_int, vp, sz, i64,
+                                    ctypes.POINTER(Stats), vp]
+    L.pmsz_correct_from.argtypes = [G, vp, vp, vp, dbl, vp, ctypes.c_int, vp, sz, i64,
                                     ctypes.POINTER(Stats), vp]
     L.pmsz_batched_workspace_size.argtypes = [i32, ctypes.POINTER(Field), ctypes.POINTER(sz)]
     L.pmsz_correct_batched.argtypes = [i32, ctypes.POINTER(Field), vp, sz, i64,
@@ -272,7 +274,7 @@ def correct(f, fhat, xi, *, inplace=False, max_iters=DEFAULT_MAX_ITERS, dirs_f=N
             mode="halving"):
     """Correct fhat toward f's topology within |g - f| <= xi.
 
-    mode: "halving" (pmsz_correct) or "targeted" (pmsz_correct_mode with
+    mode: "halving" or "targeted" (pmsz_correct_from with PMSZ_EDIT_HALVING or
     PMSZ_EDIT_TARGETED).  Returns (g, stats).  ``stats['status']`` is "OK",
     "STALLED", "NOT_CONVERGED", "NONFINITE" or "INPUT_BOUND"; argument and
     device errors raise PmszError."""
@@ -280,14 +282,17 @@ def correct(f, fhat, xi, *, inplace=False, max_iters=DEFAULT_MAX_ITERS, dirs_f=N
     _dev(fhat, "fhat")
     if fhat.shape != f.shape or fhat.dtype != f.dtype or fhat.device != f.device:
         raise ValueError("f and fhat must match in shape, dtype and device")
-    g = fhat if inplace else fhat.clone()
+    # the library copies fhat on the way; a tensor in an autograd graph keeps its clone
+    copied = inplace or (fhat.requires_grad and torch.is_grad_enabled())
+    g = (fhat if inplace else fhat.clone()) if copied else torch.empty_like(fhat)
     grid = grid_of(f)
     emode = EDIT_MODES[mode]
     if ws is None:
         ws = workspace(grid, WS_CORRECT_TARGETED if emode else WS_CORRECT, f.device)
     st = Stats()
     dptr = ctypes.c_void_p(_dev(dirs_f, "dirs_f").data_ptr()) if dirs_f is not None else None
-    code = load().pmsz_correct_mode(ctypes.byref(grid), ctypes.c_void_p(f.data_ptr()),
+    code = load().pmsz_correct_from(ctypes.byref(grid), ctypes.c_void_p(f.data_ptr()),
+                                    ctypes.c_void_p((g if copied else fhat).data_ptr()),
                                     ctypes.c_void_p(g.data_ptr()), float(xi), dptr, emode,
                                     ctypes.c_void_p(ws.data_ptr()), ws.numel(), int(max_iters),
                                     ctypes.byref(st), _stream(f))

@@ -381,8 +381,10 @@ size_t batch_stage_bytes(int32_t n) {
 // host staging of batch_stage_bytes(n) bytes, or NULL for this thread's
 // pinned buffer.  timed: record HIP events and the round trace into this
 // thread's timing record (the allocation-free path records neither).
+// src (one field; NULL: g holds fhat): fhat, copied to g on the way.
 int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* ws,
-              pmsz_stats* stats, hipStream_t s, void* stage = nullptr, bool timed = true) {
+              pmsz_stats* stats, hipStream_t s, void* stage = nullptr, bool timed = true,
+              const void* src = nullptr) {
   const int32_t n = (int32_t)P.fd.size();
   char* base = (char*)ws;
   for (int32_t i = 0; i < n; ++i) {
@@ -406,7 +408,16 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
   memcpy(stage, P.fd.data(), up);
   EngineCtl* ctl = (EngineCtl*)(base + P.ctl);
   FieldIter* out = (FieldIter*)(base + P.out);
-  HIP_TRY(engine_zero(base, P.dirs, s));
+  int64_t voxels = 0;
+  for (int32_t i = 0; i < n; ++i) voxels += P.fd[i].geo.n;
+  // Large batches run their tile sweeps as kernels of their own (below); the
+  // first of them then also copies fhat
+  const bool split = voxels >= kSplitVoxels;
+  if (src && !split)
+    HIP_TRY(engine_zero_copy(base, P.dirs, P.fd[0].g, src,
+                             (size_t)voxels * (dtype == PMSZ_F64 ? 8 : 4), s));
+  else
+    HIP_TRY(engine_zero(base, P.dirs, s));
   // proposal keys start unset (all ones)
   if (P.edit_mode) HIP_TRY(engine_fill(base + P.prop, P.total - P.prop, 0xFFFFFFFFu, s));
   HIP_TRY(hipMemcpyAsync(base + P.desc, stage, up, hipMemcpyHostToDevice, s));
@@ -416,6 +427,7 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
   a.stop_host = nullptr;
   a.split_tiles = 0;
   a.tail_ok = n <= 256 ? 1 : 0;
+  a.src = split ? src : nullptr;
   a.fd = (const FieldDesc*)(base + P.desc);
   a.out = out;
   a.nf = n;
@@ -429,11 +441,9 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
   if (timed && (r = timing_events(tm))) return r;
   int grid = 0;
   bool need_dirs = false;
-  int64_t voxels = 0;
   int dims = 0;
   for (int32_t i = 0; i < n; ++i) {
     need_dirs |= !P.fd[i].dirs_given;
-    voxels += P.fd[i].geo.n;
     dims |= P.fd[i].geo.ndim == 3 ? 4 : 2;
   }
   // Directions of f, then the correction loop.  Large batches run the tile
@@ -442,7 +452,6 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
   // each followed by an engine launch that starts with that round's apply;
   // small ones keep the whole loop in one launch (the extra launches would
   // cost more than they save).
-  const bool split = voxels >= kSplitVoxels;
   if (timed) HIP_TRY(hipEventRecord(tm.ev[0], s));
   if (need_dirs) HIP_TRY(engine_dirs(dtype, dims, a.fd, n, P.total_tiles, s));
   if (timed) HIP_TRY(hipEventRecord(tm.ev[1], s));
@@ -899,14 +908,26 @@ int pmsz_correct(const pmsz_grid* grid, const void* f, void* g, double xi,
 int pmsz_correct_mode(const pmsz_grid* grid, const void* f, void* g, double xi,
                       const uint8_t* dirs_f, int edit_mode, void* ws, size_t ws_bytes,
                       int64_t max_iters, pmsz_stats* stats, void* stream) {
+  return pmsz_correct_from(grid, f, g, g, xi, dirs_f, edit_mode, ws, ws_bytes, max_iters, stats,
+                           stream);
+}
+
+int pmsz_correct_from(const pmsz_grid* grid, const void* f, const void* fhat, void* g, double xi,
+                      const uint8_t* dirs_f, int edit_mode, void* ws, size_t ws_bytes,
+                      int64_t max_iters, pmsz_stats* stats, void* stream) {
   if (edit_mode != PMSZ_EDIT_HALVING && edit_mode != PMSZ_EDIT_TARGETED)
     return fail(PMSZ_ERR_INVALID_ARG, "unknown edit mode %d", edit_mode);
   int r = check_grid(grid);
   if (r) return r;
-  if (!f || !g || !ws || !stats) return fail(PMSZ_ERR_INVALID_ARG, "NULL argument");
+  if (!f || !fhat || !g || !ws || !stats) return fail(PMSZ_ERR_INVALID_ARG, "NULL argument");
   if (!isfinite(xi) || xi < 0) return fail(PMSZ_ERR_INVALID_ARG, "xi must be finite and >= 0");
   if (max_iters < 0) return fail(PMSZ_ERR_INVALID_ARG, "max_iters must be >= 0");
   if ((uintptr_t)ws % kAlign) return fail(PMSZ_ERR_INVALID_ARG, "workspace not 256-byte aligned");
+  const size_t field_bytes = (size_t)(grid->nx * grid->ny * grid->nz) *
+                             (grid->dtype == PMSZ_F64 ? 8 : 4);
+  if (fhat != g && (const char*)fhat < (const char*)g + field_bytes &&
+      (const char*)g < (const char*)fhat + field_bytes)
+    return fail(PMSZ_ERR_INVALID_ARG, "fhat overlaps g");
   pmsz_field one;
   one.grid = *grid;
   one.f = f;
@@ -922,7 +943,8 @@ int pmsz_correct_mode(const pmsz_grid* grid, const void* f, void* g, double xi,
     stats->status = r;
     return r;
   }
-  return run_batch(grid->dtype, P, given, ws, stats, (hipStream_t)stream);
+  return run_batch(grid->dtype, P, given, ws, stats, (hipStream_t)stream, nullptr, true,
+                   fhat == g ? nullptr : fhat);
 }
 
 // ---------------------------------------------------------------------------
@@ -1613,6 +1635,7 @@ int pmsz_session_step_ex(pmsz_session* S, int64_t max_rounds, int32_t flags) {
   a.stop_host = S->stop_word;
   // the step's last launch may hand its last rounds to the tail kernel when
   // the step has no round budget (the tail reads the stop words too)
+  a.src = nullptr;
   a.tail_ok = 0;
   const int32_t tail_ok = (max_rounds < 0 && n <= 256) ? 1 : 0;
   // a stop requested before this launch is spent (the host's store is

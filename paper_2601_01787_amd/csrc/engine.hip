@@ -1543,8 +1543,9 @@ __global__ __launch_bounds__(256) void k_dirs_fields(const FieldDesc* fd, int nf
     if (tt >= total_tiles) continue;
     const FieldDesc& d = fd[field_of_tile(fd, nf, tt)];
     if (d.dirs_given || d.geo.ndim != DIM) continue;
-    wave_tile<T, KIND_DIRS, false, DIM>(sm[wave], nullptr, (const T*)d.f, (const T*)nullptr, d.dirs,
-                                        nullptr, T(0), d.geo, (int32_t)(tt - d.tile_base), nullptr);
+    wave_tile<T, KIND_DIRS, false, false, DIM>(sm[wave], nullptr, (const T*)d.f, (const T*)nullptr,
+                                               d.dirs, nullptr, T(0), d.geo,
+                                               (int32_t)(tt - d.tile_base), nullptr, (T*)nullptr);
   }
 }
 
@@ -1562,7 +1563,9 @@ template <class T, int DIM>
 constexpr int sweep_waves() {
   return (sizeof(T) == 4 ? 4 : 3) - (DIM == 3 ? 1 : 0);
 }
-template <class T, int KIND, bool PROP, int DIM>
+// COPY (one field, first round): fhat is read from a.src, and the field's g
+// written from it on the way.
+template <class T, int KIND, bool PROP, bool COPY, int DIM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     sweep_waves<T, DIM>()))) void k_sweep(EngineArgs a) {
   __shared__ WaveLds<T, DIM, true> s_w[4];
@@ -1619,8 +1622,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
       const int32_t tile =
           (int32_t)(first_tile(base + (int64_t)l * W, run) + wave - d.tile_base);
       const LaneCounts c =
-          wave_tile<T, KIND, PROP, DIM>(sm, s_delta, (const T*)d.g, (const T*)d.f, d.dirs, d.bm,
-                                        (T)d.xi_t, d.geo, tile, d.prop);
+          wave_tile<T, KIND, PROP, COPY, DIM>(sm, s_delta, (const T*)(COPY ? a.src : d.g),
+                                              (const T*)d.f, d.dirs, d.bm, (T)d.xi_t, d.geo, tile,
+                                              d.prop, (T*)d.g);
       const unsigned long long t = wave_sum(pack3(c.mism, c.nf, c.nb));
       m += uniform((int32_t)unpack3(t, 0));
       nf += uniform((int32_t)unpack3(t, 1));
@@ -1686,6 +1690,31 @@ hipError_t engine_fill(void* p, size_t bytes, uint32_t v, hipStream_t s) {
 
 hipError_t engine_zero(void* p, size_t bytes, hipStream_t s) { return engine_fill(p, bytes, 0u, s); }
 
+// Zero `words` words of p and copy n elements of V from src to dst.
+template <class V>
+__global__ __launch_bounds__(256) void k_zero_copy(uint32_t* p, int64_t words, V* dst,
+                                                   const V* src, int64_t n) {
+  const int64_t stride = (int64_t)gridDim.x * 256, at = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  for (int64_t i = at; i < n; i += stride) dst[i] = src[i];
+  for (int64_t w = at; w < words; w += stride) p[w] = 0u;
+}
+
+hipError_t engine_zero_copy(void* p, size_t bytes, void* dst, const void* src, size_t copy_bytes,
+                            hipStream_t s) {
+  const int64_t words = (int64_t)(bytes / 4);
+  const bool wide = ((uintptr_t)dst | (uintptr_t)src | copy_bytes) % 16 == 0;
+  const int64_t n = (int64_t)(copy_bytes / (wide ? 16 : 4));
+  int64_t b = ((words > n ? words : n) + 255) / 256;
+  b = b < 1 ? 1 : b < 4096 ? b : 4096;
+  if (wide)
+    hipLaunchKernelGGL(k_zero_copy<uint4>, dim3((unsigned)b), dim3(256), 0, s, (uint32_t*)p, words,
+                       (uint4*)dst, (const uint4*)src, n);
+  else
+    hipLaunchKernelGGL(k_zero_copy<uint32_t>, dim3((unsigned)b), dim3(256), 0, s, (uint32_t*)p,
+                       words, (uint32_t*)dst, (const uint32_t*)src, n);
+  return hipGetLastError();
+}
+
 // Cooperative grid: as many resident blocks as the chip holds, but no more
 // than there is work for (fewer arrivals make the barrier cheaper).
 // Resident blocks per compute unit and compute units of a device, looked up
@@ -1719,34 +1748,35 @@ static hipError_t occupancy(int dev, Occupancy& out) {
 
 // Waves enough to fill the chip kSweepFill times over, at most one per tile.
 constexpr int64_t kSweepFill = 4;
-template <class T, int KIND, bool PROP, int DIM>
+template <class T, int KIND, bool PROP, bool COPY, int DIM>
 static hipError_t sweep_t(const EngineArgs& a, hipStream_t s) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   Occupancy occ;
-  if ((e = occupancy_of((const void*)k_sweep<T, KIND, PROP, DIM>, dev, occ)) != hipSuccess)
+  if ((e = occupancy_of((const void*)k_sweep<T, KIND, PROP, COPY, DIM>, dev, occ)) != hipSuccess)
     return e;
   int64_t grid = kSweepFill * (occ.per_cu > 0 ? occ.per_cu : 1) * (occ.cus > 0 ? occ.cus : 1);
   grid = (grid + kXcds - 1) / kXcds * kXcds;
   if (grid > tile_blocks(a.total_tiles)) grid = tile_blocks(a.total_tiles);
-  hipLaunchKernelGGL((k_sweep<T, KIND, PROP, DIM>), dim3((unsigned)grid), dim3(256), 0, s, a);
+  hipLaunchKernelGGL((k_sweep<T, KIND, PROP, COPY, DIM>), dim3((unsigned)grid), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
-template <class T, int DIM>
-static hipError_t sweep_kind(int kind, bool prop, const EngineArgs& a, hipStream_t s) {
-  if (kind == KIND_FIRST_GIVEN)
-    return prop ? sweep_t<T, KIND_FIRST_GIVEN, true, DIM>(a, s)
-                : sweep_t<T, KIND_FIRST_GIVEN, false, DIM>(a, s);
-  return prop ? sweep_t<T, KIND_NEXT, true, DIM>(a, s) : sweep_t<T, KIND_NEXT, false, DIM>(a, s);
+template <class T, bool PROP, int DIM>
+static hipError_t sweep_kind(int kind, const EngineArgs& a, hipStream_t s) {
+  if (kind != KIND_FIRST_GIVEN) return sweep_t<T, KIND_NEXT, PROP, false, DIM>(a, s);
+  return a.src ? sweep_t<T, KIND_FIRST_GIVEN, PROP, true, DIM>(a, s)
+               : sweep_t<T, KIND_FIRST_GIVEN, PROP, false, DIM>(a, s);
 }
 
 template <class T>
 static hipError_t sweep_dims(int kind, bool prop, int dims, const EngineArgs& a, hipStream_t s) {
   hipError_t e = hipSuccess;
-  if ((dims & 2) && (e = sweep_kind<T, 2>(kind, prop, a, s)) != hipSuccess) return e;
-  if (dims & 4) e = sweep_kind<T, 3>(kind, prop, a, s);
+  if (dims & 2)
+    e = prop ? sweep_kind<T, true, 2>(kind, a, s) : sweep_kind<T, false, 2>(kind, a, s);
+  if (e == hipSuccess && (dims & 4))
+    e = prop ? sweep_kind<T, true, 3>(kind, a, s) : sweep_kind<T, false, 3>(kind, a, s);
   return e;
 }
 

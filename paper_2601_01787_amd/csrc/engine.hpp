@@ -166,6 +166,8 @@ struct EngineArgs {
                          // which a field of kSplitVoxels vertices or more (among
                          // the first 256) sweeps tiles: a sweep kernel takes that
                          // round's tile detection and the next launch the rest
+  const void* src;       // nullable, one field: fhat, for the first sweep to read and to
+                         // write to the field's g (engine_sweep)
   int32_t tail_ok;       // the launch may hand its last rounds to k_tail (at most
                          // 256 fields; the host launches k_tail after it)
 };
@@ -214,6 +216,10 @@ hipError_t engine_apply_first(int dtype, const EngineArgs& a, hipStream_t s);
 // Zero `bytes` bytes (multiple of 4, 4-byte aligned) with a kernel, so that
 // the call can sit inside a captured graph.
 hipError_t engine_zero(void* p, size_t bytes, hipStream_t s);
+// The same, and copy copy_bytes bytes (multiple of 4, 4-byte aligned) from src
+// to dst, in one launch.
+hipError_t engine_zero_copy(void* p, size_t bytes, void* dst, const void* src, size_t copy_bytes,
+                            hipStream_t s);
 // Fill `bytes` bytes (multiple of 4, 4-byte aligned) with the 32-bit word v.
 hipError_t engine_fill(void* p, size_t bytes, uint32_t v, hipStream_t s);
 

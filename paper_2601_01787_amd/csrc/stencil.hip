@@ -13,8 +13,8 @@ __global__ __launch_bounds__(256) void k_dirs(const T* h, TileGeo G, uint8_t* di
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int32_t tile = (int32_t)first_tile(blockIdx.x, run) + wave;
   if (tile >= (int32_t)tile_count(G)) return;
-  wave_tile<T, KIND_DIRS, false, DIM>(sm[wave], nullptr, h, (const T*)nullptr, dirs, nullptr, T(0),
-                                      G, tile, nullptr);
+  wave_tile<T, KIND_DIRS, false, false, DIM>(sm[wave], nullptr, h, (const T*)nullptr, dirs,
+                                             nullptr, T(0), G, tile, nullptr, (T*)nullptr);
 }
 
 // Longer marches than the correction engine's on small fields (no frontier to

@@ -215,6 +215,30 @@ __device__ __forceinline__ void buf_load4(Rsrc r, uint32_t lane_off, double* v) 
   }
 }
 
+__device__ __forceinline__ void buf_store(Rsrc r, uint32_t lane_off, uint32_t line_off, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, lane_off, line_off, 0);
+}
+__device__ __forceinline__ void buf_store(Rsrc r, uint32_t lane_off, uint32_t line_off, double v) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const U32x2 x = {(uint32_t)b, (uint32_t)(b >> 32)};
+  __builtin_amdgcn_raw_buffer_store_b64(x, r, lane_off, line_off, 0);
+}
+__device__ __forceinline__ void buf_store4(Rsrc r, uint32_t lane_off, const float* v) {
+  U32x4 x;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) x[j] = __float_as_uint(v[j]);
+  __builtin_amdgcn_raw_buffer_store_b128(x, r, lane_off, 0, 0);
+}
+__device__ __forceinline__ void buf_store4(Rsrc r, uint32_t lane_off, const double* v) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const unsigned long long a = (unsigned long long)__double_as_longlong(v[2 * h]),
+                             b = (unsigned long long)__double_as_longlong(v[2 * h + 1]);
+    const U32x4 x = {(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)};
+    __builtin_amdgcn_raw_buffer_store_b128(x, r, lane_off + 16u * h, 0, 0);
+  }
+}
+
 // LDS writes of the wave's lanes are visible to its other lanes (they execute
 // in order; the compiler must keep that order).
 __device__ __forceinline__ void wave_lds_fence() {
@@ -286,15 +310,18 @@ __device__ __forceinline__ unsigned flag_mismatch(uint32_t o, uint32_t d, int32_
                          flags, fdelta, PROP ? prop : nullptr, g, lo);
 }
 
-// One 3D tile (tiles.hpp's 64 x 4 x chunk) on one wave.  Arguments as tile3.
+// One 3D tile (tiles.hpp's 64 x 4 x chunk) on one wave.  Arguments as tile3;
+// copy_to (COPY): the tile's values of h go there too (lanes and lines outside
+// the grid repeat the last ones inside).
 // The march visits the planes z0-1 .. z1; the step of plane p completes the
 // boxes between planes p-1 and p, finishes the vertices of plane p-1 and leaves
 // the boxes as lower boxes of plane p.  Loads run two planes ahead.
-template <class T, int KIND, bool PROP, class LDS>
+template <class T, int KIND, bool PROP, bool COPY, class LDS>
 __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta, const T* h_in,
                                                  const T* f_in, uint8_t* dirs_in, uint32_t* bm_in,
                                                  T xi, const TileGeo& G_in, int32_t tile,
-                                                 void* prop_in) {
+                                                 void* prop_in, T* copy_in) {
+  const gptr<T> copy_to = as_global(uniform_ptr(copy_in));
   const TileGeo G = uniform_geo(G_in);
   void* const prop = PROP ? uniform_ptr(prop_in) : nullptr;
   const gptr<const T> h = as_global((const T*)uniform_ptr(h_in));
@@ -435,6 +462,12 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
     for (int r = 0; r < V; ++r)
       xp[r] = x_pair(S.v[r], lane_shift<kFromRight>(S.v[r], E.right[r]),
                      (uint32_t)(2 * (r & 1)) | ZT);
+    if (COPY && MODE != 0) {
+      const Rsrc rc = rsrc_at(copy_to + (plane_at(q) + at0), q < nq - 1);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        buf_store(rc, xb, row[r + 1] * (uint32_t)sizeof(T), S.v[r + 1]);
+    }
     if (kFirst && MODE != 0) {
       // validation of plane q (the last one is the next tile's or absent)
       // (bound_class's fast test for all lines, one branch for the rest)
@@ -545,11 +578,12 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
 // One 2D tile (tiles.hpp's 256-wide strip) on one wave, four columns per lane,
 // marched along y like wave_tile3 along z.  RAGGED: the strip ends inside the tile,
 // and its columns are loaded one by one with clamped offsets.
-template <class T, int KIND, bool PROP, bool RAGGED, class LDS>
+template <class T, int KIND, bool PROP, bool COPY, bool RAGGED, class LDS>
 __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelta, const T* h_in,
                                                    const T* f_in, uint8_t* dirs_in,
                                                    uint32_t* bm_in, T xi, const TileGeo& G,
-                                                   int32_t tile, void* prop_in) {
+                                                   int32_t tile, void* prop_in, T* copy_in) {
+  const gptr<T> copy_to = as_global(uniform_ptr(copy_in));
   void* const prop = PROP ? uniform_ptr(prop_in) : nullptr;
   const gptr<const T> h = as_global((const T*)uniform_ptr(h_in));
   const gptr<const T> f = as_global((const T*)uniform_ptr(f_in));
@@ -649,6 +683,15 @@ __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelt
     XPair<T> xp[C];
 #pragma unroll
     for (int j = 0; j < C; ++j) xp[j] = x_pair(S.v[j], j + 1 < C ? S.v[j + 1] : right, YT);
+    if (COPY && MODE != 0) {
+      const Rsrc rc = rsrc_at(copy_to + (row_at(q) + x0), q < nq - 1);
+      if (RAGGED) {
+#pragma unroll
+        for (int j = 0; j < C; ++j) buf_store(rc, offb[j % NO], 0, S.v[j]);
+      } else {
+        buf_store4(rc, offb[0], S.v);
+      }
+    }
     if (kFirst && MODE != 0) {
       bool near = false;
 #pragma unroll
@@ -755,24 +798,22 @@ __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelt
   return n;
 }
 
-template <class T, int KIND, bool PROP, class LDS>
-__device__ __forceinline__ LaneCounts wave_tile2(LDS& sm, const int32_t* fdelta, const T* h,
-                                                 const T* f, uint8_t* dirs, uint32_t* bm, T xi,
-                                                 const TileGeo& G_in, int32_t tile, void* prop) {
-  const TileGeo G = uniform_geo(G_in);
-  if ((tile % G.tiles_x + 1) * RX > G.nx)
-    return wave_tile2_t<T, KIND, PROP, true>(sm, fdelta, h, f, dirs, bm, xi, G, tile, prop);
-  return wave_tile2_t<T, KIND, PROP, false>(sm, fdelta, h, f, dirs, bm, xi, G, tile, prop);
-}
-
-template <class T, int KIND, bool PROP, int DIM, class LDS>
+template <class T, int KIND, bool PROP, bool COPY, int DIM, class LDS>
 __device__ __forceinline__ LaneCounts wave_tile(LDS& sm, const int32_t* fdelta, const T* h,
                                                 const T* f, uint8_t* dirs, uint32_t* bm, T xi,
-                                                const TileGeo& G, int32_t tile, void* prop) {
-  if constexpr (DIM == 3)
-    return wave_tile3<T, KIND, PROP>(sm, fdelta, h, f, dirs, bm, xi, G, tile, prop);
-  else
-    return wave_tile2<T, KIND, PROP>(sm, fdelta, h, f, dirs, bm, xi, G, tile, prop);
+                                                const TileGeo& G_in, int32_t tile, void* prop,
+                                                T* copy_to) {
+  if constexpr (DIM == 3) {
+    return wave_tile3<T, KIND, PROP, COPY>(sm, fdelta, h, f, dirs, bm, xi, G_in, tile, prop,
+                                           copy_to);
+  } else {
+    const TileGeo G = uniform_geo(G_in);
+    if ((tile % G.tiles_x + 1) * RX > G.nx)
+      return wave_tile2_t<T, KIND, PROP, COPY, true>(sm, fdelta, h, f, dirs, bm, xi, G, tile, prop,
+                                                     copy_to);
+    return wave_tile2_t<T, KIND, PROP, COPY, false>(sm, fdelta, h, f, dirs, bm, xi, G, tile, prop,
+                                                    copy_to);
+  }
 }
 
 }  // namespace pmsz
