@@ -327,11 +327,21 @@ void release_staging(Staging& s) {
 }
 
 // Events around the engine launch and the figures of the last run.
+// Plain rounds of a large batch queued between read-backs.  A plain round with
+// edits takes 25 to 35 us on a 512^3 field (1024 segments), a round of the engine 32 to
+// 47 us, and more with every segment a block has to itself; one with nothing left
+// to do costs two empty launches, about 4 us, and the rounds a field needs grow with
+// it.  Measured with 4 / 6 / 7 / 8 rounds: 257 x 253 x 190 targeted (94 segments) 520 /
+// 532 / 543 / 548 us, 512^3 1463 / 1457 / 1439 / 1433 us.
+constexpr int kPlainRounds = 12;
+inline int plain_rounds_of(int64_t segs) { return segs >= 2048 ? kPlainRounds : segs >= 512 ? 8 : 4; }
+
 struct Timing {
-  // directions, first sweep, first engine launch, second sweep, second
-  // engine launch, end (the sweeps and the first launch only when split);
-  // then around each later sweep and engine launch (large tile rounds)
-  hipEvent_t ev[9] = {};
+  // start, after the directions, after the first sweep (split); start and end of
+  // a later group of launches (kGroup, kGroup + 1); then around the sweep of
+  // each plain round of a group (kSweeps + 2 i, + 1)
+  static constexpr int kGroup = 3, kSweeps = 5;
+  hipEvent_t ev[kSweeps + 2 * kPlainRounds] = {};
   uint64_t gen = 0;
   pmsz_timing last;
   pmsz_round rounds[kTraceRounds];
@@ -428,6 +438,8 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
   a.split_tiles = 0;
   a.tail_ok = n <= 256 ? 1 : 0;
   a.src = split ? src : nullptr;
+  a.plain = 0;
+  a.next_sweep = 0;
   a.fd = (const FieldDesc*)(base + P.desc);
   a.out = out;
   a.nf = n;
@@ -446,48 +458,63 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
     need_dirs |= !P.fd[i].dirs_given;
     dims |= P.fd[i].geo.ndim == 3 ? 4 : 2;
   }
-  // Directions of f, then the correction loop.  Large batches run the tile
-  // detection of rounds 0 and 1 (full sweeps: every tile in round 0, nearly
-  // every one in round 1) as plain kernels at the march's own occupancy,
-  // each followed by an engine launch that starts with that round's apply;
-  // small ones keep the whole loop in one launch (the extra launches would
-  // cost more than they save).
+  // Directions of f, then the correction loop.  Large batches run their first
+  // rounds, and any later round in which a field of kSplitVoxels vertices or more
+  // sweeps tiles, as plain kernels (engine_sweep, engine_sparse, engine_apply):
+  // each runs at its own occupancy, without the engine's register budget.  Small ones
+  // keep the whole loop in one launch (the extra launches would cost more than they
+  // save).
+  constexpr int kGroup = Timing::kGroup, kSweeps = Timing::kSweeps;
   if (timed) HIP_TRY(hipEventRecord(tm.ev[0], s));
   if (need_dirs) HIP_TRY(engine_dirs(dtype, dims, a.fd, n, P.total_tiles, s));
   if (timed) HIP_TRY(hipEventRecord(tm.ev[1], s));
+  auto sweep = [&](int i) -> int {  // of a round's marked tiles
+    if (timed) HIP_TRY(hipEventRecord(tm.ev[kSweeps + 2 * i], s));
+    HIP_TRY(engine_sweep(dtype, KIND_NEXT, P.edit_mode != 0, dims, a, s));
+    if (timed) HIP_TRY(hipEventRecord(tm.ev[kSweeps + 2 * i + 1], s));
+    return PMSZ_OK;
+  };
+  const int n_plain = plain_rounds_of(P.total_segs);
+  // (a few fields are in sparse rounds after their second as a rule: a read-back for
+  // those that are not costs less than a sweep kernel in every round)
+  const bool sweep_all = n > 16;
+  auto plain_rounds = [&]() -> int {
+    for (int i = 0; i < n_plain; ++i) {
+      if ((i == 0 || sweep_all) && (r = sweep(i))) return r;
+      a.next_sweep = sweep_all && i + 1 < n_plain;
+      HIP_TRY(engine_sparse(dtype, dims, a, s));
+      HIP_TRY(engine_apply(dtype, a, s));
+    }
+    return PMSZ_OK;
+  };
   if (split) {
-    a.tiles_swept = 1;
-    a.max_rounds = 1;
     HIP_TRY(engine_sweep(dtype, KIND_FIRST_GIVEN, P.edit_mode != 0, dims, a, s));
     if (timed) HIP_TRY(hipEventRecord(tm.ev[2], s));
-    // round 0's apply pass as a plain kernel; the engine starts at round 1
-    HIP_TRY(engine_apply_first(dtype, a, s));
-    if (timed) HIP_TRY(hipEventRecord(tm.ev[3], s));
+    a.next_sweep = 1;
+    HIP_TRY(engine_apply(dtype, a, s));
     a.has_fresh = 0;
-    a.max_rounds = -1;
-    HIP_TRY(engine_sweep(dtype, KIND_NEXT, P.edit_mode != 0, dims, a, s));
-    if (timed) HIP_TRY(hipEventRecord(tm.ev[4], s));
+    a.plain = 1;
+    a.split_tiles = 1;
+    if ((r = plain_rounds())) return r;
   }
-  // A large batch's later launches end before any round in which a field of
-  // kSplitVoxels vertices or more sweeps tiles; the host then runs that
-  // round's tile detection as a sweep kernel and launches the engine again.
-  a.split_tiles = split ? 1 : 0;
   // (the workspace, barrier state included, was cleared at the start)
   HIP_TRY(engine_launch(dtype, a, s, &grid, false));
   if (a.tail_ok) HIP_TRY(engine_tail(dtype, a, s));
-  if (timed) HIP_TRY(hipEventRecord(tm.ev[5], s));
+  if (timed) HIP_TRY(hipEventRecord(tm.ev[kGroup + 1], s));
   const EngineCtl* hc = (const EngineCtl*)stage;
   // staging: [control block][states, padded as in the workspace][trace]
   const FieldIter* hs = (const FieldIter*)((char*)stage + kCtlHostBytes);
   const unsigned long long* tr =
       (const unsigned long long*)((char*)stage + kCtlHostBytes + (P.trace - P.out));
-  // the sweeps of those later tile rounds: ms by round (timed runs), count
-  float late_ms[kTraceRounds] = {};
-  int64_t late = 0;
-  unsigned long long late_round = 0;
-  float late_sweep_ms = 0.f, late_engine_ms = 0.f;
-  int32_t tail_rounds = 0, handbacks = 0;
-  for (;;) {
+  // sweeps: ms of the first, and by round of those that the round's record does
+  // not hold (after a read-back; timed runs)
+  float first_ms = 0.f, late_ms[kTraceRounds] = {};
+  bool late_only[kTraceRounds] = {};
+  double sweep_ms = 0., engine_ms = 0.;
+  int32_t sweeps = split ? 1 : 0, tail_rounds = 0, handbacks = 0;
+  int group_sweeps = split ? n_plain : 0;  // of the group of launches just read back
+  unsigned long long group_round = split ? 1 : 0;  // the round of the first of them
+  for (int64_t group = 0;; ++group) {
     // the staging buffer is reused for the results: the upload above is
     // stream-ordered before this copy, so it has been consumed
     HIP_TRY(hipMemcpyAsync(stage, ctl, kCtlHostBytes, hipMemcpyDeviceToHost, s));
@@ -501,13 +528,30 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
       tail_rounds += (int32_t)hc->rounds;
       handbacks += hc->handoff == kHandToEngine ? 1 : 0;
     }
-    if (late > 0 && timed) {
-      float ms = 0.f;
-      HIP_TRY(hipEventElapsedTime(&ms, tm.ev[6], tm.ev[7]));
-      if (late_round < (unsigned long long)kTraceRounds) late_ms[late_round] += ms;
-      late_sweep_ms += ms;
-      HIP_TRY(hipEventElapsedTime(&ms, tm.ev[7], tm.ev[8]));
-      late_engine_ms += ms;
+    if (timed) {
+      float all = 0.f, ms = 0.f;
+      HIP_TRY(hipEventElapsedTime(&all, tm.ev[group ? kGroup : 1], tm.ev[kGroup + 1]));
+      if (group == 0 && split) {
+        HIP_TRY(hipEventElapsedTime(&first_ms, tm.ev[1], tm.ev[2]));
+        sweep_ms += first_ms;
+        all -= first_ms;
+      }
+      for (int i = 0; i < group_sweeps; ++i) {
+        const unsigned long long E = group_round + (unsigned long long)i;
+        // (a plain round without tiles to sweep: no sweep to count)
+        if ((i > 0 && !sweep_all) || E >= hc->epoch || E >= (unsigned long long)kTraceRounds ||
+            tr[kTraceSlots * E + 3] == tr[kTraceSlots * E + 6])
+          continue;
+        HIP_TRY(hipEventElapsedTime(&ms, tm.ev[kSweeps + 2 * i], tm.ev[kSweeps + 2 * i + 1]));
+        sweep_ms += ms;
+        all -= ms;
+        ++sweeps;
+        if (group && i == 0) {
+          late_ms[E] = ms;
+          late_only[E] = split;  // (its record starts before the read-back)
+        }
+      }
+      engine_ms += all;
     }
     bool running = false;
     for (int32_t i = 0; i < n && !running; ++i) running = !hs[i].done;
@@ -515,17 +559,19 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
     // the launches ended before a round with tile sweeps: a large one (split
     // batches), or one after the tail (k_tail handed the loop back)
     if (!split && hc->handoff != kHandToEngine) break;
-    ++late;
-    late_round = hc->epoch;
-    a.tiles_swept = 1;
     a.has_fresh = 0;
-    a.max_rounds = -1;
-    if (timed) HIP_TRY(hipEventRecord(tm.ev[6], s));
-    HIP_TRY(engine_sweep(dtype, KIND_NEXT, P.edit_mode != 0, dims, a, s));
-    if (timed) HIP_TRY(hipEventRecord(tm.ev[7], s));
+    group_round = hc->epoch;
+    group_sweeps = split ? n_plain : 1;
+    if (timed) HIP_TRY(hipEventRecord(tm.ev[kGroup], s));
+    if (split) {
+      if ((r = plain_rounds())) return r;
+    } else {
+      a.tiles_swept = 1;
+      if ((r = sweep(0))) return r;
+    }
     HIP_TRY(engine_launch(dtype, a, s, &grid));
     if (a.tail_ok) HIP_TRY(engine_tail(dtype, a, s));
-    if (timed) HIP_TRY(hipEventRecord(tm.ev[8], s));
+    if (timed) HIP_TRY(hipEventRecord(tm.ev[kGroup + 1], s));
   }
   if (!timed) {
     int first = PMSZ_OK;
@@ -537,20 +583,15 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
     if (first != PMSZ_OK) return fail(first, "%s", pmsz_status_string(first));
     return PMSZ_OK;
   }
-  float el[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-  HIP_TRY(hipEventElapsedTime(&el[0], tm.ev[0], tm.ev[1]));
-  if (split) {
-    for (int k = 1; k < 5; ++k) HIP_TRY(hipEventElapsedTime(&el[k], tm.ev[k], tm.ev[k + 1]));
-  } else {
-    HIP_TRY(hipEventElapsedTime(&el[4], tm.ev[1], tm.ev[5]));
-  }
+  float dirs_ms = 0.f;
+  HIP_TRY(hipEventElapsedTime(&dirs_ms, tm.ev[0], tm.ev[1]));
   memset(&tm.last, 0, sizeof(tm.last));
-  tm.last.dirs_ms = el[0];
-  tm.last.sweep_ms = el[1] + el[3] + late_sweep_ms;
-  tm.last.sweeps = split ? 2 + late : 0;
+  tm.last.dirs_ms = dirs_ms;
+  tm.last.sweep_ms = sweep_ms;
+  tm.last.sweeps = sweeps;
   tm.last.tail_rounds = tail_rounds;
   tm.last.handbacks = handbacks;
-  tm.last.engine_ms = el[2] + el[4] + late_engine_ms;
+  tm.last.engine_ms = engine_ms;
   tm.last.rounds = (int64_t)hc->epoch;  // the workspace starts every call at round 0
   tm.last.tiles = P.total_tiles;
   tm.last.grid = grid;
@@ -568,8 +609,9 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
       o.flagged = (int64_t)t[4];
       o.edits = (int64_t)t[5];
       o.sparse = (int64_t)t[6];
-      if (split && r < 2) o.detect_ms += (double)el[r == 0 ? 1 : 3];  // the sweep kernel
-      o.detect_ms += (double)late_ms[r];  // a later round's sweep kernel
+      if (r == 0) o.detect_ms += (double)first_ms;  // the first sweep
+      if (late_only[r]) o.detect_ms = 0.;
+      o.detect_ms += (double)late_ms[r];  // a sweep after a read-back
       if (r == 0) {
         tm.last.first_round_ms = o.detect_ms + o.apply_ms;
       } else {
@@ -1636,6 +1678,8 @@ int pmsz_session_step_ex(pmsz_session* S, int64_t max_rounds, int32_t flags) {
   // the step's last launch may hand its last rounds to the tail kernel when
   // the step has no round budget (the tail reads the stop words too)
   a.src = nullptr;
+  a.plain = 0;
+  a.next_sweep = 0;
   a.tail_ok = 0;
   const int32_t tail_ok = (max_rounds < 0 && n <= 256) ? 1 : 0;
   // a stop requested before this launch is spent (the host's store is

@@ -195,7 +195,7 @@ __device__ __forceinline__ void xcd_sync(EngineCtl* ctl, const XcdBar& xb, unsig
 // agent-scope acquire also drops the XCD's L2: every line read after it came
 // from HBM at about 2 us, against about 0.12 us for a device-scope load that
 // hits the L2, measured between two units of one XCD.)
-__device__ __noinline__ void tail_sync(EngineCtl* ctl, const XcdBar& xb, unsigned& gen) {
+__device__ __forceinline__ void tail_sync(EngineCtl* ctl, const XcdBar& xb, unsigned& gen) {
   __builtin_amdgcn_s_waitcnt(0);  // this wave's stores are complete in L2
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -1085,6 +1085,347 @@ __device__ __forceinline__ void apply_unit(const EngineArgs& a, int64_t u, int p
   }
 }
 
+// ---------------------------------------------------------------------------
+// Apply pass of a plain round (engine_round), by waves.  A wave takes runs of
+// 256-word units of the flag bitmaps (four words per lane, the next unit's
+// loads in flight), or of 16-word units where there are fewer large ones than
+// waves (small fields: each wave's edits are one chain).  Targets of sparse units gather in an LDS list of the wave's and are
+// edited 64 at a time when it is full, the field changes or the wave is done; a
+// unit with more targets than the list holds is edited in place, 64
+// consecutive vertices at a time.
+//
+// What bounds the pass is memory: a sparse round reads the bitmap, and each
+// edit touches a line of f and of g.  With a block per 4096-word segment, every
+// segment with a target paid its own chain of dependent round trips (words,
+// list slot, values, activity bytes, counters: 10 to 14 us); a
+// 1024 x 1024 x 768 binary64 field has eight segments per block, and its rounds of a
+// few thousand edits took 0.11 to 0.14 ms.
+// ---------------------------------------------------------------------------
+constexpr int kUnitWords = 256;
+constexpr int kWaveList = kApplyCap / 4;
+constexpr int kSmallUnit = kWaveList / 32;  // words that fit the list whatever they hold
+
+// What a wave needs of the field it works on, in scalar registers.
+template <class T>
+struct ApplyField {
+  gptr<const T> f;
+  gptr<T> g;
+  gptr<uint32_t> bm, tlist;
+  gptr<uint8_t> nxt;
+  gptr<FieldCtr> cq;
+  void* prop;
+  const FieldDesc* d;
+  T xi;
+  int64_t slice;
+  int32_t words;
+  int nls;
+  bool edit;
+};
+
+// One edit: the value of target t, or its old one; counts what happened.
+template <class T>
+__device__ __forceinline__ T edited_value(const ApplyField<T>& F, T gt, T ft, T pv, bool& above) {
+  const T lb = lower_bound<T>(ft, F.xi);
+  above = gt > lb;
+  if (!(above && F.edit)) return gt;
+  if (F.prop) return pv > lb ? pv : lb;  // the smallest proposal, never below the bound
+  return halving_edit<T>(gt, lb);
+}
+
+// Edit the n targets of the wave's list.
+template <class T>
+__device__ __forceinline__ void apply_list(const ApplyField<T>& F, const uint32_t* list, int n,
+                                           int slot, unsigned& at_lb, unsigned& edits) {
+  const int lane = threadIdx.x & 63;
+  constexpr int U = kEditUnroll;
+  using K = decltype(prop_key(T(0)));
+  long long lbase = 0;
+  if (F.edit && lane == 0)
+    lbase = (long long)__hip_atomic_fetch_add(&F.cq->s[slot].nlist, (unsigned long long)n,
+                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  bool based = false;
+  for (int j0 = lane; j0 < n; j0 += 64 * U) {
+    int32_t t[U];
+    T gt[U], ft[U], pv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] = (int32_t)list[j0 + 64 * u < n ? j0 + 64 * u : j0];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      gt[u] = F.g[t[u]];
+      ft[u] = F.f[t[u]];
+      pv[u] = F.prop ? prop_value(*((gptr<K>)F.prop + t[u])) : T(0);
+    }
+    if (!based) {  // (its round trip overlaps the first gathers')
+      lbase = __shfl(lbase, 0, 64);
+      based = true;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + 64 * u;
+      if (j >= n) break;
+      bool above;
+      const T v = edited_value<T>(F, gt[u], ft[u], pv[u], above);
+      if (above && F.edit) F.g[t[u]] = v;
+      if (F.prop) *((gptr<K>)F.prop + t[u]) = ~K(0);  // unset for the next round
+      edits += above && F.edit ? 1u : 0u;
+      at_lb += above ? 0u : 1u;
+      if (F.edit) {
+        if (lbase + j < F.slice) F.tlist[(int64_t)slot * F.slice + lbase + j] = (uint32_t)t[u];
+        mark_box(*F.d, box_of(F.d->geo, t[u]), F.nxt);
+      }
+    }
+  }
+}
+
+// Mark the tiles within one vertex of the vertices v0 .. v1.
+__device__ __forceinline__ void mark_range(const TileGeo& G, int32_t v0, int32_t v1,
+                                           gptr<uint8_t> nxt) {
+  const int32_t r0 = fdiv(v0, G.div_nx), r1 = fdiv(v1, G.div_nx);  // y + ny z
+  int32_t xl = 0, xh = G.nx - 1, yl = r0, yh = r1, zl = 0, zh = 0;
+  if (r0 == r1) {
+    xl = v0 - r0 * G.nx;
+    xh = v1 - r0 * G.nx;
+  }
+  if (G.ndim == 3) {
+    zl = fdiv(r0, G.div_ny);
+    zh = fdiv(r1, G.div_ny);
+    yl = zl == zh ? r0 - zl * G.ny : 0;
+    yh = zl == zh ? r1 - zl * G.ny : G.ny - 1;
+  }
+  auto below = [](int32_t v) { return v > 0 ? v - 1 : 0; };
+  auto above = [](int32_t v, int32_t n) { return v + 1 < n ? v + 1 : v; };
+  xl = below(xl), xh = above(xh, G.nx), yl = below(yl), yh = above(yh, G.ny);
+  int32_t ax, bx, ay, by, az = 0, bz = 0;
+  if (G.ndim == 3) {
+    ax = xl / TX, bx = xh / TX, ay = yl / TY, by = yh / TY;
+    az = fdiv(below(zl), G.div_chunk), bz = fdiv(above(zh, G.nz), G.div_chunk);
+  } else {
+    ax = xl / RX, bx = xh / RX, ay = fdiv(yl, G.div_chunk), by = fdiv(yh, G.div_chunk);
+  }
+  const int32_t wx = bx - ax + 1, wy = by - ay + 1, wz = bz - az + 1;
+  for (int32_t i = threadIdx.x & 63; i < wx * wy * wz; i += 64) {
+    const int32_t x = ax + i % wx, y = ay + i / wx % wy, z = az + i / (wx * wy);
+    nxt[x + G.tiles_x * (y + G.tiles_y * z)] = 1;
+  }
+}
+
+// Edit a unit's targets in place: words w of lane l are w0 + 4 l .., 64
+// consecutive vertices per step, loads and stores masked by their offsets.
+template <class T>
+__device__ __forceinline__ void apply_dense(const ApplyField<T>& F, int32_t w0, const U32x4 w,
+                                            int total, int slot, unsigned& at_lb,
+                                            unsigned& edits) {
+  const int lane = threadIdx.x & 63;
+  const int32_t v0 = w0 * 32;
+  constexpr uint32_t S = (uint32_t)sizeof(T);
+  const Rsrc rg = rsrc_at(F.g + v0), rf = rsrc_at(F.f + v0),
+             rp = rsrc_at((gptr<T>)F.prop + v0, F.prop != nullptr);
+  long long at = 0;
+  if (F.edit) {
+    if (lane == 0)
+      at = (long long)__hip_atomic_fetch_add(&F.cq->s[slot].nlist, (unsigned long long)total,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    at = __shfl(at, 0, 64);
+    const int32_t n = F.d->geo.n;
+    mark_range(F.d->geo, v0, v0 + 32 * kUnitWords < n ? v0 + 32 * kUnitWords - 1 : n - 1, F.nxt);
+  }
+  unsigned n_above = 0, n_all = 0;
+  for (int l = 0; l < 64; l += 2) {
+    unsigned long long m[4];
+    uint32_t off[4];
+    T gt[4], ft[4], pv[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)w[2 * (k & 1)], l + (k >> 1));
+      const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)w[2 * (k & 1) + 1], l + (k >> 1));
+      m[k] = ((unsigned long long)b << 32) | a;
+      off[k] = (m[k] >> lane) & 1ull ? (uint32_t)(128 * l + 64 * k + lane) * S : kNoStore;
+      buf_load(rg, off[k], 0, gt[k]);
+      buf_load(rf, off[k], 0, ft[k]);
+      pv[k] = T(0);
+      if (F.prop) buf_load(rp, off[k], 0, pv[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const bool mine = off[k] != kNoStore;
+      bool above;
+      using K = decltype(prop_key(T(0)));
+      const T v = edited_value<T>(F, gt[k], ft[k],
+                                  F.prop ? prop_value((K)FP<T>::bits(pv[k])) : T(0), above);
+      const unsigned long long up = __ballot(mine && above);
+      buf_store(rg, mine && above && F.edit ? off[k] : kNoStore, 0, v);
+      if (F.prop) buf_store(rp, off[k], 0, FP<T>::from(~typename FP<T>::U(0)));
+      n_above += (unsigned)__builtin_popcountll(up);
+      n_all += (unsigned)__builtin_popcountll(m[k]);
+      if (F.edit && at < F.slice) {
+        const int64_t i = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m[k] >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m[k], 0));
+        if (mine && i < F.slice)
+          F.tlist[(int64_t)slot * F.slice + i] = (uint32_t)(v0 + 128 * l + 64 * k + lane);
+        at += __builtin_popcountll(m[k]);
+      }
+    }
+  }
+  if (lane == 0) {
+    edits += F.edit ? n_above : 0u;
+    at_lb += n_all - n_above;
+  }
+}
+
+// The apply pass of a round (parity p, counter set q) on the whole grid.  list:
+// kWaveList words per wave; fin, sums: one slot per wave.  Ends with the block in
+// step.
+template <class T>
+__device__ __forceinline__ void apply_pass(const EngineArgs& a, int p, int q, uint32_t* list_all,
+                                           int* fin, unsigned long long (*sums)[3]) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  uint32_t* const list = list_all + wave * kWaveList;
+  EngineCtl* const ctl = a.ctl;
+  const int64_t waves = (int64_t)gridDim.x * 4;
+  const bool wide = a.total_segs * (kSegWords / kUnitWords) >= waves;
+  const int32_t unit = wide ? kUnitWords : kSmallUnit;
+  const int32_t per_seg = (int32_t)kSegWords / unit;
+  const int64_t units = a.total_segs * per_seg;
+  // units of a run: as many as share the waves evenly, within one segment
+  int run_log = 0;
+  while ((1 << run_log) < per_seg && units >> (run_log + 1) >= waves) ++run_log;
+  const int64_t runs = units >> run_log;
+  ApplyField<T> F{};
+  int cur = -1, fill = 0, slot = 0;
+  int64_t seg0 = 0, seg1 = 0;  // the field's segments
+  bool idle = true;            // nothing to apply in it
+  unsigned nflag = 0, at_lb = 0, edits = 0;
+  unsigned long long c_flag = 0, c_lb = 0, c_ed = 0;
+  auto flush = [&]() {
+    wave_lds_fence();
+    if (fill) apply_list<T>(F, list, fill, slot, at_lb, edits);
+    wave_lds_fence();
+    fill = 0;
+  };
+  auto add_counts = [&](int fi, unsigned long long nf_, unsigned long long al_,
+                        unsigned long long ed_) {
+    const gptr<FieldCtr> cq = &as_global(a.fd[fi].st)->c[q];
+    const int cs = ctr_slot();
+    if (nf_) {
+      relaxed_add(&cq->s[cs].nflag, nf_);
+      atomicAdd(&ctl->tot[q][cs].flagged, nf_);
+    }
+    if (al_) relaxed_add(&cq->s[cs].at_lb, al_);
+    if (ed_) atomicAdd(&ctl->tot[q][cs].edits, ed_);
+  };
+  auto sum_counts = [&]() {  // of the current field, into c_*
+    c_flag = wave_sum((unsigned long long)nflag);
+    c_lb = wave_sum((unsigned long long)at_lb);
+    c_ed = wave_sum((unsigned long long)edits);
+    nflag = at_lb = edits = 0;
+  };
+  for (int64_t r = (int64_t)blockIdx.x * 4 + wave; r < runs; r += waves) {
+    const int64_t u0 = r << run_log, sg = u0 / per_seg;
+    if (cur < 0 || sg < seg0 || sg >= seg1) {
+      flush();
+      if (cur >= 0) {
+        sum_counts();
+        if (lane == 0) add_counts(cur, c_flag, c_lb, c_ed);
+      }
+      cur = __builtin_amdgcn_readfirstlane(field_of_seg(a.fd, a.nf, sg));
+      const FieldDesc& d = a.fd[cur];
+      F.d = &d;
+      F.words = uniform((int32_t)d.words);
+      seg0 = d.seg_base;
+      seg1 = seg0 + (F.words + kSegWords - 1) / kSegWords;
+      const gptr<FieldState> st = as_global(uniform_ptr(d.st));
+      // the state at the start of the round (persisted before this pass)
+      const FieldIter s = load_iter(&st->s[p]);
+      F.cq = &st->c[q];
+      bool bad = false;
+      if (!s.started) {
+        const CtrSum cs = load_ctr((gptr<const FieldCtr>)F.cq);
+        bad = cs.bad_nf || cs.bad_b;
+      }
+      idle = uniform((int32_t)(s.done || bad || load_mism((gptr<const FieldCtr>)F.cq) == 0)) != 0;
+      F.edit = uniform((int32_t)((long long)s.k < d.max_iters)) != 0;
+      F.f = as_global((const T*)uniform_ptr(d.f));
+      F.g = as_global((T*)uniform_ptr(d.g));
+      F.bm = as_global(uniform_ptr(d.bm));
+      F.tlist = as_global(uniform_ptr(d.list));
+      F.nxt = as_global(uniform_ptr(d.act)) + (p ^ 1) * tile_count(d.geo);
+      F.prop = uniform_ptr(d.prop);
+      F.xi = (T)d.xi_t;
+      F.nls = list_slices(F.words);
+      F.slice = uniform(d.list_cap) / F.nls;
+    }
+    if (idle) continue;
+    const int32_t seg = (int32_t)(sg - seg0);
+    int32_t w0 = seg * (int32_t)kSegWords + (int32_t)(u0 % per_seg) * unit;
+    const int32_t wl = wide ? 4 * lane : lane;  // this lane's (first) word of a unit
+    // (the bitmap ends on a 256-byte boundary, clear past the field)
+    auto load = [&](int32_t at) {
+      U32x4 x = {0u, 0u, 0u, 0u};
+      if (at + wl < F.words) {
+        if (wide) x = *(gptr<const U32x4>)(F.bm + at + wl);
+        else if (lane < kSmallUnit) x.x = F.bm[at + wl];
+      }
+      return x;
+    };
+    U32x4 next = load(w0);
+    for (int k = 0; k < (1 << run_log); ++k, w0 += unit) {
+      const U32x4 w = next;
+      if (k + 1 < (1 << run_log)) next = load(w0 + unit);
+      const uint32_t any = w.x | w.y | w.z | w.w;
+      if (__ballot(any != 0u) == 0ull) continue;
+      if (any) {
+        if (wide) *(gptr<U32x4>)(F.bm + w0 + wl) = U32x4{0u, 0u, 0u, 0u};
+        else F.bm[w0 + wl] = 0u;
+      }
+      const int cnt = __popc(w.x) + __popc(w.y) + __popc(w.z) + __popc(w.w);
+      nflag += (unsigned)cnt;
+      int incl = cnt;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+      }
+      const int total = __builtin_amdgcn_readlane(incl, 63);
+      if (fill + total > kWaveList) flush();
+      if (fill == 0) slot = seg % F.nls;
+      if (total > kWaveList) {
+        apply_dense<T>(F, w0, w, total, slot, at_lb, edits);
+        continue;
+      }
+      int o = fill + incl - cnt;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        for (uint32_t bits = w[j]; bits; bits &= bits - 1u)
+          list[o++] = (uint32_t)((w0 + wl + j) * 32 + __ffs(bits) - 1);
+      fill += total;
+    }
+  }
+  flush();
+  if (cur >= 0) sum_counts();
+  // one set of atomics for the waves that end on the same field
+  if (lane == 0) {
+    fin[wave] = cur;
+    sums[wave][0] = c_flag;
+    sums[wave][1] = c_lb;
+    sums[wave][2] = c_ed;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int i = 0; i < 4; ++i) {
+      const int f = fin[i];
+      if (f < 0) continue;
+      for (int j = i + 1; j < 4; ++j) {
+        if (fin[j] != f) continue;
+        for (int k = 0; k < 3; ++k) sums[i][k] += sums[j][k];
+        fin[j] = -1;
+      }
+      add_counts(f, sums[i][0], sums[i][1], sums[i][2]);
+    }
+  }
+  __syncthreads();
+}
+
 // Block 0 at the start of round E: persist the field states of round E, clear
 // the next-but-one counters; a field finished at E (stop_on_done) or the
 // host's request ends the launch after this round (every block reads the word
@@ -1130,50 +1471,394 @@ __device__ __forceinline__ void persist_round(const EngineArgs& a, unsigned long
   }
 }
 
-// Round 0's apply pass of a batch whose round-0 tile detection ran as a sweep
-// kernel, as a plain kernel at the apply pass's own occupancy instead of a
-// one-round engine launch: the pass needs no grid barrier of its own, and
-// its scattered gathers want more waves in flight than the engine's register
-// budget allows.  k_first_round_end then does what the engine's block 0 and
-// tracer do at the end of a round, and the engine starts at round 1.
-template <class T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_apply_first(
-    EngineArgs a, int plog) {
-  __shared__ uint32_t s_list[kApplyCap];
-  __shared__ int s_scan[4];
-  __shared__ long long s_lbase;
-  __shared__ unsigned long long red[4];
-  if (a.trace && blockIdx.x == 0 && threadIdx.x == 0) {
-    // round 0 starts here (its detection was the sweep kernel's)
-    const unsigned long long now = wall_clock64();
-    a.trace[kTraceRounds * kTraceSlots] = now;
-    a.trace[0] = now;
-    a.trace[1] = now;
-  }
-  for (int64_t u = blockIdx.x; u < (a.total_segs << plog); u += gridDim.x)
-    apply_unit<T>(a, u, plog, 0, 0, s_list, s_scan, &s_lbase, red);
+// ---------------------------------------------------------------------------
+// Plain rounds (engine_round): the kernels of one round of a large batch, each at
+// its own occupancy, for the round E that the workspace's epoch names.  The
+// detection of fields in tile rounds is k_sweep's, of fields in sparse rounds
+// k_sparse's; k_apply applies, and its last block does what the engine's block 0
+// and tracer do between rounds.  A kernel with nothing to do returns at once.
+// ---------------------------------------------------------------------------
+// k_tail takes the rest of the loop after a round with so many edits: the next
+// one examines at most 15 neighbours per edit, few enough for the blocks of one
+// XCD, and few enough segments to mark for its apply pass.
+__device__ __forceinline__ bool tail_takes(const EngineArgs& a, unsigned long long edited) {
+  return a.tail_ok && a.nf <= 256 &&
+         edited * 15ull <= (unsigned long long)(kTailGrid / 8) * 256ull * kTailExams &&
+         (edited <= (unsigned long long)kTailSegs || a.total_segs <= kTailSegs);
 }
 
-__global__ __launch_bounds__(256) void k_first_round_end(EngineArgs a) {
-  const int fi = blockIdx.x * 256 + threadIdx.x;
-  if (fi < a.nf) {
-    // the state at the start of round 1, as state_at(d, 1, 0) computes it
-    const FieldDesc& d = a.fd[fi];
+// End of a plain round, in one block: the state of every field at round E + 1 and
+// the counters of round E + 2, as persist_round leaves them; the round's record;
+// the epoch.  idle: the plain rounds that follow leave everything as it is, because no
+// field is left running (kAllDone), the tail takes the next rounds (kFewEdits; the
+// engine launch does nothing either in these two cases), or the next round
+// sweeps tiles and its launches have no sweep (kTilesNext).  Other blocks' counts are
+// atomics, read past this unit's caches (ld<true>).
+__device__ __forceinline__ void round_end(const EngineArgs& a, unsigned long long E) {
+  EngineCtl* const ctl = a.ctl;
+  const int tid = threadIdx.x;
+  const int q = (int)(E % 3), qn = (int)((E + 2) % 3);
+  int tiles = 0, sparse = 0;
+  // eight lanes per field, one per counter slot: one round trip, few registers
+  static_assert(kCtrSlots == 8, "a lane per slot");
+  for (int f0 = 0; f0 < a.nf; f0 += 32) {
+    const int fi = f0 + (tid >> 3), k = tid & 7;
+    const bool mine = fi < a.nf;
+    const FieldDesc& d = a.fd[mine ? fi : 0];
     const gptr<FieldState> st = as_global(d.st);
-    store_iter(&st->s[1], state_at(d, 1, 0));
+    const gptr<const CtrSlot> c = &st->c[q].s[k];
+    CtrSum cs{ld<true>(&c->mism), ld<true>(&c->nflag), ld<true>(&c->at_lb), ld<true>(&c->bad_nf),
+              ld<true>(&c->bad_b), ld<true>(&c->swept), ld<true>(&c->nlist)};
+    // a slice of the target list overflowed (sparse_items)
+    int over = cs.nlist > (unsigned long long)(d.list_cap / list_slices(d.words));
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) {
+      cs.mism += __shfl_xor(cs.mism, o, 64);
+      cs.nflag += __shfl_xor(cs.nflag, o, 64);
+      cs.at_lb += __shfl_xor(cs.at_lb, o, 64);
+      cs.bad_nf += __shfl_xor(cs.bad_nf, o, 64);
+      cs.bad_b += __shfl_xor(cs.bad_b, o, 64);
+      cs.swept += __shfl_xor(cs.swept, o, 64);
+      over |= __shfl_xor(over, o, 64);
+    }
+    if (!mine) continue;
+    const gptr<CtrSlot> x = &st->c[qn].s[k];
+    x->mism = x->nflag = x->at_lb = x->bad_nf = x->bad_b = x->swept = x->nlist = 0;
+    if (k != 0) continue;
+    const FieldIter s =
+        next_state(load_iter((gptr<const FieldIter>)&st->s[E & 1]), cs, d.max_iters);
+    store_iter(&st->s[(E + 1) & 1], s);
+    if (s.done) continue;
+    if (over) tiles = 1;
+    else sparse = 1;
   }
-  if (fi == 0) {
-    a.ctl->epoch = 1;
-    a.ctl->rounds = 1;
-    if (a.trace) {
-      unsigned long long* t = a.trace;
-      const RoundTot rt = load_tot(a.ctl, 0);
-      t[2] = wall_clock64();
+  tiles = __syncthreads_or(tiles);
+  sparse = __syncthreads_or(sparse);
+  if (tid < kCtrSlots) {
+    ctl->tot[qn][tid].edits = 0;
+    ctl->tot[qn][tid].swept = 0;
+    ctl->tot[qn][tid].sparse = 0;
+    ctl->tot[qn][tid].flagged = 0;
+  }
+  if (tid == 0) {
+    RoundTot rt{0, 0, 0, 0, {0, 0, 0, 0}};
+#pragma unroll 4
+    for (int k = 0; k < kCtrSlots; ++k) {
+      const gptr<const RoundTot> t = as_global(&ctl->tot[q][k]);
+      rt.edits += ld<true>(&t->edits);
+      rt.swept += ld<true>(&t->swept);
+      rt.sparse += ld<true>(&t->sparse);
+      rt.flagged += ld<true>(&t->flagged);
+    }
+    ctl->epoch = E + 1;
+    ctl->rounds = E + 1;
+    ctl->kinds = (tiles ? kKindTiles : 0) | (sparse ? kKindSparse : 0);
+    ctl->idle = !(tiles || sparse) ? kAllDone
+              : !tiles && tail_takes(a, rt.edits) ? kFewEdits
+              : tiles && !a.next_sweep ? kTilesNext : 0;
+    if (a.trace && E < kTraceRounds) {
+      unsigned long long* t = a.trace + kTraceSlots * E;
+      const unsigned long long now = wall_clock64();
+      t[2] = now;
       t[3] = rt.swept;
       t[4] = rt.flagged;
       t[5] = rt.edits;
       t[6] = rt.sparse;
+      if (E + 1 < kTraceRounds) t[kTraceSlots] = now;  // the next round starts
     }
+  }
+}
+
+// The block that arrives last of the grid, once its own and every other block's
+// stores and atomics are done: the arrival counters of grid_sync, left cleared.
+__device__ __forceinline__ bool last_block(EngineCtl* ctl) {
+  __shared__ int s_last;
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned groups = gridDim.x < (unsigned)kBarGroups ? gridDim.x : (unsigned)kBarGroups;
+    const unsigned grp = blockIdx.x % groups;
+    const unsigned members = gridDim.x / groups + (grp < gridDim.x % groups ? 1u : 0u);
+    auto arrive = [&](BarWord* w, unsigned n) {
+      if (__hip_atomic_fetch_add(&w->v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != n - 1u)
+        return false;
+      __hip_atomic_store(&w->v, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return true;
+    };
+    s_last = arrive(&ctl->bar[grp], members) && arrive(&ctl->bar[kBarGroups], groups);
+  }
+  __syncthreads();
+  return s_last != 0;
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void k_apply(EngineArgs a) {
+  __shared__ uint32_t s_list[kApplyCap];
+  __shared__ int s_fin[4];
+  __shared__ unsigned long long s_sums[4][3];
+  const unsigned long long E = a.ctl->epoch;
+  if (a.ctl->idle) return;
+  if (a.trace && E < kTraceRounds && blockIdx.x == 0 && threadIdx.x == 0) {
+    const unsigned long long now = wall_clock64();
+    if (E == 0) {  // round 0 starts here (its detection is timed by its sweep)
+      a.trace[kTraceRounds * kTraceSlots] = now;
+      a.trace[0] = now;
+    }
+    a.trace[kTraceSlots * E + 1] = now;
+  }
+  apply_pass<T>(a, (int)(E & 1), (int)(E % 3), s_list, s_fin, s_sums);
+  if (last_block(a.ctl)) round_end(a, E);
+}
+
+// Sparse examination of a plain round: the vertices to examine are the
+// neighbours of the listed targets (15 in 3D, 7 in 2D, with the target), and
+// what decides them lies within two steps of the target: 65 vertices (19),
+// which 15 gathers per examined vertex would read 225 times (49).  Sixteen
+// (eight) lanes share a target: they stage its surroundings as a 5 x 5 x 5 box in
+// LDS, five (three) loads each, and examine one vertex each from there.  The loads
+// of the plain gather kept the units' address path busy: 30 M examinations of a
+// 1024 x 1024 x 768 binary64 field took 1.6 ms.
+constexpr int kBoxN3 = 65, kBoxN2 = 19;
+// Box offsets in staging order: coordinates + 2, three bits each.
+struct BoxTable {
+  uint16_t v[kBoxN3];
+};
+template <int DIM>
+constexpr BoxTable make_box_table() {
+  BoxTable t{};
+  int n = 0;
+  for (int z = DIM == 3 ? -2 : 0; z <= (DIM == 3 ? 2 : 0); ++z)
+    for (int y = -2; y <= 2; ++y)
+      for (int x = -2; x <= 2; ++x) {
+        const int lo = x < y ? (x < z ? x : z) : (y < z ? y : z);
+        const int hi = x > y ? (x > z ? x : z) : (y > z ? y : z);
+        // a sum of two offsets, each all >= 0 or all <= 0
+        if (!(lo < 0 && hi > 0) || (lo == -1 && hi == 1))
+          t.v[n++] = (uint16_t)((x + 2) | ((y + 2) << 3) | ((z + 2) << 6));
+      }
+  return t;
+}
+__constant__ BoxTable kBox3 = make_box_table<3>();
+__constant__ BoxTable kBox2 = make_box_table<2>();
+
+template <int DIM>
+struct ExamGeo {
+  static constexpr int L = DIM == 3 ? 16 : 8;           // lanes per target
+  static constexpr int N = DIM == 3 ? kBoxN3 : kBoxN2;  // vertices staged
+  static constexpr int B = DIM == 3 ? 128 : 32;         // box stride in LDS (125, 25)
+  static constexpr int K = (N + L - 1) / L;             // loads per lane
+  static constexpr int A = 64 / L;                      // targets at once
+};
+// This lane's vertices of the box.
+template <int DIM>
+struct BoxLane {
+  uint32_t c[ExamGeo<DIM>::K];
+};
+template <int DIM>
+__device__ __forceinline__ BoxLane<DIM> box_lane() {
+  using X = ExamGeo<DIM>;
+  BoxLane<DIM> b;
+  const int me = threadIdx.x & (X::L - 1);
+#pragma unroll
+  for (int i = 0; i < X::K; ++i)
+    b.c[i] = (DIM == 3 ? kBox3 : kBox2).v[me + X::L * i < X::N ? me + X::L * i : X::N - 1];
+  return b;
+}
+
+// The k-th listed target (the last one past the end).
+__device__ __forceinline__ int32_t listed_target(const FieldDesc& d, uint32_t k, uint32_t n,
+                                                 const uint32_t* cnt) {
+  uint32_t kk = k < n ? k : n - 1u, at = 0;
+  const uint32_t slice = (uint32_t)(d.list_cap / list_slices(d.words));
+#pragma unroll
+  for (int i = 0; i < kCtrSlots - 1; ++i) {
+    const uint32_t ci = cnt[i];
+    const bool past = at == (uint32_t)i * slice && kk >= ci;
+    kk -= past ? ci : 0u;
+    at += past ? slice : 0u;
+  }
+  return (int32_t)as_global((const uint32_t*)d.list)[at + kk];
+}
+
+// Examine the surroundings of target t (one per ExamGeo::L lanes; have: there is
+// one).
+template <class T, int DIM>
+__device__ __forceinline__ unsigned examine_target(const FieldDesc& d, const TileGeo& G, int32_t t,
+                                                   bool have, const BoxLane<DIM>& lanes, T* box) {
+  using GX = ExamGeo<DIM>;
+  constexpr int L = GX::L, N = GX::N;
+  const int lane = threadIdx.x & 63, me = lane & (L - 1);
+  const int32_t row = fdiv(t, G.div_nx);  // y + ny z
+  const int32_t x = t - row * G.nx;
+  const int32_t z = DIM == 3 ? fdiv(row, G.div_ny) : 0;
+  const int32_t y = row - z * G.ny;
+  const gptr<const T> g = as_global((const T*)uniform_ptr(d.g));
+  T* const mine = box + lane / L * GX::B;
+  T val[GX::K];
+#pragma unroll
+  for (int i = 0; i < GX::K; ++i) {
+    const int32_t c = (int32_t)lanes.c[i];
+    const int32_t dx = (c & 7) - 2, dy = ((c >> 3) & 7) - 2, dz = DIM == 3 ? (c >> 6) - 2 : 0;
+    const bool in = (uint32_t)(x + dx) < (uint32_t)G.nx && (uint32_t)(y + dy) < (uint32_t)G.ny &&
+                    (DIM == 2 || (uint32_t)(z + dz) < (uint32_t)G.nz);
+    const int32_t v = t + dx + dy * G.nx + (DIM == 3 ? dz * G.sxy : 0);
+    val[i] = g[in ? v : t];
+    if (!in) val[i] = T(__builtin_nan(""));
+  }
+  // the vertex examined: code 0 (the target), 1..7, 9..15; 2D 1..3, 9..11
+  constexpr int M = DIM == 3 ? 15 : 7;
+  const int j = me < M ? me : 0;
+  const int code = DIM == 3 ? (j < 8 ? j : j + 1) : (j < 4 ? j : j + 5);
+  const int mm = code & 7, sg = (code & 8) ? -1 : 1;
+  const int32_t ox = sg * (mm & 1), oy = sg * ((mm >> 1) & 1), oz = sg * ((mm >> 2) & 1);
+  const int32_t X = x + ox, Y = y + oy, Z = z + oz;
+  const bool look = have && me < M && X >= G.cx0 && X < G.cx1 && Y >= G.cy0 && Y < G.cy1 &&
+                    Z >= G.cz0 && Z < G.cz1;
+  const int32_t v = t + code_offset(G, code);
+  int d8 = 0;
+  if (look) d8 = as_global((const uint8_t*)d.dirs)[v];
+#pragma unroll
+  for (int i = 0; i < GX::K; ++i) {
+    const uint32_t c = lanes.c[i];
+    if (me + L * i < N)
+      mine[(c & 7) + 5 * ((c >> 3) & 7) + (DIM == 3 ? 25 * (c >> 6) : 0)] = val[i];
+  }
+  wave_lds_fence();
+  unsigned found = 0;
+  if (look) {
+    const T* const at0 = mine + (ox + 2) + 5 * (oy + 2) + (DIM == 3 ? 25 * (oz + 2) : 0);
+    auto up = [&](int bx, int by, int bz) {
+      return ext_of(at0[bx + 5 * by + 25 * bz], bx | (by << 1) | (bz << 2));
+    };
+    auto dn = [&](int bx, int by, int bz) {  // the vertex (1-bx, 1-by, 1-bz) back
+      const int m = (1 - bx) | ((1 - by) << 1) | (DIM == 3 ? (1 - bz) << 2 : 0);
+      return ext_of(at0[-((1 - bx) + 5 * (1 - by) + (DIM == 3 ? 25 * (1 - bz) : 0))],
+                    m ? (8 | m) : 0);
+    };
+    Ext<T> e;
+    if constexpr (DIM == 3) {
+      const Ext<T> U = merge_up(merge_up(merge_up(up(0, 0, 0), up(1, 0, 0)),
+                                         merge_up(up(0, 1, 0), up(1, 1, 0))),
+                                merge_up(merge_up(up(0, 0, 1), up(1, 0, 1)),
+                                         merge_up(up(0, 1, 1), up(1, 1, 1))));
+      const Ext<T> D = merge_dn(merge_dn(merge_dn(dn(0, 0, 0), dn(1, 0, 0)),
+                                         merge_dn(dn(0, 1, 0), dn(1, 1, 0))),
+                                merge_dn(merge_dn(dn(0, 0, 1), dn(1, 0, 1)),
+                                         merge_dn(dn(0, 1, 1), dn(1, 1, 1))));
+      e = merge_up(D, U);
+    } else {
+      const Ext<T> U = merge_up(merge_up(up(0, 0, 0), up(1, 0, 0)),
+                                merge_up(up(0, 1, 0), up(1, 1, 0)));
+      const Ext<T> D = merge_dn(merge_dn(dn(0, 0, 0), dn(1, 0, 0)),
+                                merge_dn(dn(0, 1, 0), dn(1, 1, 0)));
+      e = merge_up(D, U);
+    }
+    const int fa = d8 & 15, fd = d8 >> 4;
+    const gptr<uint32_t> bm = as_global(d.bm);
+    // targets are neighbours of v, inside the box for directions made by the
+    // direction pass; the range check only guards the bitmap
+    if (e.ca != fa) {
+      const int32_t tt = v + code_offset(G, e.ca);
+      if ((uint32_t)tt < (uint32_t)G.n) {
+        __hip_atomic_fetch_or(bm + (tt >> 5), 1u << (tt & 31), __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_AGENT);
+        if (d.prop) {
+          const int32_t c = v + code_offset(G, fa);
+          propose<T>(d.prop, tt, c, g[c]);
+        }
+      }
+      ++found;
+    }
+    if (e.cd != fd) {
+      const int32_t tt = v + code_offset(G, fd);
+      if ((uint32_t)tt < (uint32_t)G.n) {
+        __hip_atomic_fetch_or(bm + (tt >> 5), 1u << (tt & 31), __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_AGENT);
+        if (d.prop) propose<T>(d.prop, tt, v + code_offset(G, e.cd), e.lo);
+      }
+      ++found;
+    }
+  }
+  wave_lds_fence();  // the box is staged anew
+  return found;
+}
+
+template <class T, int DIM>
+__global__ __launch_bounds__(256) void k_sparse(EngineArgs a) {
+  using GX = ExamGeo<DIM>;
+  __shared__ long long s_pre[256];
+  __shared__ uint32_t s_slot[256 * kCtrSlots];
+  __shared__ T s_box[4][GX::A * GX::B];
+  EngineCtl* const ctl = a.ctl;
+  const unsigned long long E = ctl->epoch;
+  if (ctl->idle || !(ctl->kinds & kKindSparse)) return;
+  const int q = (int)(E % 3);
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t grp = (uint32_t)((tid & 63) / GX::L);
+  const BoxLane<DIM> lanes = box_lane<DIM>();
+  for (int f0 = 0; f0 < a.nf; f0 += 256) {
+    // the groups of targets of up to 256 fields form one index space
+    const int fi = f0 + tid;
+    long long groups = 0;
+    if (fi < a.nf && a.fd[fi].geo.ndim == DIM) {
+      const FieldDesc& d = a.fd[fi];
+      const long long items = sparse_items(d, state_at(d, E, E), E, s_slot + tid * kCtrSlots);
+      if (items > 0) {
+        groups = (items / (DIM == 3 ? 15 : 7) + GX::A - 1) / GX::A;
+        if (blockIdx.x == 0) {
+          relaxed_add(&as_global(d.st)->c[q].s[0].swept, (unsigned long long)items);
+          atomicAdd(&ctl->tot[q][0].swept, (unsigned long long)items);
+          atomicAdd(&ctl->tot[q][0].sparse, (unsigned long long)items);
+        }
+      }
+    }
+    const long long total = block_prefix(groups, s_pre);
+    const int nfc = a.nf - f0 < 256 ? a.nf - f0 : 256;
+    int cur = -1;
+    unsigned found = 0;
+    auto flush = [&]() {
+      const unsigned long long w = wave_sum((unsigned long long)found);
+      if (w && (tid & 63) == 0)
+        relaxed_add(&as_global(a.fd[cur].st)->c[q].s[ctr_slot()].mism, w);
+      found = 0;
+    };
+    // a group's field and its targets; the next group's are read while this one's
+    // surroundings are examined
+    struct Group {
+      int f;
+      uint32_t n, k;
+      int32_t t;
+    };
+    auto group_at = [&](long long m) {
+      Group r;
+      r.f = __builtin_amdgcn_readfirstlane(prefix_find(s_pre, nfc, m));
+      const uint32_t* const cnt = s_slot + r.f * kCtrSlots;
+      r.n = 0;
+#pragma unroll
+      for (int i = 0; i < kCtrSlots; ++i) r.n += cnt[i];
+      r.k = (uint32_t)(m - (r.f ? s_pre[r.f - 1] : 0)) * (uint32_t)GX::A + grp;
+      r.t = listed_target(a.fd[f0 + r.f], r.k, r.n, cnt);
+      return r;
+    };
+    long long m = (long long)blockIdx.x * 4 + wave;
+    const long long step = (long long)gridDim.x * 4;
+    Group now{0, 0, 0, 0};
+    if (m < total) now = group_at(m);
+    for (; m < total; m += step) {
+      Group next = now;
+      if (m + step < total) next = group_at(m + step);
+      if (f0 + now.f != cur) {
+        if (cur >= 0) flush();
+        cur = f0 + now.f;
+      }
+      const FieldDesc& d = a.fd[cur];
+      found += examine_target<T, DIM>(d, uniform_geo(d.geo), now.t, now.k < now.n, lanes,
+                                      s_box[wave]);
+      now = next;
+    }
+    if (cur >= 0) flush();
+    __syncthreads();  // s_pre is rewritten by the next group
   }
 }
 
@@ -1303,17 +1988,19 @@ __device__ __forceinline__ int tail_round(const EngineArgs& a, const XcdBar& xb,
   return (edited == 0 || stop_here) ? 1 : 0;
 }
 
-template <class T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 3))) void k_engine(EngineArgs a) {
+// WAVES: waves per SIMD, that is the register budget.
+template <class T, int WAVES>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_engine(
+    EngineArgs a) {
   __shared__ TileLds<T> sm;
   __shared__ unsigned long long red[4];
   __shared__ unsigned long long s_acc[4];
   __shared__ uint16_t s_tiles[256];
   __shared__ long long s_pre[256];
   __shared__ uint32_t s_slot[256 * kCtrSlots];
-  __shared__ long long s_lbase;
   __shared__ uint32_t s_list[kApplyCap];
   __shared__ int s_scan[4];
+  __shared__ long long s_lbase;
   const unsigned G = gridDim.x;
   const int tid = threadIdx.x;
   for (int k = tid; k < kFlagWords; k += 256) sm.flags[k] = 0u;
@@ -1322,6 +2009,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
   unsigned gen = relaxed_load(&ctl->bar_gen.v);
   const unsigned long long E0 = ctl->epoch;
   unsigned long long E = E0;
+  // After plain rounds that left nothing to do, or the rest to the tail, the
+  // launch ends before its first barrier (idle stays, for the blocks that start
+  // last).
+  const int idle = a.plain ? ctl->idle : 0;
+  if (idle == kAllDone || idle == kFewEdits) {
+    if (blockIdx.x != 0) return;
+    for (int fi = tid; fi < a.nf; fi += 256)
+      if (a.out) a.out[fi] = load_iter((gptr<const FieldIter>)&as_global(a.fd[fi].st)->s[E0 & 1]);
+    if (tid == 0) {
+      ctl->rounds = 0;
+      ctl->handoff = idle == kFewEdits ? kHandToTail : 0;
+    }
+    return;
+  }
   const bool tracer = a.trace && blockIdx.x == 0 && tid == 0;
   if (tracer && E0 == 0) a.trace[kTraceRounds * kTraceSlots] = wall_clock64();
 
@@ -1372,11 +2073,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
         }
       }
       any_tiles |= __syncthreads_or(sweeps);
-      // A large tile round is left to a sweep kernel at the march's own
-      // occupancy: every block sees the same states and leaves here, before
-      // this round's detection has done anything (the marks of its active
-      // tiles stay set for the sweep).
-      if (a.split_tiles && r > 0 && f0 == 0 && __syncthreads_or(big)) {
+      // A large tile round is left to plain kernels (engine_round): every
+      // block sees the same states and leaves here, before this round's
+      // detection has done anything (the marks of its active tiles stay set
+      // for the sweep).
+      if (a.split_tiles && (r > 0 || a.plain) && f0 == 0 && __syncthreads_or(big)) {
         split_here = true;
         break;
       }
@@ -1444,12 +2145,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     const unsigned long long edited = load_edits(ctl, q);
     ++E;
     if (edited == 0 || stop_here) break;
-    // the next round examines at most 15 neighbours per edit: few enough for
-    // the blocks of one XCD, and few enough segments to mark for its apply
-    // pass, and k_tail takes the rest of the loop there
-    if (a.tail_ok && a.nf <= 256 &&
-        edited * 15ull <= (unsigned long long)(kTailGrid / 8) * 256ull * kTailExams &&
-        (edited <= (unsigned long long)kTailSegs || a.total_segs <= kTailSegs)) {
+    if (tail_takes(a, edited)) {
       handoff = true;
       break;
     }
@@ -1466,6 +2162,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
       ctl->epoch = E;
       ctl->rounds = E - E0;
       ctl->handoff = handoff ? kHandToTail : 0;
+      ctl->idle = 0;
+      ctl->kinds = kKindTiles | kKindSparse;
     }
     // k_tail's census starts cleared (the XCD arrival counters are cleared
     // already: each barrier's last arrival resets its XCD's)
@@ -1524,6 +2222,8 @@ __global__ __launch_bounds__(256) void k_tail(EngineArgs a) {
       ctl->epoch = E;
       ctl->rounds = E - E0;
       ctl->handoff = rc == 2 ? kHandToEngine : kTailDone;
+      ctl->idle = 0;  // (plain rounds may follow)
+      ctl->kinds = kKindTiles | kKindSparse;
     }
   }
 }
@@ -1581,6 +2281,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   __syncthreads();
   EngineCtl* ctl = a.ctl;
   const unsigned long long E = ctl->epoch;  // written by the previous launch
+  if (KIND == KIND_NEXT) {
+    // nothing to do in a round without fields in tile rounds (marks that stay
+    // set only widen a later one)
+    if (a.plain && (ctl->idle || !(ctl->kinds & kKindTiles))) return;
+  }
   const int p = (int)(E & 1), q = (int)(E % 3);
   auto counters = [&](int f) { return &as_global(a.fd[f].st)->c[q].s[ctr_slot()]; };
   unsigned long long* const all_sw = &ctl->tot[q][ctr_slot()].swept;
@@ -1741,11 +2446,6 @@ static hipError_t occupancy_of(const void* kernel, int dev, Occupancy& out) {
   out = it->second;
   return hipSuccess;
 }
-template <class T>
-static hipError_t occupancy(int dev, Occupancy& out) {
-  return occupancy_of((const void*)k_engine<T>, dev, out);
-}
-
 // Waves enough to fill the chip kSweepFill times over, at most one per tile.
 constexpr int64_t kSweepFill = 4;
 template <class T, int KIND, bool PROP, bool COPY, int DIM>
@@ -1786,57 +2486,79 @@ hipError_t engine_sweep(int dtype, int kind, bool prop, int dims, const EngineAr
   return sweep_dims<double>(kind, prop, dims, a, s);
 }
 
-template <class T>
-static hipError_t apply_first_t(const EngineArgs& a, hipStream_t s) {
+// Resident blocks of a kernel on the current device, at most `most`.
+static hipError_t resident(const void* kernel, int64_t most, unsigned* grid) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   Occupancy occ;
-  if ((e = occupancy_of((const void*)k_apply_first<T>, dev, occ)) != hipSuccess) return e;
-  int64_t grid = (int64_t)(occ.per_cu > 0 ? occ.per_cu : 1) * (occ.cus > 0 ? occ.cus : 1);
-  // parts per segment as in the engine: a power of two up to 256, so that
-  // small fields' segments are shared by the grid's blocks
-  int plog = 0;
-  while (plog < 8 && (a.total_segs << (plog + 1)) <= grid) ++plog;
-  const int64_t units = a.total_segs << plog;
-  if (grid > units) grid = units;
-  if (grid < 1) grid = 1;
-  hipLaunchKernelGGL(k_apply_first<T>, dim3((unsigned)grid), dim3(256), 0, s, a, plog);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const unsigned fb = (unsigned)((a.nf + 255) / 256);
-  hipLaunchKernelGGL(k_first_round_end, dim3(fb > 0 ? fb : 1), dim3(256), 0, s, a);
-  return hipGetLastError();
+  if ((e = occupancy_of(kernel, dev, occ)) != hipSuccess) return e;
+  int64_t n = (int64_t)(occ.per_cu > 0 ? occ.per_cu : 1) * (occ.cus > 0 ? occ.cus : 1);
+  if (n > most) n = most;
+  *grid = (unsigned)(n < 1 ? 1 : n);
+  return hipSuccess;
 }
 
-hipError_t engine_apply_first(int dtype, const EngineArgs& a, hipStream_t s) {
-  if (dtype == PMSZ_F32) return apply_first_t<float>(a, s);
-  return apply_first_t<double>(a, s);
+template <class T, int DIM>
+static hipError_t sparse_t(const EngineArgs& a, hipStream_t s) {
+  unsigned grid = 1;
+  const hipError_t e = resident((const void*)k_sparse<T, DIM>, a.total_segs * 4, &grid);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_sparse<T, DIM>), dim3(grid), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+hipError_t engine_sparse(int dtype, int dims, const EngineArgs& a, hipStream_t s) {
+  hipError_t e = hipSuccess;
+  if (dims & 2) e = dtype == PMSZ_F32 ? sparse_t<float, 2>(a, s) : sparse_t<double, 2>(a, s);
+  if (e == hipSuccess && (dims & 4))
+    e = dtype == PMSZ_F32 ? sparse_t<float, 3>(a, s) : sparse_t<double, 3>(a, s);
+  return e;
+}
+
+template <class T>
+static hipError_t apply_t(const EngineArgs& a, hipStream_t s) {
+  unsigned grid = 1;
+  hipError_t e =  // a 256-word unit per wave
+      resident((const void*)k_apply<T>, a.total_segs * (kSegWords / kUnitWords) / 4, &grid);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_apply<T>, dim3(grid), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+hipError_t engine_apply(int dtype, const EngineArgs& a, hipStream_t s) {
+  return dtype == PMSZ_F32 ? apply_t<float>(a, s) : apply_t<double>(a, s);
+}
+
+template <class T, int WAVES>
+static hipError_t launch_w(const EngineArgs& a, hipStream_t s, int64_t want, int* grid_out) {
+  unsigned grid = 1;
+  hipError_t e = resident((const void*)k_engine<T, WAVES>, want, &grid);
+  if (e != hipSuccess) return e;
+  if (grid_out) *grid_out = (int)grid;
+  EngineArgs copy = a;
+  void* args[] = {&copy};
+  return hipLaunchCooperativeKernel((const void*)k_engine<T, WAVES>, dim3(grid), dim3(256), args,
+                                    0, s);
 }
 
 template <class T>
 static hipError_t launch_t(const EngineArgs& a, hipStream_t s, int* grid_out, bool clear) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  Occupancy occ;
-  if ((e = occupancy<T>(dev, occ)) != hipSuccess) return e;
-  const int per_cu = occ.per_cu, cus = occ.cus;
   // the XCD and compute-unit barrier state starts cleared in every launch
   // (the round totals after it are kept: a sweep kernel may have added to
   // the current round's already)
+  hipError_t e;
   if (clear &&
       (e = engine_fill(&a.ctl->xbar[0], offsetof(EngineCtl, tot) - offsetof(EngineCtl, xbar), 0u,
                        s)) != hipSuccess)
     return e;
-  int64_t want = a.total_tiles > a.total_segs ? a.total_tiles : a.total_segs;
-  if (want < 1) want = 1;
-  int64_t cap = (int64_t)per_cu * cus;
-  if (cap < 1) cap = 1;
-  const unsigned grid = (unsigned)(want < cap ? want : cap);
-  if (grid_out) *grid_out = (int)grid;
-  EngineArgs copy = a;
-  void* args[] = {&copy};
-  return hipLaunchCooperativeKernel((const void*)k_engine<T>, dim3(grid), dim3(256), args, 0, s);
+  const int64_t want = a.total_tiles > a.total_segs ? a.total_tiles : a.total_segs;
+  // The full register budget (200 registers, two waves per SIMD) where the grid does
+  // not fill the chip anyway or the launch is left with sparse rounds: the tile
+  // march spills at four (three) waves, and a spill's first touch of memory costs a
+  // phase microseconds.  512 x 512 x 512: 1488 -> 1470 us, 257 x 253 x 190 targeted
+  // 555 -> 527 us, 64^3 280 -> 268 us; a serving step with tiles on the whole
+  // chip 1112 -> 1155 us, so those keep the waves.
+  if (a.plain || want <= 512) return launch_w<T, 1>(a, s, want, grid_out);
+  return launch_w<T, sizeof(T) == 4 ? 4 : 3>(a, s, want, grid_out);
 }
 
 hipError_t engine_launch(int dtype, const EngineArgs& a, hipStream_t s, int* grid_out,

@@ -106,6 +106,8 @@ struct EngineCtl {
   int error;                    // a grid barrier timed out
   int handoff;                  // how the last launch ended: kHandToTail, kHandToEngine,
                                 // kTailDone, or 0 (an engine launch that kept its rounds)
+  int idle;                     // plain rounds end here: kAllDone, ... (or 0)
+  int kinds;                    // plain rounds: kinds of detection in the next round
   // per-launch barrier state, cleared before every launch (from xbar up to tot)
   BarWord xbar[kXcdSlots];      // arrivals per XCD
   BarWord xtop;                 // XCDs arrived
@@ -141,6 +143,10 @@ constexpr int kTailGrid = 256;  // blocks of a tail launch (32 per XCD)
 // the batch has at most kTailSegs segments), so that the marks stay few.
 constexpr int64_t kTailSegs = 128;
 constexpr int kHandToTail = 1, kHandToEngine = 2, kTailDone = 3;
+// EngineCtl::idle.
+constexpr int kAllDone = 1, kFewEdits = 2, kTilesNext = 3;
+// EngineCtl::kinds: some field sweeps tiles, some field is in a sparse round.
+constexpr int kKindTiles = 1, kKindSparse = 2;
 
 // Values of the host's stop word: end the launch after the current round;
 // end it after a round that begins with a field of the launch done.
@@ -162,10 +168,12 @@ struct EngineArgs {
                          // first seen finished
   unsigned* stop_host;   // nullable, host memory: kStopNow / kStopWhenDone (below),
                          // read by block 0 at the start of every round
-  int32_t split_tiles;   // end the launch before a round, other than its first, in
-                         // which a field of kSplitVoxels vertices or more (among
-                         // the first 256) sweeps tiles: a sweep kernel takes that
-                         // round's tile detection and the next launch the rest
+  int32_t split_tiles;   // end the launch before a round, other than its first
+                         // (its first too after plain rounds), in which a field of
+                         // kSplitVoxels vertices or more (among the first 256)
+                         // sweeps tiles: plain rounds take it
+  int32_t plain;         // the launch follows plain rounds
+  int32_t next_sweep;    // engine_apply: an engine_sweep of the next round follows
   const void* src;       // nullable, one field: fhat, for the first sweep to read and to
                          // write to the field's g (engine_sweep)
   int32_t tail_ok;       // the launch may hand its last rounds to k_tail (at most
@@ -208,10 +216,12 @@ hipError_t engine_dirs(int dtype, int dims, const FieldDesc* fd, int nf, int64_t
 hipError_t engine_sweep(int dtype, int kind, bool prop, int dims, const EngineArgs& a,
                         hipStream_t s);
 
-// Round 0's apply pass as a plain kernel after a round-0 sweep, then the end
-// of round 0 (every field's state at round 1, epoch 1, the round's record):
-// the engine launch that follows starts at round 1.
-hipError_t engine_apply_first(int dtype, const EngineArgs& a, hipStream_t s);
+// The rest of a plain round, for large batches: detection of the fields in sparse
+// rounds (after engine_sweep for the others), then the apply pass and the end of
+// the round (every field's state at the next one, the epoch, the round's
+// record).  The next plain round or engine launch takes the round after.
+hipError_t engine_sparse(int dtype, int dims, const EngineArgs& a, hipStream_t s);
+hipError_t engine_apply(int dtype, const EngineArgs& a, hipStream_t s);
 
 // Zero `bytes` bytes (multiple of 4, 4-byte aligned) with a kernel, so that
 // the call can sit inside a captured graph.
