@@ -60,19 +60,21 @@ def measured_traffic(kernel):
 def kernel_split(tm, rounds, s):
     """Per kernel of one correction: (total ms, launches, algorithmic bytes).
     The directions kernel reads f and writes the direction bytes (s + 1 per
-    vertex).  Round 0's detection reads fhat, f and the direction bytes
+    vertex; large fields make them in the first sweep, which then reads f and
+    fhat and writes the bytes, the same 2s + 1).  Round 0's detection reads fhat, f and the direction bytes
     (2s + 1 per vertex); a later round's reads g and the direction bytes and
     writes flag bits (s + 1.125) per vertex examined, in tiles or by sparse
-    examination; an edit reads f and g and writes g (3s).  With split sweeps
-    the tile detection of rounds 0 and 1 is the sweep kernel's (two launches)
-    and the rest the engine's: round 0's apply kernel and the engine launch
-    from round 1 (two launches; the tail kernel's rounds, timed with the
-    engine, are counted in it)."""
+    examination; an edit reads f and g and writes g (3s).  In large batches
+    the tile detection is the sweep kernel's and the rest is counted as the
+    engine's: the sparse and apply kernels of the plain rounds, the engine
+    launch and the tail's rounds, which are timed together."""
     det = [r["swept"] * ((2 * s + 1) if i == 0 else (s + 1.125)) for i, r in enumerate(rounds)]
     tiles = [(r["swept"] - r["sparse"]) * ((2 * s + 1) if i == 0 else (s + 1.125))
              for i, r in enumerate(rounds)]
     edits = tm["edits"] * 3 * s
-    out = {"k_dirs_fields": (tm["dirs_ms"], 1, tm["voxels"] * (s + 1))}
+    out = {}
+    if tm["dirs_ms"]:
+        out["k_dirs_fields"] = (tm["dirs_ms"], 1, tm["voxels"] * (s + 1))
     if tm.get("sweeps"):
         swept_b = sum(tiles[:2])
         out["k_sweep"] = (tm["sweep_ms"], tm["sweeps"], swept_b)

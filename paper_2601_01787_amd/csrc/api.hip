@@ -452,10 +452,11 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
   Timing& tm = t_timing;
   if (timed && (r = timing_events(tm))) return r;
   int grid = 0;
-  bool need_dirs = false;
+  bool need_dirs = false, all_dirs = true;  // some field needs its directions, all do
   int dims = 0;
   for (int32_t i = 0; i < n; ++i) {
     need_dirs |= !P.fd[i].dirs_given;
+    all_dirs &= !P.fd[i].dirs_given;
     dims |= P.fd[i].geo.ndim == 3 ? 4 : 2;
   }
   // Directions of f, then the correction loop.  Large batches run their first
@@ -466,7 +467,10 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
   // save).
   constexpr int kGroup = Timing::kGroup, kSweeps = Timing::kSweeps;
   if (timed) HIP_TRY(hipEventRecord(tm.ev[0], s));
-  if (need_dirs) HIP_TRY(engine_dirs(dtype, dims, a.fd, n, P.total_tiles, s));
+  // (the first sweep of a large batch makes the directions on the way: both read f)
+  const int first_kind = split && all_dirs ? KIND_FIRST : KIND_FIRST_GIVEN;
+  if (need_dirs && first_kind != KIND_FIRST)
+    HIP_TRY(engine_dirs(dtype, dims, a.fd, n, P.total_tiles, s));
   if (timed) HIP_TRY(hipEventRecord(tm.ev[1], s));
   auto sweep = [&](int i) -> int {  // of a round's marked tiles
     if (timed) HIP_TRY(hipEventRecord(tm.ev[kSweeps + 2 * i], s));
@@ -488,7 +492,7 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
     return PMSZ_OK;
   };
   if (split) {
-    HIP_TRY(engine_sweep(dtype, KIND_FIRST_GIVEN, P.edit_mode != 0, dims, a, s));
+    HIP_TRY(engine_sweep(dtype, first_kind, P.edit_mode != 0, dims, a, s));
     if (timed) HIP_TRY(hipEventRecord(tm.ev[2], s));
     a.next_sweep = 1;
     HIP_TRY(engine_apply(dtype, a, s));
@@ -584,7 +588,8 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
     return PMSZ_OK;
   }
   float dirs_ms = 0.f;
-  HIP_TRY(hipEventElapsedTime(&dirs_ms, tm.ev[0], tm.ev[1]));
+  if (need_dirs && first_kind != KIND_FIRST)  // (else the sweep's, or the caller's)
+    HIP_TRY(hipEventElapsedTime(&dirs_ms, tm.ev[0], tm.ev[1]));
   memset(&tm.last, 0, sizeof(tm.last));
   tm.last.dirs_ms = dirs_ms;
   tm.last.sweep_ms = sweep_ms;

@@ -2234,7 +2234,7 @@ __global__ __launch_bounds__(256) void k_tail(EngineArgs a) {
 template <class T, int DIM>
 __global__ __launch_bounds__(256) void k_dirs_fields(const FieldDesc* fd, int nf,
                                                      int64_t total_tiles) {
-  __shared__ WaveLds<T, DIM, false> sm[4];
+  __shared__ WaveLds<T, DIM, KIND_DIRS> sm[4];
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int32_t run = xcd_run(total_tiles);
   const int64_t blocks = tile_blocks(total_tiles);
@@ -2258,23 +2258,27 @@ __global__ __launch_bounds__(256) void k_dirs_fields(const FieldDesc* fd, int nf
 // Waves per SIMD of the sweeps: the most that spills next to nothing (a march that
 // spills waits for memory in every step: sweeps of a 512^3 binary32 field took
 // 0.66 ms at four waves against 0.56 ms at three, of a 1024 x 1024 x 768
-// binary64 one 5.2 ms at three against 3.3 ms at two).
-template <class T, int DIM>
+// binary64 one 5.2 ms at three against 3.3 ms at two).  The first sweep that also
+// makes the directions of f marches two fields and gets one wave less: it reads
+// f once for both (1024 x 1024 x 768 binary64: 1.94 ms directions + 4.71 ms
+// sweep -> 5.74 ms; 512^3 binary32 is bound by vector instructions either way,
+// 0.21 + 0.39 -> 0.59 ms; 256 2D fields 0.59 + 1.21 -> 1.46 ms).
+template <class T, int DIM, int KIND>
 constexpr int sweep_waves() {
-  return (sizeof(T) == 4 ? 4 : 3) - (DIM == 3 ? 1 : 0);
+  return (sizeof(T) == 4 ? 4 : 3) - (DIM == 3 ? 1 : 0) - (KIND == KIND_FIRST ? 1 : 0);
 }
 // COPY (one field, first round): fhat is read from a.src, and the field's g
 // written from it on the way.
 template <class T, int KIND, bool PROP, bool COPY, int DIM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
-    sweep_waves<T, DIM>()))) void k_sweep(EngineArgs a) {
-  __shared__ WaveLds<T, DIM, true> s_w[4];
+    sweep_waves<T, DIM, KIND>()))) void k_sweep(EngineArgs a) {
+  __shared__ WaveLds<T, DIM, KIND> s_w[4];
   __shared__ int32_t s_delta[16];
   __shared__ int s_cur[4];
   __shared__ unsigned long long s_cnt[4][4];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  WaveLds<T, DIM, true>& sm = s_w[wave];
+  WaveLds<T, DIM, KIND>& sm = s_w[wave];
   for (int k = lane; k < (int)(sizeof(sm.flags) / 4); k += 64) sm.flags[k] = 0u;
   if (DIM == 3) set_flag_deltas(s_delta, kRowBits3, kRowBits3 * (TY + 2));
   else set_flag_deltas(s_delta, kRowBits2, 0);
@@ -2304,7 +2308,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
       const FieldDesc& d = a.fd[fi];
       if (d.geo.ndim == DIM) {  // (the other dimension's kernel takes the others)
         const FieldIter s = state_at(d, E, E);
-        if (KIND == KIND_FIRST_GIVEN) {
+        if (KIND != KIND_NEXT) {
           take = !s.started && !s.done;
         } else {
           const gptr<uint8_t> flag = as_global(d.act) + p * tile_count(d.geo) + (mine - d.tile_base);
@@ -2465,7 +2469,10 @@ static hipError_t sweep_t(const EngineArgs& a, hipStream_t s) {
 
 template <class T, bool PROP, int DIM>
 static hipError_t sweep_kind(int kind, const EngineArgs& a, hipStream_t s) {
-  if (kind != KIND_FIRST_GIVEN) return sweep_t<T, KIND_NEXT, PROP, false, DIM>(a, s);
+  if (kind == KIND_NEXT) return sweep_t<T, KIND_NEXT, PROP, false, DIM>(a, s);
+  if (kind == KIND_FIRST)
+    return a.src ? sweep_t<T, KIND_FIRST, PROP, true, DIM>(a, s)
+                 : sweep_t<T, KIND_FIRST, PROP, false, DIM>(a, s);
   return a.src ? sweep_t<T, KIND_FIRST_GIVEN, PROP, true, DIM>(a, s)
                : sweep_t<T, KIND_FIRST_GIVEN, PROP, false, DIM>(a, s);
 }

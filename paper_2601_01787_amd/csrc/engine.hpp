@@ -206,8 +206,9 @@ hipError_t engine_dirs(int dtype, int dims, const FieldDesc* fd, int nf, int64_t
 // Tile detection of one round as a plain kernel (no grid barrier, so it runs
 // at the march's own occupancy instead of the persistent engine's), for the
 // round the workspace's epoch names: every tile of a field in its first
-// round (kind KIND_FIRST_GIVEN) or every marked tile of a field in a tile
-// round (KIND_NEXT); fields of the other kind, finished fields and fields in
+// round (kind KIND_FIRST_GIVEN, or KIND_FIRST, which makes and writes the
+// directions of f too) or every marked tile of a field in a tile round
+// (KIND_NEXT); fields of the other kind, finished fields and fields in
 // a sparse round are left to the engine.  The engine launch that follows
 // sets tiles_swept and skips its first round's tile detection.
 // prop: the batch uses the targeted edit (flags also propose values).  dims:

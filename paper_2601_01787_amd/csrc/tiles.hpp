@@ -165,6 +165,8 @@ inline TileGeo make_tile_geo(int ndim, int64_t nx, int64_t ny, int64_t nz, int c
 // What a tile pass does with the directions it computes.
 enum TileKind {
   KIND_DIRS = 0,        // write the direction bytes of h (wave_tiles.hpp only)
+  KIND_FIRST = 1,       // first round, directions of f not given: they are made,
+                        // written and used on the way (wave_tiles.hpp only)
   KIND_FIRST_GIVEN = 2, // first round: validation of g against f, mismatch
                         // detection of g against the given directions of f
   KIND_NEXT = 3         // later rounds: mismatch detection of g

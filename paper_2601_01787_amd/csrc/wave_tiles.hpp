@@ -172,10 +172,13 @@ struct EdgeOf<T, 2> {
 // 3D edges are gathered kEdgeGroup planes at a time, two planes ahead of their use,
 // when the march (and its neighbours') load the same lines.
 constexpr int kEdgeGroup = 4;
-template <class T, int DIM, bool FLAGS>
+template <class T, int DIM, int KIND>
 struct WaveLds {
+  // of h and, where the directions of f are made too, of f
   // (2D: one more than a tile's rows, the march runs them in pairs)
-  typename EdgeOf<T, DIM>::type edge[DIM == 3 ? kEdgeGroup : kMaxChunk + 3];
+  typename EdgeOf<T, DIM>::type
+      edge[KIND == KIND_FIRST ? 2 : 1][DIM == 3 ? kEdgeGroup : kMaxChunk + 3];
+  static constexpr bool FLAGS = KIND != KIND_DIRS;
   uint32_t flags[FLAGS ? (DIM == 3 ? (kMaxChunk + 2) * (TY + 2) * kFlagW3
                                    : (kMaxChunk + 2) * kFlagW2)
                        : 1];
@@ -327,8 +330,8 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
   const gptr<const T> h = as_global((const T*)uniform_ptr(h_in));
   const gptr<const T> f = as_global((const T*)uniform_ptr(f_in));
   const gptr<uint8_t> dirs = as_global(uniform_ptr(dirs_in));
-  constexpr bool kSweep = KIND != KIND_DIRS;
-  constexpr bool kFirst = KIND == KIND_FIRST_GIVEN;
+  constexpr bool kSweep = KIND != KIND_DIRS, kMake = KIND == KIND_FIRST;
+  constexpr bool kFirst = KIND == KIND_FIRST_GIVEN || kMake;
   constexpr int R = TY, V = TY + 2;  // lines out, lines in
   const int lane = threadIdx.x & 63;
   const int32_t bx = tile % G.tiles_x, by = (tile / G.tiles_x) % G.tiles_y,
@@ -363,8 +366,9 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
   struct Plane {
     T v[V];
     uint32_t d[R];  // directions of f one plane lower
-    T fv[R];        // f in this plane
+    T fv[kMake ? V : R];  // f in this plane (its lines out, or all)
   };
+  constexpr int FO = kMake ? 1 : 0;  // first line out in fv
   auto fetch = [&](int32_t q, Plane& S) {
     const int64_t pl = plane_at(q) + at0;
     const Rsrc rh = rsrc_at(h + pl);
@@ -373,10 +377,10 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
     if (kFirst) {
       const Rsrc rf = rsrc_at(f + pl);
 #pragma unroll
-      for (int r = 0; r < R; ++r)
-        buf_load(rf, xb, row[r + 1] * (uint32_t)sizeof(T), S.fv[r]);
+      for (int r = 0; r < (kMake ? V : R); ++r)
+        buf_load(rf, xb, row[r + 1 - FO] * (uint32_t)sizeof(T), S.fv[r]);
     }
-    if (kSweep) {
+    if (kSweep && !kMake) {
       const Rsrc rd = rsrc_at(dirs + (plane_at(q - 1) + at0));
 #pragma unroll
       for (int r = 0; r < R; ++r)
@@ -401,14 +405,15 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
   struct Edges {
     T right, a, b;
   };
-  Box<T> e_last{T(0), T(0), 0u, 0u};  // lanes 0..7: squares of plane q0 - 1
-  auto edges_load = [&](int32_t q0, Edges& e) {
-    const gptr<const T> p = h + plane_at(q0 + ej);
+  // lanes 0..7: squares of plane q0 - 1
+  Box<T> e_last[2] = {{T(0), T(0), 0u, 0u}, {T(0), T(0), 0u, 0u}};
+  auto edges_load1 = [&](gptr<const T> from, int32_t q0, Edges& e) {
+    const gptr<const T> p = from + plane_at(q0 + ej);
     e.right = p[e_right];
     e.a = p[e_left];
     e.b = p[e_own];
   };
-  auto edges_store = [&](int32_t q0, const Edges& e) {
+  auto edges_store1 = [&](int which, int32_t q0, const Edges& e) {
     const XPair<T> xp = x_pair(e.a, e.b, 0u);
     const Box<T> ln{xp.hi, xp.lo, xp.c, xp.c ^ 1u};
     const Box<T> sq1 =
@@ -420,10 +425,10 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
     Box<T> below{__shfl(sq1.hi, from, 64), __shfl(sq1.lo, from, 64),
                  (uint32_t)__shfl((int)sq1.ca, from, 64), (uint32_t)__shfl((int)sq1.cd, from, 64)};
     const Box<T> next = below;
-    if (ej == 0) below = e_last;
-    e_last = next;
+    if (ej == 0) below = e_last[which];
+    e_last[which] = next;
     const Box<T> b = box_merge(below, Box<T>{sq1.hi, sq1.lo, sq1.ca | 4u, sq1.cd | 4u});
-    Edge3<T>& E = sm.edge[ej];
+    Edge3<T>& E = sm.edge[which][ej];
     E.right[er] = e.right;
     if ((lane & 7) < R) {
       E.hi[er] = b.hi;
@@ -432,11 +437,19 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
                                (x0 == 0 ? 1u : 0u) | (y0 + er == 0 ? 2u : 0u) |
                                    (z0 + q0 + ej == 1 ? 4u : 0u));
     }
+  };
+  Edges edges[2];
+  auto edges_load = [&](int32_t q0) {
+    edges_load1(h, q0, edges[0]);
+    if (kMake) edges_load1(f, q0, edges[1]);
+  };
+  auto edges_store = [&](int32_t q0) {
+    edges_store1(0, q0, edges[0]);
+    if (kMake) edges_store1(1, q0, edges[1]);
     wave_lds_fence();
   };
-  Edges edges;
-  edges_load(0, edges);
-  edges_store(0, edges);
+  edges_load(0);
+  edges_store(0);
 
   const T xi_in = fast_margin<T>(xi);
   // axes along which the vertices have an upper neighbour, per line
@@ -448,20 +461,62 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
   constexpr int32_t kPlaneBits3 = kRowBits3 * (TY + 2);
   const int32_t zc1 = G.cz1 < z1 ? G.cz1 : z1;  // end of the planes to compare
   LaneCounts n{0, 0, 0};
-  Box<T> sq[R + 1];  // squares of the last plane
-  Low<T> low[R];     // lower boxes of the last plane's vertices
+  struct March {
+    Box<T> sq[R + 1];  // squares of the last plane
+    Low<T> low[R];     // lower boxes of the last plane's vertices
+  };
+  March mh, mf;  // of h; of f, where its directions are made
   // The step of plane q (0 is z0 - 1) with parity PARITY: MODE 0 squares only, 1 boxes
   // only, 2 whole.
-  auto step = [&](auto mode, auto parity, int32_t q, Plane& S) {
-    constexpr int MODE = decltype(mode)::value;
-    constexpr uint32_t ZT = 4u * (uint32_t)decltype(parity)::value, ZP = ZT ^ 4u;
-    const Edge3<T>& E = sm.edge[q & (kEdgeGroup - 1)];
-    const int32_t z = z0 + q - 2;  // plane of the vertices finished
-    XPair<T> xp[V];
+  auto pairs = [&](auto parity, const T* v, const Edge3<T>& E, XPair<T>* xp) {
+    constexpr uint32_t ZT = 4u * (uint32_t)decltype(parity)::value;
 #pragma unroll
     for (int r = 0; r < V; ++r)
-      xp[r] = x_pair(S.v[r], lane_shift<kFromRight>(S.v[r], E.right[r]),
+      xp[r] = x_pair(v[r], lane_shift<kFromRight>(v[r], E.right[r]),
                      (uint32_t)(2 * (r & 1)) | ZT);
+  };
+  // emit(r, byte, lowest neighbour) for the vertices of the plane before
+  auto boxes = [&](auto mode, auto parity, const XPair<T>* xp, const Edge3<T>& E, March& M,
+                   auto emit) {
+    constexpr int MODE = decltype(mode)::value;
+    constexpr uint32_t ZP = 4u * (uint32_t)decltype(parity)::value ^ 4u;
+    // from the last line down: line rr's new lower box replaces the one that
+    // the vertex of line rr + 1 has used
+#pragma unroll
+    for (int rr = R; rr >= 0; --rr) {
+      const Box<T> s = box_merge(box_of_pair(xp[rr]), box_of_pair(xp[rr + 1]));
+      if (MODE != 0) {
+        const Box<T> b = box_merge(M.sq[rr], s);
+        const uint32_t w = code_word(b);
+        const uint32_t par = (uint32_t)(2 * (rr & 1)) | ZP;
+        if (MODE == 2 && rr > 0) {
+          const int r = rr - 1;
+          emit(r, dir_byte(M.low[r], b, upper_codes(w, par, keep[r])),
+               PROP ? lower(b.lo < M.low[r].lo, b.lo, M.low[r].lo) : T(0));
+        }
+        if (rr < R) {
+          uint32_t m = w;
+          // no neighbour below line 0, and below plane 0 (the y and z bits of the
+          // upper half: these boxes' line and plane parities are even)
+          if (rr == 0) m |= low_y;
+          if (MODE == 1 && z0 == 0) m |= 0x0404u;
+          const uint32_t lw = (rr & 1) ? lower_codes<2u | ZP, 7u>(m) : lower_codes<ZP, 7u>(m);
+          M.low[rr] = Low<T>{lane_shift<kFromLeft>(b.hi, E.hi[rr]),
+                             lane_shift<kFromLeft>(b.lo, E.lo[rr]),
+                             lane_shift<kFromLeft>(lw, E.w[rr])};
+        }
+      }
+      M.sq[rr] = s;
+    }
+  };
+  auto step = [&](auto mode, auto parity, int32_t q, Plane& S) {
+    constexpr int MODE = decltype(mode)::value;
+    const Edge3<T>& E = sm.edge[0][q & (kEdgeGroup - 1)];
+    const Edge3<T>& Ef = sm.edge[kMake ? 1 : 0][q & (kEdgeGroup - 1)];
+    const int32_t z = z0 + q - 2;  // plane of the vertices finished
+    XPair<T> xp[V], xf[V];
+    pairs(parity, S.v, E, xp);
+    if (kMake) pairs(parity, S.fv, Ef, xf);
     if (COPY && MODE != 0) {
       const Rsrc rc = rsrc_at(copy_to + (plane_at(q) + at0), q < nq - 1);
 #pragma unroll
@@ -474,11 +529,11 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
       bool near = false;
 #pragma unroll
       for (int r = 0; r < R; ++r)
-        near |= !(__builtin_fabs(S.v[r + 1] - S.fv[r]) < xi_in);
+        near |= !(__builtin_fabs(S.v[r + 1] - S.fv[r + FO]) < xi_in);
       if (near && in_x && q < nq - 1) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          const int bc = y0 + r < G.ny ? bound_class_exact<T>(S.fv[r], S.v[r + 1], xi) : 0;
+          const int bc = y0 + r < G.ny ? bound_class_exact<T>(S.fv[r + FO], S.v[r + 1], xi) : 0;
           n.nf += bc == 1;
           n.nb += bc == 2;
         }
@@ -486,46 +541,28 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
     }
     uint32_t os = 0, ds = 0;  // direction bytes of the lines, of g and of f
     T lows[R];                // their lowest neighbours (proposals)
-    if (kSweep && MODE == 2) {
+    if (kSweep && !kMake && MODE == 2) {
 #pragma unroll
       for (int r = 0; r < R; ++r) ds |= S.d[r] << (8 * r);
     }
     fetch(q + 2, S);
     const Rsrc rout = rsrc_at(dirs + ((int64_t)G.sxy * z + at0), z < z1);
-    // from the last line down: line rr's new lower box replaces the one that
-    // the vertex of line rr + 1 has used
-#pragma unroll
-    for (int rr = R; rr >= 0; --rr) {
-      const Box<T> s = box_merge(box_of_pair(xp[rr]), box_of_pair(xp[rr + 1]));
-      if (MODE != 0) {
-        const Box<T> b = box_merge(sq[rr], s);
-        const uint32_t w = code_word(b);
-        const uint32_t par = (uint32_t)(2 * (rr & 1)) | ZP;
-        if (MODE == 2 && rr > 0) {
-          const int r = rr - 1;
-          const uint32_t o = dir_byte(low[r], b, upper_codes(w, par, keep[r]));
-          if (KIND == KIND_DIRS) {
-            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)o, rout, xs[r], row[r + 1], 0);
-          } else {
-            os |= o << (8 * r);
-            if (PROP) lows[r] = lower(b.lo < low[r].lo, b.lo, low[r].lo);
-          }
-        }
-        if (rr < R) {
-          uint32_t m = w;
-          if (rr == 0) m |= low_y;
-          // below plane 0: no neighbour (parity of plane q - 1 is even there)
-          if (MODE == 1 && z0 == 0) m |= 0x0404u;
-          // (the minimum's x bit is inverted; y and z bits are set, which
-          // stands for the upper half: line and plane 0 are the odd ones' lower)
-          const uint32_t lw = (rr & 1) ? lower_codes<2u | ZP, 7u>(m) : lower_codes<ZP, 7u>(m);
-          low[rr] = Low<T>{lane_shift<kFromLeft>(b.hi, E.hi[rr]),
-                           lane_shift<kFromLeft>(b.lo, E.lo[rr]),
-                           lane_shift<kFromLeft>(lw, E.w[rr])};
-        }
+    auto store = [&](int r, uint32_t o) {
+      __builtin_amdgcn_raw_buffer_store_b8((uint8_t)o, rout, xs[r], row[r + 1], 0);
+    };
+    if (kMake)
+      boxes(mode, parity, xf, Ef, mf, [&](int r, uint32_t o, T) {
+        store(r, o);
+        ds |= o << (8 * r);
+      });
+    boxes(mode, parity, xp, E, mh, [&](int r, uint32_t o, T lo) {
+      if (kSweep) {
+        os |= o << (8 * r);
+        lows[r] = lo;
+      } else {
+        store(r, o);
       }
-      sq[rr] = s;
-    }
+    });
     if (kSweep && MODE == 2) {
       // mismatches, a line at a time per lane (few lanes have more than one)
       uint32_t diff = (os ^ ds) & (z >= G.cz0 && z < zc1 ? core : 0u);
@@ -552,13 +589,13 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
   step(Int<1>{}, Int<1>{}, 1, P1);
   // (an odd tile's last step finishes nothing: plane z1 is outside it)
   for (int32_t q = 2; q < nq; q += 4) {
-    edges_load(q + 2, edges);
+    edges_load(q + 2);
     last_plane(q);
     step(Int<2>{}, Int<0>{}, q, P0);
     last_plane(q + 1);
     step(Int<2>{}, Int<1>{}, q + 1, P1);
     if (q + 2 >= nq) break;
-    edges_store(q + 2, edges);
+    edges_store(q + 2);
     last_plane(q + 2);
     step(Int<2>{}, Int<0>{}, q + 2, P0);
     last_plane(q + 3);
@@ -588,8 +625,8 @@ __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelt
   const gptr<const T> h = as_global((const T*)uniform_ptr(h_in));
   const gptr<const T> f = as_global((const T*)uniform_ptr(f_in));
   const gptr<uint8_t> dirs = as_global(uniform_ptr(dirs_in));
-  constexpr bool kSweep = KIND != KIND_DIRS;
-  constexpr bool kFirst = KIND == KIND_FIRST_GIVEN;
+  constexpr bool kSweep = KIND != KIND_DIRS, kMake = KIND == KIND_FIRST;
+  constexpr bool kFirst = KIND == KIND_FIRST_GIVEN || kMake;
   constexpr int C = 4;
   const int lane = threadIdx.x & 63;
   const int32_t bx = tile % G.tiles_x, by = tile / G.tiles_x;
@@ -633,7 +670,7 @@ __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelt
   auto fetch = [&](int32_t q, Row& S) {
     load4(h + (row_at(q) + x0), S.v);
     if (kFirst) load4(f + (row_at(q) + x0), S.fv);
-    if (kSweep) {
+    if (kSweep && !kMake) {
       const Rsrc r = rsrc_at(dirs + (row_at(q - 1) + x0));
       if (RAGGED) {
 #pragma unroll
@@ -652,37 +689,79 @@ __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelt
   {
     const int32_t xr = clamp_to(x0 + RX, G.nx);
     const uint32_t gone_x = x0 == 0 ? 1u : 0u;
-    for (int32_t q = lane; q < nq; q += 64) {
-      sm.edge[q].right = h[row_at(q) + xr];
+    auto edges_of = [&](gptr<const T> from, int32_t q, Edge2<T>& E) {
+      E.right = from[row_at(q) + xr];
       Box<T> ln[2];
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const gptr<const T> p = h + (row_at(q - 1 + j) + x0);
+        const gptr<const T> p = from + (row_at(q - 1 + j) + x0);
         const T B = p[0], A = p[x0 ? -1 : 0];
         const XPair<T> xp = x_pair(A, B, (uint32_t)(2 * j));
         ln[j] = Box<T>{xp.hi, xp.lo, xp.c, xp.c ^ 1u};
       }
       const Box<T> b = box_merge(ln[0], ln[1]);
-      sm.edge[q].hi = b.hi;
-      sm.edge[q].lo = b.lo;
-      sm.edge[q].w = lower_codes_at(b.ca, b.cd, 3u, gone_x | (y0 + q == 1 ? 2u : 0u));
+      E.hi = b.hi;
+      E.lo = b.lo;
+      E.w = lower_codes_at(b.ca, b.cd, 3u, gone_x | (y0 + q == 1 ? 2u : 0u));
+    };
+    for (int32_t q = lane; q < nq; q += 64) {
+      edges_of(h, q, sm.edge[0][q]);
+      if (kMake) edges_of(f, q, sm.edge[kMake ? 1 : 0][q]);
     }
     wave_lds_fence();
   }
   const T xi_in = fast_margin<T>(xi);
   const int32_t yc1 = G.cy1 < y1 ? G.cy1 : y1;  // end of the rows to compare
   LaneCounts n{0, 0, 0};
-  XPair<T> pr[C];  // pairs of the last row
-  Low<T> low[C];   // lower boxes of the last row's vertices
+  struct March {
+    XPair<T> pr[C];  // pairs of the last row
+    Low<T> low[C];   // lower boxes of the last row's vertices
+  };
+  March mh, mf;  // of h; of f, where its directions are made
+  auto pairs = [&](auto parity, const T* v, const Edge2<T>& E, XPair<T>* xp) {
+    constexpr uint32_t YT = 2u * (uint32_t)decltype(parity)::value;
+    const T right = lane_shift<kFromRight>(v[0], E.right);
+#pragma unroll
+    for (int j = 0; j < C; ++j) xp[j] = x_pair(v[j], j + 1 < C ? v[j + 1] : right, YT);
+  };
+  // The boxes of a row; returns the direction bytes of the row before, emit(j,
+  // lowest neighbour) per column.
+  auto boxes = [&](auto mode, auto parity, const XPair<T>* xp, const Edge2<T>& E, March& M,
+                   auto emit) {
+    constexpr int MODE = decltype(mode)::value;
+    constexpr uint32_t YP = 2u * (uint32_t)decltype(parity)::value ^ 2u;
+    uint32_t o = 0;
+    if (MODE != 0) {
+      Low<T> nl[C];
+#pragma unroll
+      for (int j = 0; j < C; ++j) {
+        const Box<T> b = box_merge(box_of_pair(M.pr[j]), box_of_pair(xp[j]));
+        uint32_t w = code_word(b);
+        if (MODE == 2) {
+          o |= dir_byte(M.low[j], b, upper_codes(w, YP, keep[j])) << (8 * j);
+          emit(j, PROP ? lower(b.lo < M.low[j].lo, b.lo, M.low[j].lo) : T(0));
+        }
+        if (MODE == 1 && y0 == 0) w |= 0x0202u;  // no row below row 0
+        nl[j] = Low<T>{b.hi, b.lo, lower_codes<YP, 3u>(w)};
+      }
+      M.low[0] = Low<T>{lane_shift<kFromLeft>(nl[C - 1].hi, E.hi),
+                        lane_shift<kFromLeft>(nl[C - 1].lo, E.lo),
+                        lane_shift<kFromLeft>(nl[C - 1].w, E.w)};
+#pragma unroll
+      for (int j = 1; j < C; ++j) M.low[j] = nl[j - 1];
+    }
+#pragma unroll
+    for (int j = 0; j < C; ++j) M.pr[j] = xp[j];
+    return o;
+  };
   auto step = [&](auto mode, auto parity, int32_t q, Row& S) {
     constexpr int MODE = decltype(mode)::value;
-    constexpr uint32_t YT = 2u * (uint32_t)decltype(parity)::value, YP = YT ^ 2u;
-    const Edge2<T>& E = sm.edge[q];
+    const Edge2<T>& E = sm.edge[0][q];
+    const Edge2<T>& Ef = sm.edge[kMake ? 1 : 0][q];
     const int32_t y = y0 + q - 2;  // row of the vertices finished
-    const T right = lane_shift<kFromRight>(S.v[0], E.right);
-    XPair<T> xp[C];
-#pragma unroll
-    for (int j = 0; j < C; ++j) xp[j] = x_pair(S.v[j], j + 1 < C ? S.v[j + 1] : right, YT);
+    XPair<T> xp[C], xf[C];
+    pairs(parity, S.v, E, xp);
+    if (kMake) pairs(parity, S.fv, Ef, xf);
     if (COPY && MODE != 0) {
       const Rsrc rc = rsrc_at(copy_to + (row_at(q) + x0), q < nq - 1);
       if (RAGGED) {
@@ -706,7 +785,7 @@ __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelt
       }
     }
     uint32_t d = 0;
-    if (kSweep && MODE == 2) {
+    if (kSweep && !kMake && MODE == 2) {
       d = S.d[0];
       if (RAGGED) {
 #pragma unroll
@@ -714,64 +793,37 @@ __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelt
       }
     }
     fetch(q + 2, S);
-    if (MODE != 0) {
-      Box<T> b[C];
-      uint32_t w[C];
-#pragma unroll
-      for (int j = 0; j < C; ++j) {
-        b[j] = box_merge(box_of_pair(pr[j]), box_of_pair(xp[j]));
-        w[j] = code_word(b[j]);
-      }
-      if (MODE == 2) {
-        uint32_t o = 0;
+    auto store = [&](uint32_t o) {
+      const Rsrc r = rsrc_at(dirs + ((int64_t)G.nx * y + x0), y < y1);
+      if (RAGGED) {
 #pragma unroll
         for (int j = 0; j < C; ++j)
-          o |= dir_byte(low[j], b[j], upper_codes(w[j], YP, keep[j])) << (8 * j);
-        if (KIND == KIND_DIRS) {
-          const Rsrc r = rsrc_at(dirs + ((int64_t)G.nx * y + x0), y < y1);
-          if (RAGGED) {
-#pragma unroll
-            for (int j = 0; j < C; ++j)
-              __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(o >> (8 * j)), r,
-                                                   (in_x >> j) & 1 ? off[j % NO] : kNoStore, 0, 0);
-          } else {
-            __builtin_amdgcn_raw_buffer_store_b32(o, r, off[0], 0, 0);
-          }
-        } else {
-          uint32_t diff = (o ^ d) & (y >= G.cy0 && y < yc1 ? core_x : 0u);
-          while (__ballot(diff != 0u)) {
-            if (diff != 0u) {
-              const int j = __builtin_ctz(diff) >> 3;
-              diff &= ~(0xffu << (8 * j));
-              T lo = T(0);
-              if (PROP) {
-#pragma unroll
-                for (int k = 0; k < C; ++k)
-                  if (k == j) lo = lower(b[k].lo < low[k].lo, b[k].lo, low[k].lo);
-              }
-              n.mism += flag_mismatch<T, PROP>(
-                  (o >> (8 * j)) & 0xffu, (d >> (8 * j)) & 0xffu,
-                  (y - y0 + 1) * kRowBits2 + C * lane + j + 1, X + j + G.nx * y, G, sm.flags,
-                  fdelta, prop, h, lo);
-            }
-          }
+          __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(o >> (8 * j)), r,
+                                               (in_x >> j) & 1 ? off[j % NO] : kNoStore, 0, 0);
+      } else {
+        __builtin_amdgcn_raw_buffer_store_b32(o, r, off[0], 0, 0);
+      }
+    };
+    if (kMake) {
+      d = boxes(mode, parity, xf, Ef, mf, [](int, T) {});
+      if (MODE == 2) store(d);
+    }
+    T lows[C];
+    const uint32_t o = boxes(mode, parity, xp, E, mh, [&](int j, T lo) { lows[j] = lo; });
+    if (!kSweep && MODE == 2) store(o);
+    if (kSweep && MODE == 2) {
+      uint32_t diff = (o ^ d) & (y >= G.cy0 && y < yc1 ? core_x : 0u);
+      while (__ballot(diff != 0u)) {
+        if (diff != 0u) {
+          const int j = __builtin_ctz(diff) >> 3;
+          diff &= ~(0xffu << (8 * j));
+          n.mism += flag_mismatch<T, PROP>(
+              (o >> (8 * j)) & 0xffu, (d >> (8 * j)) & 0xffu,
+              (y - y0 + 1) * kRowBits2 + C * lane + j + 1, X + j + G.nx * y, G, sm.flags, fdelta,
+              prop, h, PROP ? (j == 0 ? lows[0] : j == 1 ? lows[1] : j == 2 ? lows[2] : lows[3]) : T(0));
         }
       }
-      Low<T> nl[C];
-#pragma unroll
-      for (int j = 0; j < C; ++j) {
-        uint32_t m = w[j];
-        if (MODE == 1 && y0 == 0) m |= 0x0202u;  // no row below row 0
-        nl[j] = Low<T>{b[j].hi, b[j].lo, lower_codes<YP, 3u>(m)};
-      }
-      low[0] = Low<T>{lane_shift<kFromLeft>(nl[C - 1].hi, E.hi),
-                      lane_shift<kFromLeft>(nl[C - 1].lo, E.lo),
-                      lane_shift<kFromLeft>(nl[C - 1].w, E.w)};
-#pragma unroll
-      for (int j = 1; j < C; ++j) low[j] = nl[j - 1];
     }
-#pragma unroll
-    for (int j = 0; j < C; ++j) pr[j] = xp[j];
   };
   auto last_row = [&](int32_t q) {
     if (q == nq - 1 && y1 == G.ny) {
