@@ -21,7 +21,7 @@ sys.path.insert(0, ROOT)
 
 METRIC = "Gvoxels/s corrected at 512^3 fp32 ε=1e-4; batched vs plain; serve p50/p99 ms"
 HBM_PEAK_GBS = 8000.0
-ENGINE_SOURCES = ["engine.hip", "engine.hpp", "tiles.hpp", "common.hpp"]
+ENGINE_SOURCES = ["engine.hip", "engine.hpp", "tiles.hpp", "wave_tiles.hpp", "common.hpp"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "engine_perlin512_f32_traffic.json")
 
 
