@@ -1426,6 +1426,17 @@ __device__ __forceinline__ void apply_pass(const EngineArgs& a, int p, int q, ui
   __syncthreads();
 }
 
+// The totals of a counter set, by the first threads of a block.
+__device__ __forceinline__ void clear_tot(EngineCtl* ctl, int q) {
+  const int tid = threadIdx.x;
+  if (tid < kCtrSlots) {
+    ctl->tot[q][tid].edits = 0;
+    ctl->tot[q][tid].swept = 0;
+    ctl->tot[q][tid].sparse = 0;
+    ctl->tot[q][tid].flagged = 0;
+  }
+}
+
 // Block 0 at the start of round E: persist the field states of round E, clear
 // the next-but-one counters; a field finished at E (stop_on_done) or the
 // host's request ends the launch after this round (every block reads the word
@@ -1463,12 +1474,7 @@ __device__ __forceinline__ void persist_round(const EngineArgs& a, unsigned long
       __hip_atomic_load(a.stop_host, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == kStopNow)
     stop = true;
   if (stop) __hip_atomic_store(&ctl->stop.v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (tid < kCtrSlots) {
-    ctl->tot[qn][tid].edits = 0;
-    ctl->tot[qn][tid].swept = 0;
-    ctl->tot[qn][tid].sparse = 0;
-    ctl->tot[qn][tid].flagged = 0;
-  }
+  clear_tot(ctl, qn);
 }
 
 // ---------------------------------------------------------------------------
@@ -1534,12 +1540,7 @@ __device__ __forceinline__ void round_end(const EngineArgs& a, unsigned long lon
   }
   tiles = __syncthreads_or(tiles);
   sparse = __syncthreads_or(sparse);
-  if (tid < kCtrSlots) {
-    ctl->tot[qn][tid].edits = 0;
-    ctl->tot[qn][tid].swept = 0;
-    ctl->tot[qn][tid].sparse = 0;
-    ctl->tot[qn][tid].flagged = 0;
-  }
+  clear_tot(ctl, qn);
   if (tid == 0) {
     RoundTot rt{0, 0, 0, 0, {0, 0, 0, 0}};
 #pragma unroll 4
@@ -2217,7 +2218,11 @@ __global__ __launch_bounds__(256) void k_tail(EngineArgs a) {
       const FieldIter s = state_at<true>(d, E, E0);
       if (E > E0) store_iter(&as_global(d.st)->s[E & 1], s);
       if (a.out) a.out[fi] = s;
+      // (round E was handed back before its start: whoever runs it finds the
+      // counters of round E + 1 clear, as after a round's start)
+      if (rc == 2) clear_ctr(&as_global(d.st)->c[(E + 1) % 3]);
     }
+    if (rc == 2) clear_tot(ctl, (int)((E + 1) % 3));
     if (tid == 0) {
       ctl->epoch = E;
       ctl->rounds = E - E0;

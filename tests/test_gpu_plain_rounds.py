@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 import paper_2601_01787_amd as pmsz
-from test_gpu_parity import dev, host, random_case, same_bits
+from test_gpu_parity import dev, host, noise_case, random_case, same_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -37,3 +37,25 @@ def test_fields_in_rounds_of_different_kinds():
         g_ref, st_ref = oracle.correct(f, h, xi)
         assert st == {**st, **st_ref}
         assert same_bits(host(g), g_ref)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_round_handed_back_by_the_tail(dtype):
+    """A small field whose target list overflows in the tail, beside a large one
+    that needs no edit: the round handed back runs as a plain one, and every
+    statistic is that of the field alone."""
+    f, fhat, xi = noise_case(24, 0.2, 31)
+    f = f.astype(dtype)
+    lb, ub = oracle.bounds(f, xi)
+    fhat = np.minimum(np.maximum(fhat.astype(dtype), lb), ub)
+    still = random_case((2900, 2900), dtype, 5)[0]
+    cases = [(still, still.copy(), 0.05), (f, fhat, xi)]
+    fields = [(dev(a), dev(h), e) for a, h, e in cases]
+    stats = pmsz.correct_batched(fields)
+    tm, rounds = pmsz.last_timing(), pmsz.last_rounds()
+    assert tm["handbacks"] > 0, tm
+    for (a, h, e), (_, g, _), st in zip(cases, fields, stats):
+        g_ref, st_ref = oracle.correct(a, h, e)
+        assert st == {**st, **st_ref}
+        assert same_bits(host(g), g_ref)
+    assert sum(r["edits"] for r in rounds) == sum(st["steps_applied"] for st in stats)
