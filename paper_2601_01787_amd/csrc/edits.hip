@@ -367,6 +367,7 @@ constexpr int kDecThreads = 512;
 constexpr int kDecBytes = 16;                        // payload bytes per thread and tile
 constexpr int kDecTile = kDecThreads * kDecBytes;    // 8 KiB
 constexpr int kDecPer = kEditChunk / kDecThreads;    // entries per thread
+constexpr int kVarintMost = 10;                      // bytes of a 64-bit varint
 
 // Exclusive sum over the kDecThreads threads of a block; *total (all threads).
 template <class V>
@@ -418,9 +419,12 @@ __global__ __launch_bounds__(kDecThreads) void k_edit_decode(const uint8_t* tabl
   bool bad = false;
   if (tid < kDecBytes / 8) s_raw[tid] = 0ull;  // no varint runs into the chunk's first byte
   int found = 0;                               // varints that ended before this tile
+  // a varint takes ten bytes at most: a payload of longer ones is read no further
+  const int64_t most = 2 * kVarintMost * (int64_t)cnt;
   // the payload is 8-byte aligned, and so is every tile
   for (int64_t at = start & ~int64_t(7); found < 2 * cnt; at += kDecTile) {
-    if (at >= payload_bytes) {  // the payload ends inside the chunk
+    // the payload ends inside the chunk, or its entries cannot be this long
+    if (at >= payload_bytes || at >= start + most) {
       bad = true;
       break;
     }
@@ -461,15 +465,15 @@ __global__ __launch_bounds__(kDecThreads) void k_edit_decode(const uint8_t* tabl
       unsigned long long x = 0;
       int len = 0;
       for (; q < p; ++q, ++len)
-        if (len < 10) x |= (unsigned long long)(bytes[q] & 0x7f) << (7 * len);
+        if (len < kVarintMost) x |= (unsigned long long)(bytes[q] & 0x7f) << (7 * len);
       for (int k = 0; k < kDecBytes && mine > 0 && v < 2 * cnt; ++k) {
         const int64_t b = at + tid * kDecBytes + k;
         if (b < start) continue;
         const uint8_t y = bytes[p + k];
-        if (len < 10) x |= (unsigned long long)(y & 0x7f) << (7 * len);
+        if (len < kVarintMost) x |= (unsigned long long)(y & 0x7f) << (7 * len);
         ++len;
         if (y & 0x80) continue;
-        bad |= len > 10;
+        bad |= len > kVarintMost;
         if (v & 1) {
           s_steps[v >> 1] = x;
           bad |= x == 0ull;

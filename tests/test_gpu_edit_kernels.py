@@ -118,3 +118,26 @@ def test_valid_oddities_are_accepted():
         want = np.ones((1, 100), np.float32)
         want[0, 0] = want[0, 3] = np.nextafter(one, np.float32(0))
         assert np.array_equal(g, want)
+
+
+def test_malformed_payload_is_read_a_chunk_at_most():
+    """No chunk reads past the bytes its entries can take: 2048 chunks of a 64 MiB
+    payload in which no varint ends (a block that read on to the end of the
+    payload would make 128 GiB of it, more than 15 ms at any rate of the memory)."""
+    chunks, n = 2048, 2048 * 4096
+    head = torch.from_numpy(np.frombuffer(_stream(n, n, b""), np.uint8).copy()).cuda()
+    payload = torch.full((1 << 26,), 0x80, dtype=torch.uint8, device="cuda")
+    head[24:32] = torch.tensor(list(struct.pack("<Q", payload.numel())), dtype=torch.uint8)
+    fhat, s = torch.ones((1, n), device="cuda"), torch.cat([head, payload])
+    assert s.numel() == 40 + 16 * chunks + payload.numel()
+    ms = []
+    for _ in range(3):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        with pytest.raises(pmsz.PmszError) as e:
+            pmsz.decode_edits(fhat, s)
+        t1.record()
+        torch.cuda.synchronize()
+        assert e.value.status == 1
+        ms.append(t0.elapsed_time(t1))
+    assert min(ms) < 5.0, ms
