@@ -270,6 +270,15 @@ def directions(h, out=None):
     return out
 
 
+def _is_derived(t):
+    """True when a clone of t may be more than a copy of its memory: t is of a
+    subclass, has a place in an autograd graph or a forward-mode tangent, or
+    is a pending negation or a zero without memory."""
+    return (type(t) not in (torch.Tensor, torch.nn.Parameter) or
+            (t.requires_grad and torch.is_grad_enabled()) or t.is_neg() or t._is_zerotensor() or
+            torch.autograd.forward_ad.unpack_dual(t).tangent is not None)
+
+
 def correct(f, fhat, xi, *, inplace=False, max_iters=DEFAULT_MAX_ITERS, dirs_f=None, ws=None,
             mode="halving"):
     """Correct fhat toward f's topology within |g - f| <= xi.
@@ -282,8 +291,8 @@ def correct(f, fhat, xi, *, inplace=False, max_iters=DEFAULT_MAX_ITERS, dirs_f=N
     _dev(fhat, "fhat")
     if fhat.shape != f.shape or fhat.dtype != f.dtype or fhat.device != f.device:
         raise ValueError("f and fhat must match in shape, dtype and device")
-    # the library copies fhat on the way; a tensor in an autograd graph keeps its clone
-    copied = inplace or (fhat.requires_grad and torch.is_grad_enabled())
+    # the library copies fhat on the way, unless a copy carries more than its memory
+    copied = inplace or _is_derived(fhat)
     g = (fhat if inplace else fhat.clone()) if copied else torch.empty_like(fhat)
     grid = grid_of(f)
     emode = EDIT_MODES[mode]

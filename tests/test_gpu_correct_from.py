@@ -59,3 +59,36 @@ def test_overlapping_arrays_are_refused():
 
     assert call(1) == call(99) == 1
     assert call(0) == call(100) == 0
+
+
+def test_derived_tensors_keep_what_a_copy_carries():
+    """g starts as a clone of fhat where that is more than a copy of its memory: a
+    tangent, a pending negation, a zero without memory, a subclass with a clone of
+    its own, a place in an autograd graph."""
+    f, fhat, xi = random_case((6, 7, 8), np.float32, 11)
+    g_ref, _ = oracle.correct(f, fhat, xi)
+    d_f, d_h = dev(f), dev(fhat)
+    tangent = torch.ones_like(d_h)
+    with torch.autograd.forward_ad.dual_level():
+        dual = torch.autograd.forward_ad.make_dual(d_h, tangent)
+        g, _ = pmsz.correct(d_f, dual, xi)
+        g, t = torch.autograd.forward_ad.unpack_dual(g)
+        assert t is not None and torch.equal(t, tangent)
+        assert same_bits(host(g), g_ref)
+    neg = torch._neg_view(-d_h)
+    assert neg.is_neg()
+    g, st = pmsz.correct(d_f, neg, xi)
+    assert st["status"] == "OK" and not g.is_neg() and same_bits(host(g), g_ref)
+    zeros = torch._efficientzerotensor((6, 7, 8), device="cuda")
+    g, st = pmsz.correct(torch.zeros((6, 7, 8), device="cuda"), zeros, xi)
+    assert st["status"] == "OK" and not host(g).any()
+
+    class Doubled(torch.Tensor):
+        def clone(self):
+            return self.as_subclass(torch.Tensor) * 2
+
+    g, _ = pmsz.correct(d_f, (d_h / 2).as_subclass(Doubled), xi)
+    assert same_bits(host(g), g_ref)
+    g, _ = pmsz.correct(d_f, d_h.clone().requires_grad_(), xi)
+    assert g.grad_fn is not None
+    assert same_bits(host(g.detach()), g_ref)
