@@ -800,7 +800,8 @@ static size_t session_ctl_bytes(int32_t cap) {
          align_up(sizeof(FieldIter) * (size_t)cap);
 }
 
-// Labels by tiles, then pointer jumping over those left open (see labels.hip).
+// Labels by tiles or, on thin grids, from the neighbours, then pointer jumping over
+// those left open (see labels.hip).
 // ws: kLabelsWsBytes of device workspace.  Invalid direction codes and cycles
 // of pointers (possible only for caller-supplied bytes) are reported as
 // PMSZ_ERR_INVALID_ARG (the label arrays are then unspecified).
@@ -818,10 +819,21 @@ int labels_impl(const Geo& G, const uint8_t* dirs, int32_t* lmax, int32_t* lmin,
   memset(&tm.labels, 0, sizeof(tm.labels));
   HIP_TRY(engine_zero(ws, kLabelsWsBytes, s));
   HIP_TRY(hipEventRecord(tm.ev[0], s));
-  // the tile pass checks the codes of the labels asked for
-  if (!lmax || !lmin) HIP_TRY(launch_check_dirs(dirs, G, bad, s));
-  if (lmax || lmin) HIP_TRY(launch_labels_tile(dirs, G, lmax, lmin, flags, bad, s));
-  for (int pass = 1;; pass += kLabelBatch) {
+  int pass = 1;  // the next one
+  auto finish = [&]() -> int {
+    for (const int end = pass + kLabelBatch; pass < end; ++pass)
+      HIP_TRY(launch_labels_finish(lmax, lmin, G.n, flags, pass, s));
+    return PMSZ_OK;
+  };
+  if (labels_by_tiles(G)) {
+    // the tile pass checks the codes of the labels asked for
+    if (!lmax || !lmin) HIP_TRY(launch_check_dirs(dirs, G, bad, s));
+    if (lmax || lmin) HIP_TRY(launch_labels_tile(dirs, G, lmax, lmin, flags, bad, s));
+  } else {
+    HIP_TRY(launch_labels_init(dirs, G, lmax, lmin, flags, bad, s));
+    if ((lmax || lmin) && (r = finish())) return r;
+  }
+  for (;;) {
     HIP_TRY(hipEventRecord(tm.ev[1], s));
     HIP_TRY(hipMemcpyAsync(stage, ws, kLabelsWsBytes, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
@@ -833,8 +845,7 @@ int labels_impl(const Geo& G, const uint8_t* dirs, int32_t* lmax, int32_t* lmin,
       return fail(PMSZ_ERR_INVALID_ARG,
                   "label propagation did not settle in %d passes: the direction bytes do not form "
                   "a forest", pass);
-    for (int p = pass; p < pass + kLabelBatch; ++p)
-      HIP_TRY(launch_labels_finish(lmax, lmin, G.n, flags, p, s));
+    if ((r = finish())) return r;
   }
   for (int p = 0; p < kLabelMaxPasses; ++p) {
     if (lmax && (p == 0 || open[2 * (p - 1)])) tm.labels.passes_max = p + 1;

@@ -8,7 +8,8 @@
 // cycles).  A block resolves the pointers of one tile in LDS (k_labels_tile);
 // paths that leave the tile are followed on over the direction bytes, and the
 // few that do not end within kWalkHops steps are finished by pointer jumping
-// over the labels (k_labels_finish).
+// over the labels (k_labels_finish).  Grids too thin for tiles start with every
+// vertex at its neighbour (k_labels_init) and are finished in the same way.
 #include "launch.hpp"
 
 namespace pmsz {
@@ -260,6 +261,34 @@ k_labels_tile(const uint8_t* __restrict__ dirs_in, Geo G, int32_t tiles_x, int32
   if (lane == 0 && all_bad) atomicAdd(bad, all_bad);
 }
 
+// First pass over a grid that fills little of its tiles (labels_by_tiles): every
+// vertex labels itself (the extrema, and invalid codes, whose bytes are counted in
+// *bad) or, not final, its neighbour; k_labels_finish does the rest.
+__global__ __launch_bounds__(256) void k_labels_init(const uint8_t* __restrict__ dirs, Geo G,
+                                                     int32_t* lmax, int32_t* lmin,
+                                                     unsigned int* flags, unsigned long long* bad) {
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  unsigned long long nb = 0;
+  int open = 0;  // bit k: a label of nibble k is not final
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < G.n; i += stride) {
+    const int a = dirs[i] & 15, d = dirs[i] >> 4;
+    const int64_t x = i % G.nx, y = (i / G.nx) % G.ny, z = i / G.sxy;
+    const bool va = code_valid(a, x, y, z, G), vd = code_valid(d, x, y, z, G);
+    nb += !(va && vd);
+    const bool oa = va && a, od = vd && d;
+    if (lmax) lmax[i] = (int32_t)(oa ? ~(i + code_delta(a, G.nx, G.sxy)) : i);
+    if (lmin) lmin[i] = (int32_t)(od ? ~(i + code_delta(d, G.nx, G.sxy)) : i);
+    open |= (int)oa | ((int)od << 1);
+  }
+  const bool any_a = __ballot(open & 1) != 0ull, any_d = __ballot(open & 2) != 0ull;
+  if ((threadIdx.x & 63) == 0) {
+    if (lmax && any_a) flags[0] = 1u;
+    if (lmin && any_d) flags[1] = 1u;
+  }
+  nb = wave_sum(nb);
+  if ((threadIdx.x & 63) == 0 && nb) atomicAdd(bad, nb);
+}
+
 // Pass `pass` (from 1) over the labels that are not final, ~(vertex reached):
 // each follows up to kLabelHops of them, in place (whatever a thread reads is
 // an ancestor).  Skipped when the pass before left none; flags[2 pass +
@@ -295,17 +324,47 @@ hipError_t launch_check_dirs(const uint8_t* dirs, const Geo& G, unsigned long lo
   return hipGetLastError();
 }
 
+// Tiles of a grid.
+struct LabelTiles {
+  int64_t x, y, z;
+};
+static LabelTiles label_tiles(const Geo& G) {
+  const int ly = G.ndim == 3 ? 16 : 256, lz = G.ndim == 3 ? 16 : 1;
+  return LabelTiles{(G.nx + 63) / 64, (G.ny + ly - 1) / ly, (G.nz + lz - 1) / lz};
+}
+
+// A tile costs k_labels_tile about the same however few of its vertices lie in the
+// grid, so grids that fill less than a quarter of their tiles start from
+// k_labels_init.  Both ways, us, white noise / smooth: 4096 vertices per tile
+// (2048 x 2048 x 4) 294 / 319 by tiles, 261 / 441 from k_labels_init; 2048
+// (2048 x 2048 x 2) 274 / 324 and 136 / 272; 1024 (8 M x 4 in 2D) 1114 / 1177 and 250 /
+// 383; 64 (2 x 2 x 2 M) 6909 / 7166 and 142 / 188.  8192 and more: tiles (1024 x
+// 2048 x 8: 187 / 207 and 256 / 431).
+constexpr int64_t kTileShare = kTileVerts / 4;
+static_assert(((1ll << 31) / kTileShare + 1) * kTileThreads < (1ll << 32),
+              "a launch holds fewer than 2^32 threads");
+bool labels_by_tiles(const Geo& G) {
+  const LabelTiles t = label_tiles(G);
+  return G.n >= kTileShare * (t.x * t.y * t.z);
+}
+
+hipError_t launch_labels_init(const uint8_t* dirs, const Geo& G, int32_t* lmax, int32_t* lmin,
+                              unsigned int* flags, unsigned long long* bad, hipStream_t s) {
+  hipLaunchKernelGGL(k_labels_init, dim3(grid_for(G.n, 2048)), dim3(256), 0, s, dirs, G, lmax, lmin,
+                     flags, bad);
+  return hipGetLastError();
+}
+
 hipError_t launch_labels_tile(const uint8_t* dirs, const Geo& G, int32_t* lmax, int32_t* lmin,
                               unsigned int* flags, unsigned long long* bad, hipStream_t s) {
-  const int ly = G.ndim == 3 ? 16 : 256, lz = G.ndim == 3 ? 16 : 1;
-  const int64_t tx = (G.nx + 63) / 64, ty = (G.ny + ly - 1) / ly, tz = (G.nz + lz - 1) / lz;
-  const dim3 grid((unsigned)(tx * ty * tz));
+  const LabelTiles t = label_tiles(G);
+  const dim3 grid((unsigned)(t.x * t.y * t.z));
   if (G.ndim == 3)
-    hipLaunchKernelGGL(k_labels_tile<3>, grid, dim3(kTileThreads), 0, s, dirs, G, (int32_t)tx,
-                       (int32_t)ty, lmax, lmin, flags, bad);
+    hipLaunchKernelGGL(k_labels_tile<3>, grid, dim3(kTileThreads), 0, s, dirs, G, (int32_t)t.x,
+                       (int32_t)t.y, lmax, lmin, flags, bad);
   else
-    hipLaunchKernelGGL(k_labels_tile<2>, grid, dim3(kTileThreads), 0, s, dirs, G, (int32_t)tx,
-                       (int32_t)ty, lmax, lmin, flags, bad);
+    hipLaunchKernelGGL(k_labels_tile<2>, grid, dim3(kTileThreads), 0, s, dirs, G, (int32_t)t.x,
+                       (int32_t)t.y, lmax, lmin, flags, bad);
   return hipGetLastError();
 }
 

@@ -30,18 +30,22 @@ inline int64_t bitmap_words(int64_t n) { return (n + 31) / 32; }
 hipError_t launch_dirs(int dtype, const void* h, const Geo& G, uint8_t* dirs, hipStream_t s);
 
 // labels.hip
-// Labels: one pass over tiles (launch_labels_tile), then, when some paths are
-// not finished, pointer-jumping passes over the labels that are not final:
-// each follows up to kLabelHops links, and they are queued kLabelBatch at a
-// time between read-backs of their flags, at most kLabelMaxPasses with the
-// tile pass.  Labels workspace: [bad-code counter (8 bytes), padded to 256][two
-// words per pass: labels of that kind left open by it].
+// Labels: one pass over tiles (launch_labels_tile) or, where the grid fills
+// little of them (labels_by_tiles false), one that starts every vertex at its
+// neighbour (launch_labels_init); then pointer-jumping passes over the labels that
+// are not final: each follows up to kLabelHops links, and they are queued
+// kLabelBatch at a time between read-backs of their flags, at most kLabelMaxPasses
+// with the first.  Labels workspace: [bad-code counter (8 bytes), padded to
+// 256][two words per pass: labels of that kind left open by it].
 constexpr int kLabelHops = 8;
 constexpr int kLabelBatch = 4;
 constexpr int kLabelMaxPasses = 32;
 constexpr size_t kLabelsWsBytes = 256 + 8 * kLabelMaxPasses;
 hipError_t launch_check_dirs(const uint8_t* dirs, const Geo& G, unsigned long long* bad,
                              hipStream_t s);
+bool labels_by_tiles(const Geo& G);
+hipError_t launch_labels_init(const uint8_t* dirs, const Geo& G, int32_t* lmax, int32_t* lmin,
+                              unsigned int* flags, unsigned long long* bad, hipStream_t s);
 hipError_t launch_labels_tile(const uint8_t* dirs, const Geo& G, int32_t* lmax, int32_t* lmin,
                               unsigned int* flags, unsigned long long* bad, hipStream_t s);
 hipError_t launch_labels_finish(int32_t* lmax, int32_t* lmin, int64_t n, unsigned int* flags,

@@ -112,3 +112,37 @@ def test_verify_counts_at_block_edges(shape, dtype):
     rep = pmsz.verify(dev(f), dev(g), dev(fhat), xi)
     assert rep == oracle.verify(f, g, fhat, xi)
     assert rep["bound_violations"] == 1
+
+
+@pytest.mark.parametrize("shape", [(33, 33, 129), (18, 40, 200), (16, 16, 16), (15, 16, 16), (8, 50, 128),
+                                   (3000, 16), (3000, 15), (64, 900), (63, 900), (2, 2, 5000),
+                                   (5000, 3, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_both_sides_of_the_thin_rule(shape):
+    """Grids that fill a quarter of their tiles or more, and less."""
+    _check(random_case(shape, np.float32, 3)[0])
+    _check(random_case(shape, np.float32, 4, ties=True)[0])
+    ramp = np.arange(np.prod(shape), dtype=np.float64).reshape(shape)  # paths of full length
+    info = _check(ramp)
+    assert info["passes_max"] > 1 or max(shape) <= 64
+
+
+@pytest.mark.parametrize("shape", [(28, 28, 100), (9, 9, 100)], ids=["tiles", "thin"])
+@pytest.mark.parametrize("ring", ["pair", "loop_in_a_tile", "loop_across_tiles"])
+def test_cycles_on_both_sides_of_the_thin_rule(shape, ring):
+    d = pmsz.directions(dev(random_case(shape, np.float32, 6)[0]))
+    x0, x1 = {"pair": (63, 64), "loop_in_a_tile": (5, 50), "loop_across_tiles": (50, 75)}[ring]
+    for x in range(x0, x1):
+        d[2, 4, x] = (d[2, 4, x] & 0xF0) | 1
+        d[2, 4 if ring == "pair" else 5, x + 1] = (d[2, 4 if ring == "pair" else 5, x + 1] & 0xF0) | 9
+    if ring != "pair":
+        d[2, 4, x1] = (d[2, 4, x1] & 0xF0) | 2
+        d[2, 5, x0] = (d[2, 5, x0] & 0xF0) | 10
+    with pytest.raises(pmsz.PmszError) as e:
+        pmsz.labels(d)
+    assert e.value.status == 1
+
+
+def test_thin_grid_of_more_tiles_than_a_launch_holds():
+    """1 x 1 x (2^26 + 1): more than 2^22 tiles of 1024 threads each."""
+    h = np.random.default_rng(5).random((2 ** 26 + 1, 1, 1), np.float32)
+    _check(h)
