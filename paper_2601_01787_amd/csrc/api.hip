@@ -826,7 +826,7 @@ int labels_impl(const Geo& G, const uint8_t* dirs, int32_t* lmax, int32_t* lmin,
     return PMSZ_OK;
   };
   if (labels_by_tiles(G)) {
-    // the tile pass checks the codes of the labels asked for
+    // (the tile pass counts invalid bytes when both labels are asked for)
     if (!lmax || !lmin) HIP_TRY(launch_check_dirs(dirs, G, bad, s));
     if (lmax || lmin) HIP_TRY(launch_labels_tile(dirs, G, lmax, lmin, flags, bad, s));
   } else {

@@ -142,6 +142,15 @@ def test_cycles_on_both_sides_of_the_thin_rule(shape, ring):
     assert e.value.status == 1
 
 
+@pytest.mark.parametrize("shape", [(28, 28, 100), (9, 9, 100)], ids=["tiles", "thin"])
+def test_invalid_bytes_are_counted_once(shape):
+    d = pmsz.directions(dev(random_case(shape, np.float32, 6)[0]))
+    d[3, 3, 3] = 0x88  # both codes
+    d[3, 4, 70] = 0x08
+    with pytest.raises(pmsz.PmszError, match=r"\b2 direction bytes"):
+        pmsz.labels(d)
+
+
 def test_thin_grid_of_more_tiles_than_a_launch_holds():
     """1 x 1 x (2^26 + 1): more than 2^22 tiles of 1024 threads each."""
     h = np.random.default_rng(5).random((2 ** 26 + 1, 1, 1), np.float32)
