@@ -1226,8 +1226,7 @@ __device__ __forceinline__ void apply_dense(const ApplyField<T>& F, int32_t w0, 
       at = (long long)__hip_atomic_fetch_add(&F.cq->s[slot].nlist, (unsigned long long)total,
                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     at = __shfl(at, 0, 64);
-    const int32_t n = F.d->geo.n;
-    mark_range(F.d->geo, v0, v0 + 32 * kUnitWords < n ? v0 + 32 * kUnitWords - 1 : n - 1, F.nxt);
+    mark_range(F.d->geo, v0, tile_end(v0, 32 * kUnitWords, F.d->geo.n) - 1, F.nxt);
   }
   unsigned n_above = 0, n_all = 0;
   for (int l = 0; l < 64; l += 2) {

@@ -90,6 +90,17 @@ struct FastDiv {
 __host__ __device__ inline int32_t fdiv(int32_t n, FastDiv d) {
   return (int32_t)(((uint64_t)(uint32_t)n * d.m) >> d.sh);
 }
+// Sums of a coordinate and an extent that stay below 2^31 whatever the grid's
+// extents: the end of a tile of `size` that starts at `at` on an axis of n, and
+// the coordinate `step` (down to -1) from `at`, clamped to the axis.
+__host__ __device__ inline int32_t tile_end(int32_t at, int32_t size, int32_t n) {
+  return n - at > size ? at + size : n;
+}
+__host__ __device__ inline int32_t clamp_step(int32_t at, int32_t step, int32_t n) {
+  const int32_t left = n - 1 - at, v = at + (step < left ? step : left);
+  return v < 0 ? 0 : v;
+}
+
 inline FastDiv make_div(int64_t d) {
   int l = 0;
   while ((int64_t(1) << l) < d) ++l;
@@ -398,7 +409,7 @@ __device__ TileCounts tile3(TileLds<T>& sm, unsigned long long* red, const T* h_
   const int32_t bx = t32 % G.tiles_x, by = (t32 / G.tiles_x) % G.tiles_y,
                 bz = t32 / (G.tiles_x * G.tiles_y);
   const int32_t x0 = bx * TX, y0 = by * TY, z0 = bz * G.chunk;
-  const int32_t z1 = (z0 + G.chunk < G.nz) ? z0 + G.chunk : G.nz;
+  const int32_t z1 = tile_end(z0, G.chunk, G.nz);
 
   // Addressing: a uniform base per plane, at the tile's halo corner
   // (x0-1, y0-1), plus a 32-bit per-lane byte offset fixed for the tile, so
@@ -574,7 +585,7 @@ __device__ TileCounts tile2(TileLds<T>& sm, unsigned long long* red, const T* h_
   const int32_t t32 = (int32_t)tile;
   const int32_t bx = t32 % G.tiles_x, by = t32 / G.tiles_x;
   const int32_t x0 = bx * RX, y0 = by * G.chunk;
-  const int32_t y1 = (y0 + G.chunk < G.ny) ? y0 + G.chunk : G.ny;
+  const int32_t y1 = tile_end(y0, G.chunk, G.ny);
 
   // uniform base per row at the strip's halo corner x0-1, 32-bit lane offsets
   uint32_t offb[PER];
@@ -713,15 +724,12 @@ __device__ __forceinline__ int32_t tile_voxels(const TileGeo& G, int64_t tile) {
   if (G.ndim == 3) {
     const int32_t bx = t32 % G.tiles_x, by = (t32 / G.tiles_x) % G.tiles_y,
                   bz = t32 / (G.tiles_x * G.tiles_y);
-    const int32_t w = (bx * TX + TX <= G.nx) ? TX : G.nx - bx * TX;
-    const int32_t hgt = (by * TY + TY <= G.ny) ? TY : G.ny - by * TY;
-    const int32_t d = (bz * G.chunk + G.chunk <= G.nz) ? G.chunk : G.nz - bz * G.chunk;
-    return w * hgt * d;
+    return (tile_end(bx * TX, TX, G.nx) - bx * TX) * (tile_end(by * TY, TY, G.ny) - by * TY) *
+           (tile_end(bz * G.chunk, G.chunk, G.nz) - bz * G.chunk);
   }
   const int32_t bx = t32 % G.tiles_x, by = t32 / G.tiles_x;
-  const int32_t w = (bx * RX + RX <= G.nx) ? RX : G.nx - bx * RX;
-  const int32_t hgt = (by * G.chunk + G.chunk <= G.ny) ? G.chunk : G.ny - by * G.chunk;
-  return w * hgt;
+  return (tile_end(bx * RX, RX, G.nx) - bx * RX) *
+         (tile_end(by * G.chunk, G.chunk, G.ny) - by * G.chunk);
 }
 
 }  // namespace pmsz

@@ -302,11 +302,12 @@ __device__ __forceinline__ int64_t first_tile(int64_t vb, int32_t run) {
 struct Span {
   int32_t a, b;
 };
-__device__ __forceinline__ Span part_of(int32_t at, int32_t chunk, int32_t n, int32_t part,
+__host__ __device__ inline Span part_of(int32_t at, int32_t chunk, int32_t n, int32_t part,
                                         int32_t parts) {
   const int32_t each = parts == 1 ? chunk : (chunk + parts - 1) / parts;
-  const int32_t end = at + chunk < n ? at + chunk : n, a = at + part * each;
-  return Span{a, a + each < end ? a + each : end};
+  const int32_t end = tile_end(at, chunk, n), off = part * each;
+  if (off >= end - at) return Span{end, end};
+  return Span{at + off, tile_end(at + off, each, end)};
 }
 
 // Counts of a tile, per lane.
@@ -355,16 +356,16 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
   if (z0 >= z1) return LaneCounts{0, 0, 0};
   const int32_t nq = z1 - z0 + 2;
   auto clamp_to = [](int32_t v, int32_t n) { return v < 0 ? 0 : v < n ? v : n - 1; };
-  auto plane_at = [&](int32_t q) { return (int64_t)G.sxy * clamp_to(z0 - 1 + q, G.nz); };
+  auto plane_at = [&](int32_t q) { return (int64_t)G.sxy * clamp_step(z0, q - 1, G.nz); };
   // a uniform base per plane, at the first line loaded and column x0; from there
   // the lines' offsets (below 6 nx sizeof(T), which the host keeps under 2^32) and
   // the lanes'
-  const int32_t y_first = clamp_to(y0 - 1, G.ny);
+  const int32_t y_first = clamp_step(y0, -1, G.ny);
   const int64_t at0 = (int64_t)G.nx * y_first + x0;
   uint32_t row[V];
 #pragma unroll
   for (int r = 0; r < V; ++r)
-    row[r] = (uint32_t)G.nx * (uint32_t)(clamp_to(y0 - 1 + r, G.ny) - y_first);
+    row[r] = (uint32_t)G.nx * (uint32_t)(clamp_step(y0, r - 1, G.ny) - y_first);
 
   const int32_t X = x0 + lane;
   const bool in_x = X < G.nx;
@@ -413,8 +414,8 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
   // group's last.
   static_assert(R == 4 && V <= 8 && kEdgeGroup == 4, "lane layout of the edges");
   const int32_t ej = (lane >> 3) & 3, er = (lane & 7) < V ? lane & 7 : V - 1;
-  const int32_t e_row = G.nx * clamp_to(y0 - 1 + er, G.ny);
-  const uint32_t e_right = (uint32_t)(e_row + clamp_to(x0 + TX, G.nx));
+  const int32_t e_row = G.nx * clamp_step(y0, er - 1, G.ny);
+  const uint32_t e_right = (uint32_t)(e_row + clamp_step(x0, TX, G.nx));
   const uint32_t e_left = (uint32_t)(e_row + (x0 ? x0 - 1 : 0));
   const uint32_t e_own = (uint32_t)(e_row + x0);
   struct Edges {
@@ -652,7 +653,7 @@ __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelt
   if (y0 >= y1) return LaneCounts{0, 0, 0};
   const int32_t nq = y1 - y0 + 2;
   auto clamp_to = [](int32_t v, int32_t n) { return v < 0 ? 0 : v < n ? v : n - 1; };
-  auto row_at = [&](int32_t q) { return (int64_t)G.nx * clamp_to(y0 - 1 + q, G.ny); };
+  auto row_at = [&](int32_t q) { return (int64_t)G.nx * clamp_step(y0, q - 1, G.ny); };
 
   const int32_t X = x0 + C * lane;
   constexpr int NO = RAGGED ? C : 1;
@@ -705,7 +706,7 @@ __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelt
 
   // ---- the tile's edges
   {
-    const int32_t xr = clamp_to(x0 + RX, G.nx);
+    const int32_t xr = clamp_step(x0, RX, G.nx);
     const uint32_t gone_x = x0 == 0 ? 1u : 0u;
     auto edges_of = [&](gptr<const T> from, int32_t q, Edge2<T>& E) {
       E.right = from[row_at(q) + xr];
@@ -879,7 +880,7 @@ __device__ __forceinline__ LaneCounts wave_tile(LDS& sm, const int32_t* fdelta, 
                                            copy_to, part, parts);
   } else {
     const TileGeo G = uniform_geo(G_in);
-    if ((tile % G.tiles_x + 1) * RX > G.nx)
+    if (G.nx - tile % G.tiles_x * RX < RX)
       return wave_tile2_t<T, KIND, PROP, COPY, true>(sm, fdelta, h, f, dirs, bm, xi, G, tile, prop,
                                                      copy_to, part, parts);
     return wave_tile2_t<T, KIND, PROP, COPY, false>(sm, fdelta, h, f, dirs, bm, xi, G, tile, prop,

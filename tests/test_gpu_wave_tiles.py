@@ -5,6 +5,7 @@ an odd number of planes, both edit rules, detection boxes of a decomposed
 domain, and bounds missed in the last column, line or plane."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_2601_01787_amd as pmsz
@@ -69,3 +70,24 @@ def test_sweeps_validate_every_vertex(shape, bad):
         _, st = pmsz.correct(dev(f), g, xi, inplace=True)
         assert st["status"] == ("NONFINITE" if np.isnan(bad) else "INPUT_BOUND"), at
         assert same_bits(host(g), h)
+
+
+def test_directions_of_the_longest_row():
+    """1 x (2^31 - 1): the last tile's columns end one short of 2^31."""
+    n = 2 ** 31 - 1
+    h = torch.empty((1, n), device="cuda").uniform_(generator=torch.Generator("cuda").manual_seed(3))
+    d = pmsz.directions(h).view(-1)
+    h = h.view(-1)
+    for at in [*range(0, n, 1 << 28), n - 1000]:
+        a, b = max(at - 1, 0), min(at + (1 << 28) + 1, n)
+        v = h[a:b]
+        lo, hi = torch.full_like(v[:1], -torch.inf), torch.full_like(v[:1], torch.inf)
+        left, right = v[:-1], v[1:]
+        # (ties: the larger index is the higher)
+        up_r, up_l = torch.cat([right, lo]), torch.cat([lo, left])
+        mx = torch.where((up_r >= v) & (up_r >= up_l), 1, torch.where(up_l > v, 9, 0))
+        dn_r, dn_l = torch.cat([right, hi]), torch.cat([hi, left])
+        mn = torch.where((dn_l <= v) & (dn_l <= dn_r), 9, torch.where(dn_r < v, 1, 0))
+        want = (mx | (mn << 4)).to(torch.uint8)
+        i, j = (0 if a == 0 else 1), (len(v) if b == n else len(v) - 1)
+        assert torch.equal(d[a + i:a + j], want[i:j]), at
