@@ -326,22 +326,35 @@ void release_staging(Staging& s) {
   s.cap = 0;
 }
 
-// Events around the engine launch and the figures of the last run.
-// Plain rounds of a large batch queued between read-backs.  A plain round with
-// edits takes 25 to 35 us on a 512^3 field (1024 segments), a round of the engine 32 to
-// 47 us, and more with every segment a block has to itself; one with nothing left
-// to do costs two empty launches, about 4 us, and the rounds a field needs grow with
-// it.  Measured with 4 / 6 / 7 / 8 rounds: 257 x 253 x 190 targeted (94 segments) 520 /
-// 532 / 543 / 548 us, 512^3 1463 / 1457 / 1439 / 1433 us.
+// Plain rounds of a large batch queued between read-backs.  A round left to the
+// engine costs more the more segments a block has to itself, a plain round with
+// nothing to do two empty launches, about 6 us.  Whole calls with 4 / 6 / 8 / 10 / 12
+// rounds, us (Perlin noise, eps 1e-4; segments of 131072 vertices): 208^3 (69 segments)
+// 415 / 424 / 439 / 443 / 463, 400^3 (489) 902 / 907 / 897 / 903 / 918; 412^3 (534) 969 /
+// 958 / 952 / 957 / 971, 640^3 (2000) 2881 / 2840 / 2795 / 2810 / 2822; 656^3 (2154) 3105 /
+// 3056 / 3015 / 3021 / 3038, 1024 x 1024 x 768 binary64 (6144) 7808 / 7754 / 7700 / 7613 /
+// 7621, 20 2D fields of 3000^2 to 6000^2 9728 / 9507 / 9636 / 9416 / 9416.
 constexpr int kPlainRounds = 12;
 inline int plain_rounds_of(int64_t segs) { return segs >= 2048 ? kPlainRounds : segs >= 512 ? 8 : 4; }
 
+// Sweep kernels of those rounds: in all of them for more than kSweepFields
+// fields, else in the first two; a round that needs tiles later waits for a
+// read-back (a field of kSplitVoxels or more) or is the engine's.  A sweep with
+// nothing to do costs about 3 us, a read-back with its idle launches 85 us.  Two
+// sweeps against one, us: white noise that stays dense, 208^3 binary64 1480 -> 1228,
+// eight fields of 128^3 1619 -> 1561; fields that are sparse after round 1 within 2
+// us.  Sweeps in every round against two: sixteen sparse fields of 2000 x 2400 774
+// -> 799, sixteen dense ones of 144^3 3102 -> 2341; against one: 24 of the first 1031 ->
+// 1109, 24 of the second 4595 -> 3001.
+constexpr int32_t kSweepFields = 16;
+
+// Events around a call's launches and the figures of the last run.
 struct Timing {
   // start, after the directions, after the first sweep (split); start and end of
-  // a later group of launches (kGroup, kGroup + 1); then around the sweep of
-  // each plain round of a group (kSweeps + 2 i, + 1)
-  static constexpr int kGroup = 3, kSweeps = 5;
-  hipEvent_t ev[kSweeps + 2 * kPlainRounds] = {};
+  // a later group of launches (kGroup, kGroup + 1); around the first sweep of a
+  // group (kSweep, kSweep + 1)
+  static constexpr int kGroup = 3, kSweep = 5;
+  hipEvent_t ev[kSweep + 2] = {};
   uint64_t gen = 0;
   pmsz_timing last;
   pmsz_round rounds[kTraceRounds];
@@ -465,7 +478,7 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
   // each runs at its own occupancy, without the engine's register budget.  Small ones
   // keep the whole loop in one launch (the extra launches would cost more than they
   // save).
-  constexpr int kGroup = Timing::kGroup, kSweeps = Timing::kSweeps;
+  constexpr int kGroup = Timing::kGroup, kSweep = Timing::kSweep;
   if (timed) HIP_TRY(hipEventRecord(tm.ev[0], s));
   // (the first sweep of a large batch makes the directions on the way: both read f)
   const int first_kind = split && all_dirs ? KIND_FIRST : KIND_FIRST_GIVEN;
@@ -473,19 +486,20 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
     HIP_TRY(engine_dirs(dtype, dims, a.fd, n, P.total_tiles, s));
   if (timed) HIP_TRY(hipEventRecord(tm.ev[1], s));
   auto sweep = [&](int i) -> int {  // of a round's marked tiles
-    if (timed) HIP_TRY(hipEventRecord(tm.ev[kSweeps + 2 * i], s));
+    // (two events cost about 11 us: the later sweeps of a group are timed by their
+    // rounds' records)
+    const bool events = timed && i == 0;
+    if (events) HIP_TRY(hipEventRecord(tm.ev[kSweep], s));
     HIP_TRY(engine_sweep(dtype, KIND_NEXT, P.edit_mode != 0, dims, a, s));
-    if (timed) HIP_TRY(hipEventRecord(tm.ev[kSweeps + 2 * i + 1], s));
+    if (events) HIP_TRY(hipEventRecord(tm.ev[kSweep + 1], s));
     return PMSZ_OK;
   };
   const int n_plain = plain_rounds_of(P.total_segs);
-  // (a few fields are in sparse rounds after their second as a rule: a read-back for
-  // those that are not costs less than a sweep kernel in every round)
-  const bool sweep_all = n > 16;
+  const int n_sweeps = n > kSweepFields ? n_plain : std::min(n_plain, 2);
   auto plain_rounds = [&]() -> int {
     for (int i = 0; i < n_plain; ++i) {
-      if ((i == 0 || sweep_all) && (r = sweep(i))) return r;
-      a.next_sweep = sweep_all && i + 1 < n_plain;
+      if (i < n_sweeps && (r = sweep(i))) return r;
+      a.next_sweep = i + 1 < n_sweeps;
       HIP_TRY(engine_sparse(dtype, dims, a, s));
       HIP_TRY(engine_apply(dtype, a, s));
     }
@@ -516,7 +530,7 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
   bool late_only[kTraceRounds] = {};
   double sweep_ms = 0., engine_ms = 0.;
   int32_t sweeps = split ? 1 : 0, tail_rounds = 0, handbacks = 0;
-  int group_sweeps = split ? n_plain : 0;  // of the group of launches just read back
+  int group_sweeps = split ? n_sweeps : 0;  // of the group of launches just read back
   unsigned long long group_round = split ? 1 : 0;  // the round of the first of them
   for (int64_t group = 0;; ++group) {
     // the staging buffer is reused for the results: the upload above is
@@ -543,10 +557,13 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
       for (int i = 0; i < group_sweeps; ++i) {
         const unsigned long long E = group_round + (unsigned long long)i;
         // (a plain round without tiles to sweep: no sweep to count)
-        if ((i > 0 && !sweep_all) || E >= hc->epoch || E >= (unsigned long long)kTraceRounds ||
+        if (E >= hc->epoch || E >= (unsigned long long)kTraceRounds ||
             tr[kTraceSlots * E + 3] == tr[kTraceSlots * E + 6])
           continue;
-        HIP_TRY(hipEventElapsedTime(&ms, tm.ev[kSweeps + 2 * i], tm.ev[kSweeps + 2 * i + 1]));
+        if (i == 0)
+          HIP_TRY(hipEventElapsedTime(&ms, tm.ev[kSweep], tm.ev[kSweep + 1]));
+        else
+          ms = (float)((double)(tr[kTraceSlots * E + 1] - tr[kTraceSlots * E]) * 1e-5);
         sweep_ms += ms;
         all -= ms;
         ++sweeps;
@@ -565,7 +582,7 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
     if (!split && hc->handoff != kHandToEngine) break;
     a.has_fresh = 0;
     group_round = hc->epoch;
-    group_sweeps = split ? n_plain : 1;
+    group_sweeps = split ? n_sweeps : 1;
     if (timed) HIP_TRY(hipEventRecord(tm.ev[kGroup], s));
     if (split) {
       if ((r = plain_rounds())) return r;

@@ -2288,10 +2288,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   WaveLds<T, DIM, KIND>& sm = s_w[wave];
-  for (int k = lane; k < (int)(sizeof(sm.flags) / 4); k += 64) sm.flags[k] = 0u;
-  if (DIM == 3) set_flag_deltas(s_delta, kRowBits3, kRowBits3 * (TY + 2));
-  else set_flag_deltas(s_delta, kRowBits2, 0);
-  __syncthreads();
   EngineCtl* ctl = a.ctl;
   const unsigned long long E = ctl->epoch;  // written by the previous launch
   if (KIND == KIND_NEXT) {
@@ -2299,6 +2295,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     // set only widen a later one)
     if (a.plain && (ctl->idle || !(ctl->kinds & kKindTiles))) return;
   }
+  for (int k = lane; k < (int)(sizeof(sm.flags) / 4); k += 64) sm.flags[k] = 0u;
+  if (DIM == 3) set_flag_deltas(s_delta, kRowBits3, kRowBits3 * (TY + 2));
+  else set_flag_deltas(s_delta, kRowBits2, 0);
+  __syncthreads();
   const int p = (int)(E & 1), q = (int)(E % 3);
   auto counters = [&](int f) { return &as_global(a.fd[f].st)->c[q].s[ctr_slot()]; };
   unsigned long long* const all_sw = &ctl->tot[q][ctr_slot()].swept;
