@@ -58,23 +58,24 @@ __device__ __forceinline__ uint32_t leb_len(unsigned long long v) {
   return n;
 }
 
-// Exclusive sum over the 256 threads of a block; *total (all threads).
-__device__ __forceinline__ unsigned long long block_excl(unsigned long long v,
-                                                         unsigned long long* sh,
-                                                         unsigned long long* total) {
+// Exclusive sum over the THREADS threads of a block; *total (all threads).
+template <int THREADS, class V>
+__device__ __forceinline__ V block_excl(V v, V* sh, V* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  unsigned long long x = v;
+  V x = v;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const unsigned long long y = __shfl_up(x, o, 64);
+    const V y = __shfl_up(x, o, 64);
     if (lane >= o) x += y;
   }
   if (lane == 63) sh[wave] = x;
   __syncthreads();
-  unsigned long long before = 0, all = 0;
-  for (int w = 0; w < 4; ++w) {
-    if (w < wave) before += sh[w];
-    all += sh[w];
+  V before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < THREADS / 64; ++w) {
+    const V t = sh[w];
+    before += w < wave ? t : V(0);
+    all += t;
   }
   __syncthreads();
   *total = all;
@@ -96,10 +97,18 @@ __device__ __forceinline__ unsigned long long block_excl(unsigned long long v,
 // values; count and compaction passes whose threads each took 16 consecutive
 // values read the fields twice at 1.1 and 0.5 TB/s.  512^3 binary32, 1.8 M
 // changes: find 203 us (5.3 TB/s), emit 81 us, scans 2 x 19 us, write 15 us;
-// the call 3.39 ms before, 0.36 ms now.
+// the call 3.39 ms before, 0.36 ms now.  Spans with many changes are listed word
+// by word and written four entries per thread at a time (a lane per list and one
+// entry at a time: 2^18 binary32 values, all changed, 156 us; now 87 us).
 constexpr int kSpan = 16384;            // vertices per block
 constexpr int kWaveSpan = kSpan / 4;    // per wave: 64 ballots, one per lane
 constexpr int kFindLoads = 8;           // ballots whose loads are in flight together
+// Changes of 64 vertices that one lane of `emit` lists by itself.  Where the spans
+// fill the chip the lanes that wait for the longest list cost their issue slots, else
+// only the time of that list (2^27 binary32 values, a tenth changed: 1012 us at 32, 730
+// at 12; 2^18: 61 and 76).
+constexpr int kDenseWord = 32, kDenseWordFull = 12;
+constexpr int64_t kFullSpans = 512;
 
 struct EncSpan {
   uint32_t count, last;           // changes; last changed vertex + 1 (0: none)
@@ -253,7 +262,7 @@ __global__ __launch_bounds__(256) void k_edit_emit(const T* fhat, const T* g, in
                                    : change_bits<T>(fhat, g, n, v0);
   unsigned long long total;
   int64_t r = (int64_t)spans[blockIdx.x].rank +
-              (int64_t)block_excl((unsigned long long)__popcll(w), sh, &total);
+              (int64_t)block_excl<256, unsigned long long>(__popcll(w), sh, &total);
   // the changed vertex before this thread's word (+ 1)
   uint32_t last = w ? (uint32_t)(v0 + 64 * lane + 64 - __clzll(w)) : 0u;
 #pragma unroll
@@ -270,18 +279,55 @@ __global__ __launch_bounds__(256) void k_edit_emit(const T* fhat, const T* g, in
   for (int k = 0; k < wave; ++k) prev = s_last[k] > prev ? s_last[k] : prev;
   const gptr<const T> a = as_global(fhat);
   const gptr<const T> b = as_global(g);
-  unsigned long long bits = w, len = 0;
-  while (bits) {
-    const int64_t i = v0 + 64 * lane + (__ffsll(bits) - 1);
-    bits &= bits - 1;
-    const unsigned long long st = order_key(a[i]) - order_key(b[i]);
-    len += leb_len((unsigned long long)(i - (int64_t)prev)) + leb_len(st);
-    if (r < cap) {
-      idx[r] = (uint32_t)i;
-      steps[r] = st;
+  unsigned long long len = 0;
+  auto entry = [&](int64_t i, int64_t rank, uint32_t before_i, T x, T y) {
+    const unsigned long long st = order_key(x) - order_key(y);
+    len += leb_len((unsigned long long)(i - (int64_t)before_i)) + leb_len(st);
+    if (rank < cap) {
+      idx[rank] = (uint32_t)i;
+      steps[rank] = st;
     }
-    prev = (uint32_t)(i + 1);
-    ++r;
+  };
+  if (__ballot(__popcll(w) > (gridDim.x < kFullSpans ? kDenseWord : kDenseWordFull))) {
+    // many changes: word by word, a lane per bit
+    const int32_t r0 = __builtin_amdgcn_readfirstlane((int)r);  // (below 2^31)
+    uint32_t seen = 0, last_i = (uint32_t)__builtin_amdgcn_readfirstlane((int)prev);
+    for (int k0 = 0; k0 < 64; k0 += kFindLoads) {
+      unsigned long long word[kFindLoads], any = 0;
+#pragma unroll
+      for (int k = 0; k < kFindLoads; ++k) {
+        word[k] = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)w, k0 + k) |
+                  (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(w >> 32), k0 + k)
+                      << 32;
+        any |= word[k];
+      }
+      if (any == 0) continue;
+      T x[kFindLoads], y[kFindLoads];
+#pragma unroll
+      for (int k = 0; k < kFindLoads; ++k) {
+        const int64_t i = v0 + 64 * (k0 + k) + lane;
+        const int64_t j = i < n ? i : n - 1;
+        x[k] = a[j];
+        y[k] = b[j];
+      }
+#pragma unroll
+      for (int k = 0; k < kFindLoads; ++k) {
+        const int64_t i0 = v0 + 64 * (k0 + k);
+        const unsigned long long below = word[k] & ((1ull << lane) - 1ull);
+        if ((word[k] >> lane) & 1ull)
+          entry(i0 + lane, (int64_t)r0 + seen + __popcll(below),
+                below ? (uint32_t)(i0 + 64 - __clzll(below)) : last_i, x[k], y[k]);
+        if (word[k]) last_i = (uint32_t)(i0 + 64 - __clzll(word[k]));
+        seen += __popcll(word[k]);
+      }
+    }
+  } else {
+    for (unsigned long long bits = w; bits; bits &= bits - 1) {
+      const int64_t i = v0 + 64 * lane + (__ffsll(bits) - 1);
+      entry(i, r, prev, a[i], b[i]);
+      prev = (uint32_t)(i + 1);
+      ++r;
+    }
   }
   len = block_sum(len, sh);
   if (threadIdx.x == 0) spans[blockIdx.x].bytes = len;
@@ -298,13 +344,13 @@ __device__ __forceinline__ uint8_t* put_leb(uint8_t* p, unsigned long long v) {
 
 // Header, table and payload.  Writes nothing when the edits exceed cap or the
 // stream exceeds out_cap.
-template <class T>
-__global__ __launch_bounds__(256) void k_edit_write(const EncSpan* spans, const EncTotal* total,
+template <class T, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_edit_write(const EncSpan* spans, const EncTotal* total,
                                                     const uint32_t* idx,
                                                     const unsigned long long* steps, int64_t n,
                                                     int64_t cap, unsigned long long out_cap,
                                                     uint8_t* out) {
-  __shared__ unsigned long long sh[4];
+  __shared__ unsigned long long sh[THREADS / 64];
   const unsigned long long ne = total->edits, nb = total->bytes;
   const unsigned long long nch = (ne + kEditChunk - 1) / kEditChunk;
   const unsigned long long head = 40 + 16 * nch;
@@ -319,31 +365,47 @@ __global__ __launch_bounds__(256) void k_edit_write(const EncSpan* spans, const 
     h[3] = nb;
     h[4] = (unsigned long long)kEditChunk | (nch << 32);
   }
+  // U entries per thread at a time: their lengths (at most 15 bytes) are scanned together,
+  // in 16 bits each
+  constexpr int U = 4;
+  static_assert(THREADS * 15 < (1 << 16), "a sum of lengths fits its field");
   const EncSpan sp = spans[blockIdx.x];
   unsigned long long at = sp.off;
-  for (uint32_t base = 0; base < sp.count; base += 256) {
-    const uint32_t k = base + threadIdx.x;
-    const int64_t r = (int64_t)sp.rank + k;
-    const bool mine = k < sp.count;
-    unsigned long long gap = 0, st = 0;
-    uint32_t len = 0, prev = 0;
-    if (mine) {
-      prev = r ? idx[r - 1] + 1u : 0u;
-      gap = (unsigned long long)(idx[r] - prev);
-      st = steps[r];
-      len = leb_len(gap) + leb_len(st);
+  for (uint32_t base = 0; base < sp.count; base += THREADS * U) {
+    unsigned long long gap[U], st[U], lens = 0;
+    uint32_t prev[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t k0 = base + THREADS * u, k = k0 + threadIdx.x;
+      prev[u] = 0;
+      gap[u] = st[u] = 0;
+      if (k0 >= sp.count) continue;
+      const int64_t r = (int64_t)sp.rank + (k < sp.count ? k : k0);
+      prev[u] = r ? idx[r - 1] + 1u : 0u;
+      gap[u] = (unsigned long long)(idx[r] - prev[u]);
+      st[u] = steps[r];
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (base + THREADS * u + threadIdx.x < sp.count)
+        lens |= (unsigned long long)(leb_len(gap[u]) + leb_len(st[u])) << (16 * u);
     unsigned long long all;
-    const unsigned long long o = at + block_excl(len, sh, &all);
-    if (mine) {
-      put_leb(put_leb(out + head + o, gap), st);
-      if (r % kEditChunk == 0) {
-        unsigned long long* t = (unsigned long long*)(out + 40 + 16 * (r / kEditChunk));
-        t[0] = o;
-        t[1] = prev ? (unsigned long long)prev - 1ull : ~0ull;
+    const unsigned long long ex = block_excl<THREADS, unsigned long long>(lens, sh, &all);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t k = base + THREADS * u + threadIdx.x;
+      const unsigned long long o = at + ((ex >> (16 * u)) & 0xffffull);
+      if (k < sp.count) {
+        put_leb(put_leb(out + head + o, gap[u]), st[u]);
+        const int64_t r = (int64_t)sp.rank + k;
+        if (r % kEditChunk == 0) {
+          unsigned long long* t = (unsigned long long*)(out + 40 + 16 * (r / kEditChunk));
+          t[0] = o;
+          t[1] = prev[u] ? (unsigned long long)prev[u] - 1ull : ~0ull;
+        }
       }
+      at += (all >> (16 * u)) & 0xffffull;
     }
-    at += all;
   }
 }
 
@@ -368,30 +430,6 @@ constexpr int kDecBytes = 16;                        // payload bytes per thread
 constexpr int kDecTile = kDecThreads * kDecBytes;    // 8 KiB
 constexpr int kDecPer = kEditChunk / kDecThreads;    // entries per thread
 constexpr int kVarintMost = 10;                      // bytes of a 64-bit varint
-
-// Exclusive sum over the kDecThreads threads of a block; *total (all threads).
-template <class V>
-__device__ __forceinline__ V dec_excl(V v, V* sh, V* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  V x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const V y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) sh[wave] = x;
-  __syncthreads();
-  V before = 0, all = 0;
-#pragma unroll
-  for (int w = 0; w < kDecThreads / 64; ++w) {
-    const V t = sh[w];
-    before += w < wave ? t : V(0);
-    all += t;
-  }
-  __syncthreads();
-  *total = all;
-  return before + x - v;
-}
 
 template <class T>
 __global__ __launch_bounds__(kDecThreads) void k_edit_decode(const uint8_t* table,
@@ -456,7 +494,7 @@ __global__ __launch_bounds__(kDecThreads) void k_edit_decode(const uint8_t* tabl
       mine += __popcll(ends);
     }
     int all;
-    int v = found + dec_excl<int>(mine, s_cnt, &all);  // (its barriers publish s_raw)
+    int v = found + block_excl<kDecThreads, int>(mine, s_cnt, &all);  // (its barriers publish s_raw)
     if (mine && v < 2 * cnt) {
       // the part of this thread's first varint that lies before its bytes
       int p = kDecBytes + tid * kDecBytes;
@@ -506,7 +544,7 @@ __global__ __launch_bounds__(kDecThreads) void k_edit_decode(const uint8_t* tabl
     if (e < cnt) sum += (unsigned long long)s_at[e] + 1ull;
   }
   unsigned long long all;
-  unsigned long long i = first + dec_excl<unsigned long long>(sum, s_sum, &all);
+  unsigned long long i = first + block_excl<kDecThreads, unsigned long long>(sum, s_sum, &all);
 #pragma unroll
   for (int k = 0; k < kDecPer; ++k) {
     const int e = tid * kDecPer + k;
@@ -608,9 +646,16 @@ static int encode_t(const T* fhat, const T* g, int64_t n, int64_t cap, char* ws,
   EDIT_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_edit_scan<1>, dim3(1), dim3(1024), 0, s, spans, L.nspans, total);
   EDIT_TRY(hipGetLastError());
-  hipLaunchKernelGGL(k_edit_write<T>, grid, block, 0, s, (const EncSpan*)spans,
-                     (const EncTotal*)total, (const uint32_t*)idx,
-                     (const unsigned long long*)steps, n, cap, (unsigned long long)out_cap, out);
+  // (twice the threads per span where the spans leave the chip idle: 2^18 binary64
+  // values, all changed, 126 -> 109 us; 2^27, one in 74 changed, 865 -> 888)
+  if (L.nspans < kFullSpans)
+    hipLaunchKernelGGL((k_edit_write<T, 512>), grid, dim3(512), 0, s, (const EncSpan*)spans,
+                       (const EncTotal*)total, (const uint32_t*)idx,
+                       (const unsigned long long*)steps, n, cap, (unsigned long long)out_cap, out);
+  else
+    hipLaunchKernelGGL((k_edit_write<T, 256>), grid, block, 0, s, (const EncSpan*)spans,
+                       (const EncTotal*)total, (const uint32_t*)idx,
+                       (const unsigned long long*)steps, n, cap, (unsigned long long)out_cap, out);
   EDIT_TRY(hipGetLastError());
   EncTotal h = {0, 0};
   EDIT_TRY(hipMemcpyAsync(&h, total, sizeof(h), hipMemcpyDeviceToHost, s));

@@ -57,6 +57,23 @@ def test_span_edges(dtype, n):
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("spans", [3, 513])
+def test_spans_with_many_changes(dtype, spans):
+    """Words of 64 vertices with up to 64 changes beside empty ones, in grids on
+    both sides of 512 spans: listed by lane or by word, written by 512 or 256
+    threads."""
+    n = spans * 16384 - 77
+    rng = np.random.default_rng(spans)
+    share = rng.choice([0.0, 0.02, 0.15, 0.3, 0.6, 1.0], size=n // 64 + 1)
+    if spans > 3:  # (the oracle takes a second per million entries)
+        share[rng.uniform(size=share.size) < 0.9] = 0.0
+    fhat = (rng.standard_normal(n) * 3).astype(dtype)
+    m = rng.uniform(size=n) < np.repeat(share, 64)[:n]
+    g = np.where(m, fhat - dtype(1e-3) * rng.uniform(size=n).astype(dtype), fhat).astype(dtype)
+    _round_trip(fhat, g)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
 def test_long_gaps_and_no_room_for_the_change_bits(dtype):
     n = 40 * 16384 + 5
     fhat, g = _case(dtype, n, 0.0, 3)
