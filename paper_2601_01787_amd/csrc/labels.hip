@@ -342,13 +342,15 @@ static LabelTiles label_tiles(const Geo& G) {
 // (2048 x 2048 x 4) 294 / 319 by tiles, 261 / 441 from k_labels_init; 2048
 // (2048 x 2048 x 2) 274 / 324 and 136 / 272; 1024 (8 M x 4 in 2D) 1114 / 1177 and 250 /
 // 383; 64 (2 x 2 x 2 M) 6909 / 7166 and 142 / 188.  8192 and more: tiles (1024 x
-// 2048 x 8: 187 / 207 and 256 / 431).
+// 2048 x 8: 187 / 207 and 256 / 431).  A grid within one tile is one launch by
+// tiles and five the other way (3 x 3 x 3: 55 and 64).
 constexpr int64_t kTileShare = kTileVerts / 4;
 static_assert(((1ll << 31) / kTileShare + 1) * kTileThreads < (1ll << 32),
               "a launch holds fewer than 2^32 threads");
 bool labels_by_tiles(const Geo& G) {
   const LabelTiles t = label_tiles(G);
-  return G.n >= kTileShare * (t.x * t.y * t.z);
+  const int64_t tiles = t.x * t.y * t.z;
+  return tiles == 1 || G.n >= kTileShare * tiles;
 }
 
 hipError_t launch_labels_init(const uint8_t* dirs, const Geo& G, int32_t* lmax, int32_t* lmin,
