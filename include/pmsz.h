@@ -187,7 +187,7 @@ int pmsz_correct_mode(const pmsz_grid* grid, const void* f, void* g, double xi,
 
 /* pmsz_correct_mode with fhat in an array of its own: g receives fhat, then the
  * edits, in one pass less over both than a copy before the call.  fhat must be
- * g itself or not overlap it.  After a validation failure g holds fhat; after an
+ * g itself, or neither f nor fhat may overlap g.  After a validation failure g holds fhat; after an
  * argument error it is unchanged, after a device error unspecified. */
 int pmsz_correct_from(const pmsz_grid* grid, const void* f, const void* fhat, void* g, double xi,
                       const uint8_t* dirs_f, int edit_mode, void* ws, size_t ws_bytes,

@@ -1000,9 +1000,13 @@ int pmsz_correct_from(const pmsz_grid* grid, const void* f, const void* fhat, vo
   if ((uintptr_t)ws % kAlign) return fail(PMSZ_ERR_INVALID_ARG, "workspace not 256-byte aligned");
   const size_t field_bytes = (size_t)(grid->nx * grid->ny * grid->nz) *
                              (grid->dtype == PMSZ_F64 ? 8 : 4);
-  if (fhat != g && (const char*)fhat < (const char*)g + field_bytes &&
-      (const char*)g < (const char*)fhat + field_bytes)
-    return fail(PMSZ_ERR_INVALID_ARG, "fhat overlaps g");
+  auto overlaps_g = [&](const void* a) {
+    return (const char*)a < (const char*)g + field_bytes &&
+           (const char*)g < (const char*)a + field_bytes;
+  };
+  // (the first sweep reads f and fhat while it writes g)
+  if (fhat != g && overlaps_g(fhat)) return fail(PMSZ_ERR_INVALID_ARG, "fhat overlaps g");
+  if (fhat != g && overlaps_g(f)) return fail(PMSZ_ERR_INVALID_ARG, "f overlaps g");
   pmsz_field one;
   one.grid = *grid;
   one.f = f;

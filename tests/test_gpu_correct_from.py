@@ -61,6 +61,22 @@ def test_overlapping_arrays_are_refused():
     assert call(0) == call(100) == 0
 
 
+def test_g_over_f_is_refused_where_fhat_is_separate():
+    buf = torch.zeros(300, device="cuda")
+    f, fhat = buf[100:200].view(10, 10), torch.zeros((10, 10), device="cuda")
+    grid, st = pmsz.grid_of(f), pmsz.Stats()
+    ws = pmsz.workspace(grid, pmsz.WS_CORRECT, f.device)
+
+    def call(at, h=fhat):
+        p = [ctypes.c_void_p(t.data_ptr()) for t in (f, h, buf[at:], ws)]
+        return pmsz.load().pmsz_correct_from(ctypes.byref(grid), *p[:3], 0.1, None, 0, p[3],
+                                             ws.numel(), 10, ctypes.byref(st), None)
+
+    assert [call(at) for at in (1, 100, 199)] == [1, 1, 1]
+    assert [call(at) for at in (0, 200)] == [0, 0]
+    assert call(100, f) == 0  # all three the same array, as in a call in place
+
+
 def test_derived_tensors_keep_what_a_copy_carries():
     """g starts as a clone of fhat where that is more than a copy of its memory: a
     tangent, a pending negation, a zero without memory, a subclass with a clone of
