@@ -408,30 +408,33 @@ int pmsz_session_destroy(pmsz_session* s);
  * events recorded on the caller's stream around each launch, and the work it
  * did.  Used by the benchmark for roofline figures. */
 typedef struct {
-  double engine_ms;  /* the persistent correction kernel (all its launches),
-                        with round 0's apply kernel of large batches and the
-                        tail kernel                                           */
+  double engine_ms;  /* the launches after the directions, without the sweep
+                        kernels: the persistent correction kernel, the tail
+                        kernel and, in large batches (2^23 vertices or more),
+                        the other kernels of rounds run as plain kernels       */
   int64_t rounds;    /* detect/apply rounds run                               */
   int64_t swept;     /* vertices examined by detect passes, all rounds        */
   int64_t edits;     /* value changes, all fields                             */
   int64_t voxels;    /* vertices of the batch                                 */
   int64_t tiles;     /* tiles of the batch                                    */
   int32_t grid;      /* blocks of the cooperative launch                      */
-  int32_t sweeps;    /* tile sweeps run as kernels of their own (large
-                        batches: 2 for rounds 0 and 1, one more per later
-                        round with a large tile sweep; else 0)                 */
+  int32_t sweeps;    /* tile sweeps run as kernels of their own: in large
+                        batches the first round's and those of later plain
+                        rounds that had tiles to sweep; one after a handback   */
   double first_round_ms; /* first round: validation, detect, apply            */
   double detect_ms;  /* detect phases of the later rounds (block 0's clock)    */
   double apply_ms;   /* apply phases of the later rounds                       */
-  double dirs_ms;    /* directions of f, computed before the correction kernel
-                        (0 when the caller gave them)                           */
-  double sweep_ms;   /* the sweep kernels; engine_ms covers the engine
-                        launches only (with the tail kernel's)                  */
+  double dirs_ms;    /* directions of f, computed before the correction (0 when
+                        the caller gave them, and for large batches, whose
+                        first sweep makes them)                                 */
+  double sweep_ms;   /* the sweep kernels: by events around the first of those
+                        queued together, by their rounds' records (which hold
+                        the round's sparse examinations too) for the others     */
   int32_t tail_rounds; /* rounds run by the tail kernel: the sparse rounds
                         after a round with few edits, on the blocks of one
                         XCD (Sec. IV-A's loop, unchanged)                       */
   int32_t handbacks; /* times the tail kernel stopped before a round with
-                        tile sweeps and the engine was launched again          */
+                        tile sweeps, which a sweep kernel then began            */
 } pmsz_timing;
 int pmsz_last_timing(pmsz_timing* out);
 

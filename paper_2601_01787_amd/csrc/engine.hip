@@ -1086,13 +1086,11 @@ __device__ __forceinline__ void apply_unit(const EngineArgs& a, int64_t u, int p
 }
 
 // ---------------------------------------------------------------------------
-// Apply pass of a plain round (engine_round), by waves.  A wave takes runs of
-// 256-word units of the flag bitmaps (four words per lane, the next unit's
-// loads in flight), or of 16-word units where there are fewer large ones than
-// waves (small fields: each wave's edits are one chain).  Targets of sparse units gather in an LDS list of the wave's and are
-// edited 64 at a time when it is full, the field changes or the wave is done; a
-// unit with more targets than the list holds is edited in place, 64
-// consecutive vertices at a time.
+// Apply pass of a plain round (k_apply), by waves.  A wave takes runs of 256-word
+// units of the flag bitmaps (four words per lane, the next unit's loads in flight).
+// Targets of sparse units gather in an LDS list of the wave's and are edited 64 at a
+// time when it is full, the field changes or the wave is done; a unit with more
+// targets than the list holds is edited in place, 64 consecutive vertices at a time.
 //
 // What bounds the pass is memory: a sparse round reads the bitmap, and each
 // edit touches a line of f and of g.  With a block per 4096-word segment, every
@@ -1103,7 +1101,6 @@ __device__ __forceinline__ void apply_unit(const EngineArgs& a, int64_t u, int p
 // ---------------------------------------------------------------------------
 constexpr int kUnitWords = 256;
 constexpr int kWaveList = kApplyCap / 4;
-constexpr int kSmallUnit = kWaveList / 32;  // words that fit the list whatever they hold
 
 // What a wave needs of the field it works on, in scalar registers.
 template <class T>
@@ -1282,9 +1279,8 @@ __device__ __forceinline__ void apply_pass(const EngineArgs& a, int p, int q, ui
   uint32_t* const list = list_all + wave * kWaveList;
   EngineCtl* const ctl = a.ctl;
   const int64_t waves = (int64_t)gridDim.x * 4;
-  const bool wide = a.total_segs * (kSegWords / kUnitWords) >= waves;
-  const int32_t unit = wide ? kUnitWords : kSmallUnit;
-  const int32_t per_seg = (int32_t)kSegWords / unit;
+  constexpr int32_t unit = kUnitWords;
+  constexpr int32_t per_seg = (int32_t)kSegWords / unit;
   const int64_t units = a.total_segs * per_seg;
   // units of a run: as many as share the waves evenly, within one segment
   int run_log = 0;
@@ -1357,14 +1353,11 @@ __device__ __forceinline__ void apply_pass(const EngineArgs& a, int p, int q, ui
     if (idle) continue;
     const int32_t seg = (int32_t)(sg - seg0);
     int32_t w0 = seg * (int32_t)kSegWords + (int32_t)(u0 % per_seg) * unit;
-    const int32_t wl = wide ? 4 * lane : lane;  // this lane's (first) word of a unit
+    const int32_t wl = 4 * lane;  // this lane's first word of a unit
     // (the bitmap ends on a 256-byte boundary, clear past the field)
     auto load = [&](int32_t at) {
       U32x4 x = {0u, 0u, 0u, 0u};
-      if (at + wl < F.words) {
-        if (wide) x = *(gptr<const U32x4>)(F.bm + at + wl);
-        else if (lane < kSmallUnit) x.x = F.bm[at + wl];
-      }
+      if (at + wl < F.words) x = *(gptr<const U32x4>)(F.bm + at + wl);
       return x;
     };
     U32x4 next = load(w0);
@@ -1373,10 +1366,7 @@ __device__ __forceinline__ void apply_pass(const EngineArgs& a, int p, int q, ui
       if (k + 1 < (1 << run_log)) next = load(w0 + unit);
       const uint32_t any = w.x | w.y | w.z | w.w;
       if (__ballot(any != 0u) == 0ull) continue;
-      if (any) {
-        if (wide) *(gptr<U32x4>)(F.bm + w0 + wl) = U32x4{0u, 0u, 0u, 0u};
-        else F.bm[w0 + wl] = 0u;
-      }
+      if (any) *(gptr<U32x4>)(F.bm + w0 + wl) = U32x4{0u, 0u, 0u, 0u};
       const int cnt = __popc(w.x) + __popc(w.y) + __popc(w.z) + __popc(w.w);
       nflag += (unsigned)cnt;
       int incl = cnt;
@@ -1477,7 +1467,7 @@ __device__ __forceinline__ void persist_round(const EngineArgs& a, unsigned long
 }
 
 // ---------------------------------------------------------------------------
-// Plain rounds (engine_round): the kernels of one round of a large batch, each at
+// Plain rounds: the kernels of one round of a large batch, each at
 // its own occupancy, for the round E that the workspace's epoch names.  The
 // detection of fields in tile rounds is k_sweep's, of fields in sparse rounds
 // k_sparse's; k_apply applies, and its last block does what the engine's block 0
@@ -2073,10 +2063,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
         }
       }
       any_tiles |= __syncthreads_or(sweeps);
-      // A large tile round is left to plain kernels (engine_round): every
-      // block sees the same states and leaves here, before this round's
-      // detection has done anything (the marks of its active tiles stay set
-      // for the sweep).
+      // A large tile round is left to plain rounds: every block sees the same
+      // states and leaves here, before this round's detection has done anything
+      // (the marks of its active tiles stay set for the sweep).
       if (a.split_tiles && (r > 0 || a.plain) && f0 == 0 && __syncthreads_or(big)) {
         split_here = true;
         break;
@@ -2180,7 +2169,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
 // The tail of the correction loop (kHandToTail): the sparse rounds after the
 // engine launch that handed them over, on the blocks of one XCD (tail_round),
 // until every field is done, a round needs tile sweeps (kHandToEngine: the
-// host launches the engine again), or a barrier times out.  Launched after
+// host sweeps and launches the rounds again), or a barrier times out.  Launched after
 // every engine launch that may hand over; without a handover it ends at once.
 template <class T>
 __global__ __launch_bounds__(256) void k_tail(EngineArgs a) {

@@ -234,9 +234,10 @@ hipError_t engine_zero_copy(void* p, size_t bytes, void* dst, const void* src, s
 // Fill `bytes` bytes (multiple of 4, 4-byte aligned) with the 32-bit word v.
 hipError_t engine_fill(void* p, size_t bytes, uint32_t v, hipStream_t s);
 
-// Target list: the apply pass lists its targets, the pass over apply segment
-// k in slice k mod S of the list (S = min(kCtrSlots, the field's segments),
-// list_capacity / S entries each, counted in that counter slot); when no
+// Target list: the apply pass lists its targets in S = min(kCtrSlots, the field's
+// segments) slices of list_capacity / S entries, each counted in that counter
+// slot: the engine's and the tail's pass over segment k in slice k mod S, a wave of
+// k_apply a listful in the slice of the segment it began with.  When no
 // slice overflowed, the next round examines the Freudenthal neighbours of
 // exactly those vertices instead of sweeping tiles.  A field of few segments
 // thus keeps the whole capacity in few slices.  The capacity sits near the
