@@ -16,6 +16,7 @@ import os
 import sys
 
 import torch
+from torch.autograd import forward_ad
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libpmsz.so")
@@ -274,9 +275,13 @@ def _is_derived(t):
     """True when a clone of t may be more than a copy of its memory: t is of a
     subclass, has a place in an autograd graph or a forward-mode tangent, or
     is a pending negation or a zero without memory."""
-    return (type(t) not in (torch.Tensor, torch.nn.Parameter) or
-            (t.requires_grad and torch.is_grad_enabled()) or t.is_neg() or t._is_zerotensor() or
-            torch.autograd.forward_ad.unpack_dual(t).tangent is not None)
+    if type(t) is not torch.Tensor and type(t) is not torch.nn.Parameter:
+        return True
+    if (t.requires_grad and torch.is_grad_enabled()) or t.is_neg() or t._is_zerotensor():
+        return True
+    # (no tensor has a tangent outside a forward-mode level)
+    return (getattr(forward_ad, "_current_level", 0) >= 0 and
+            forward_ad.unpack_dual(t).tangent is not None)
 
 
 def correct(f, fhat, xi, *, inplace=False, max_iters=DEFAULT_MAX_ITERS, dirs_f=None, ws=None,
