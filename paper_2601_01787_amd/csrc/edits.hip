@@ -98,15 +98,15 @@ __device__ __forceinline__ V block_excl(V v, V* sh, V* total) {
 // values read the fields twice at 1.1 and 0.5 TB/s.  512^3 binary32, 1.8 M
 // changes: find 203 us (5.3 TB/s), emit 81 us, scans 2 x 19 us, write 15 us;
 // the call 3.39 ms before, 0.36 ms now.  Spans with many changes are listed word
-// by word and written four entries per thread at a time (a lane per list and one
-// entry at a time: 2^18 binary32 values, all changed, 156 us; now 87 us).
+// by word, and written several entries per thread at a time (a lane per list and one
+// entry at a time: 2^18 binary32 values, all changed, 156 us; now 89 us).
 constexpr int kSpan = 16384;            // vertices per block
 constexpr int kWaveSpan = kSpan / 4;    // per wave: 64 ballots, one per lane
 constexpr int kFindLoads = 8;           // ballots whose loads are in flight together
 // Changes of 64 vertices that one lane of `emit` lists by itself.  Where the spans
 // fill the chip the lanes that wait for the longest list cost their issue slots, else
-// only the time of that list (2^27 binary32 values, a tenth changed: 1012 us at 32, 730
-// at 12; 2^18: 61 and 76).
+// only the time of that list (2^27 binary32 values, a tenth changed: 1012 us at 32, 712
+// at 12; 2^18: 60 and 76).
 constexpr int kDenseWord = 32, kDenseWordFull = 12;
 constexpr int64_t kFullSpans = 512;
 
@@ -249,7 +249,7 @@ template <class T, bool MAP>
 __global__ __launch_bounds__(256) void k_edit_emit(const T* fhat, const T* g, int64_t n,
                                                    EncSpan* spans, const unsigned long long* map,
                                                    uint32_t* idx, unsigned long long* steps,
-                                                   int64_t cap) {
+                                                   int64_t cap, int dense_word) {
   __shared__ unsigned long long sh[4];
   __shared__ uint32_t s_last[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -274,22 +274,18 @@ __global__ __launch_bounds__(256) void k_edit_emit(const T* fhat, const T* g, in
   uint32_t prev = __shfl_up(last, 1, 64);
   if (lane == 0) prev = 0;
   __syncthreads();
-  const uint32_t before = spans[blockIdx.x].prev;
-  prev = before > prev ? before : prev;
-  for (int k = 0; k < wave; ++k) prev = s_last[k] > prev ? s_last[k] : prev;
+  // (in the branches, so that the first gathers do not wait for it)
+  auto before = [&]() {
+    const uint32_t p = spans[blockIdx.x].prev;
+    prev = p > prev ? p : prev;
+    for (int k = 0; k < wave; ++k) prev = s_last[k] > prev ? s_last[k] : prev;
+  };
   const gptr<const T> a = as_global(fhat);
   const gptr<const T> b = as_global(g);
   unsigned long long len = 0;
-  auto entry = [&](int64_t i, int64_t rank, uint32_t before_i, T x, T y) {
-    const unsigned long long st = order_key(x) - order_key(y);
-    len += leb_len((unsigned long long)(i - (int64_t)before_i)) + leb_len(st);
-    if (rank < cap) {
-      idx[rank] = (uint32_t)i;
-      steps[rank] = st;
-    }
-  };
-  if (__ballot(__popcll(w) > (gridDim.x < kFullSpans ? kDenseWord : kDenseWordFull))) {
+  if (__ballot(__popcll(w) > dense_word)) {
     // many changes: word by word, a lane per bit
+    before();
     const int32_t r0 = __builtin_amdgcn_readfirstlane((int)r);  // (below 2^31)
     uint32_t seen = 0, last_i = (uint32_t)__builtin_amdgcn_readfirstlane((int)prev);
     for (int k0 = 0; k0 < 64; k0 += kFindLoads) {
@@ -314,17 +310,32 @@ __global__ __launch_bounds__(256) void k_edit_emit(const T* fhat, const T* g, in
       for (int k = 0; k < kFindLoads; ++k) {
         const int64_t i0 = v0 + 64 * (k0 + k);
         const unsigned long long below = word[k] & ((1ull << lane) - 1ull);
-        if ((word[k] >> lane) & 1ull)
-          entry(i0 + lane, (int64_t)r0 + seen + __popcll(below),
-                below ? (uint32_t)(i0 + 64 - __clzll(below)) : last_i, x[k], y[k]);
+        if ((word[k] >> lane) & 1ull) {
+          const uint32_t was = below ? (uint32_t)(i0 + 64 - __clzll(below)) : last_i;
+          const unsigned long long st = order_key(x[k]) - order_key(y[k]);
+          len += leb_len((unsigned long long)(i0 + lane - (int64_t)was)) + leb_len(st);
+          const int64_t at = (int64_t)r0 + seen + __popcll(below);
+          if (at < cap) {
+            idx[at] = (uint32_t)(i0 + lane);
+            steps[at] = st;
+          }
+        }
         if (word[k]) last_i = (uint32_t)(i0 + 64 - __clzll(word[k]));
         seen += __popcll(word[k]);
       }
     }
   } else {
-    for (unsigned long long bits = w; bits; bits &= bits - 1) {
+    before();
+    unsigned long long bits = w;
+    while (bits) {
       const int64_t i = v0 + 64 * lane + (__ffsll(bits) - 1);
-      entry(i, r, prev, a[i], b[i]);
+      bits &= bits - 1;
+      const unsigned long long st = order_key(a[i]) - order_key(b[i]);
+      len += leb_len((unsigned long long)(i - (int64_t)prev)) + leb_len(st);
+      if (r < cap) {
+        idx[r] = (uint32_t)i;
+        steps[r] = st;
+      }
       prev = (uint32_t)(i + 1);
       ++r;
     }
@@ -344,7 +355,7 @@ __device__ __forceinline__ uint8_t* put_leb(uint8_t* p, unsigned long long v) {
 
 // Header, table and payload.  Writes nothing when the edits exceed cap or the
 // stream exceeds out_cap.
-template <class T, int THREADS>
+template <class T, int THREADS, int U>
 __global__ __launch_bounds__(THREADS) void k_edit_write(const EncSpan* spans, const EncTotal* total,
                                                     const uint32_t* idx,
                                                     const unsigned long long* steps, int64_t n,
@@ -367,7 +378,6 @@ __global__ __launch_bounds__(THREADS) void k_edit_write(const EncSpan* spans, co
   }
   // U entries per thread at a time: their lengths (at most 15 bytes) are scanned together,
   // in 16 bits each
-  constexpr int U = 4;
   static_assert(THREADS * 15 < (1 << 16), "a sum of lengths fits its field");
   const EncSpan sp = spans[blockIdx.x];
   unsigned long long at = sp.off;
@@ -637,23 +647,25 @@ static int encode_t(const T* fhat, const T* g, int64_t n, int64_t cap, char* ws,
   EDIT_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_edit_scan<0>, dim3(1), dim3(1024), 0, s, spans, L.nspans, total);
   EDIT_TRY(hipGetLastError());
+  const int dense_word = L.nspans < kFullSpans ? kDenseWord : kDenseWordFull;
   if (L.keep_map)
     hipLaunchKernelGGL((k_edit_emit<T, true>), grid, block, 0, s, fhat, g, n, spans,
-                       (const unsigned long long*)map, idx, steps, cap);
+                       (const unsigned long long*)map, idx, steps, cap, dense_word);
   else
     hipLaunchKernelGGL((k_edit_emit<T, false>), grid, block, 0, s, fhat, g, n, spans,
-                       (const unsigned long long*)map, idx, steps, cap);
+                       (const unsigned long long*)map, idx, steps, cap, dense_word);
   EDIT_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_edit_scan<1>, dim3(1), dim3(1024), 0, s, spans, L.nspans, total);
   EDIT_TRY(hipGetLastError());
-  // (twice the threads per span where the spans leave the chip idle: 2^18 binary64
-  // values, all changed, 126 -> 109 us; 2^27, one in 74 changed, 865 -> 888)
+  // (more threads and entries per span where the spans leave the chip idle: the
+  // call on 2^18 binary64 values, all changed, takes 110 us this way and 126 with 256
+  // threads; on 2^27, one in 74 changed, 888 and 862)
   if (L.nspans < kFullSpans)
-    hipLaunchKernelGGL((k_edit_write<T, 512>), grid, dim3(512), 0, s, (const EncSpan*)spans,
+    hipLaunchKernelGGL((k_edit_write<T, 512, 4>), grid, dim3(512), 0, s, (const EncSpan*)spans,
                        (const EncTotal*)total, (const uint32_t*)idx,
                        (const unsigned long long*)steps, n, cap, (unsigned long long)out_cap, out);
   else
-    hipLaunchKernelGGL((k_edit_write<T, 256>), grid, block, 0, s, (const EncSpan*)spans,
+    hipLaunchKernelGGL((k_edit_write<T, 256, 2>), grid, block, 0, s, (const EncSpan*)spans,
                        (const EncTotal*)total, (const uint32_t*)idx,
                        (const unsigned long long*)steps, n, cap, (unsigned long long)out_cap, out);
   EDIT_TRY(hipGetLastError());
