@@ -2558,12 +2558,14 @@ static hipError_t launch_t(const EngineArgs& a, hipStream_t s, int* grid_out, bo
                        s)) != hipSuccess)
     return e;
   const int64_t want = a.total_tiles > a.total_segs ? a.total_tiles : a.total_segs;
-  // The full register budget (200 registers, two waves per SIMD) where the grid does
-  // not fill the chip anyway or the launch is left with sparse rounds: the tile
-  // march spills at four (three) waves, and a spill's first touch of memory costs a
-  // phase microseconds.  512 x 512 x 512: 1488 -> 1470 us, 257 x 253 x 190 targeted
-  // 555 -> 527 us, 64^3 280 -> 268 us; a serving step with tiles on the whole
-  // chip 1112 -> 1155 us, so those keep the waves.
+  // The full register budget (200 registers, two waves per SIMD, so 512 resident
+  // blocks) where a grid of a block per tile fits in that, or the launch is left with
+  // sparse rounds: the tile march spills at four (three) waves, and a spill's first
+  // touch of memory costs a phase microseconds.  Whole calls with four (three) waves
+  // and with two, us: 64^3 binary32 (256 tiles) 271 and 265, two of 64^3 (512) 311 and
+  // 294, binary64 278 and 265; two of 1337 x 1021 binary64 with dense rounds (536) 472 and
+  // 476, two of 100^3 (600) 640 and 656, eight of 100^3 (2400) 1133 and 1218, binary32 1101
+  // and 1143; 320^3, sparse after plain rounds, 627 and 593.
   if (a.plain || want <= 512) return launch_w<T, 1>(a, s, want, grid_out);
   return launch_w<T, sizeof(T) == 4 ? 4 : 3>(a, s, want, grid_out);
 }
