@@ -9,11 +9,11 @@ namespace pmsz {
 template <class T, int DIM>
 __global__ __launch_bounds__(256) void k_dirs(const T* h, TileGeo G, uint8_t* dirs,
                                               int32_t run) {
-  __shared__ WaveLds<T, DIM, KIND_DIRS> sm[4];
+  __shared__ WaveLds<T, DIM, KIND_DIRS_ANY> sm[4];
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int32_t tile = (int32_t)first_tile(blockIdx.x, run) + wave;
   if (tile >= (int32_t)tile_count(G)) return;
-  wave_tile<T, KIND_DIRS, false, false, DIM>(sm[wave], nullptr, h, (const T*)nullptr, dirs,
+  wave_tile<T, KIND_DIRS_ANY, false, false, DIM>(sm[wave], nullptr, h, (const T*)nullptr, dirs,
                                              nullptr, T(0), G, tile, nullptr, (T*)nullptr);
 }
 

@@ -180,7 +180,8 @@ enum TileKind {
                         // written and used on the way (wave_tiles.hpp only)
   KIND_FIRST_GIVEN = 2, // first round: validation of g against f, mismatch
                         // detection of g against the given directions of f
-  KIND_NEXT = 3         // later rounds: mismatch detection of g
+  KIND_NEXT = 3,        // later rounds: mismatch detection of g
+  KIND_DIRS_ANY = 4     // as KIND_DIRS, of values that may be NaN (wave_tiles.hpp only)
 };
 
 // Per-tile counts, packed three to a word (21 bits each) so that one block

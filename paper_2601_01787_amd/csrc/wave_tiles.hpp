@@ -179,7 +179,7 @@ struct WaveLds {
   // (2D: one more than a tile's rows, the march runs them in pairs)
   typename EdgeOf<T, DIM>::type
       edge[KIND == KIND_FIRST ? 2 : 1][DIM == 3 ? kEdgeGroup : kMaxChunk + 3];
-  static constexpr bool FLAGS = KIND != KIND_DIRS;
+  static constexpr bool FLAGS = KIND != KIND_DIRS && KIND != KIND_DIRS_ANY;
   uint32_t flags[FLAGS ? (DIM == 3 ? (kMaxChunk + 2) * (TY + 2) * kFlagW3
                                    : (kMaxChunk + 2) * kFlagW2)
                        : 1];
@@ -326,6 +326,120 @@ __device__ __forceinline__ unsigned flag_mismatch(uint32_t o, uint32_t d, int32_
                          flags, fdelta, PROP ? prop : nullptr, g, lo);
 }
 
+// Direction bytes of a wave's tile by the merges of tiles.hpp, each box reduced for
+// its own vertex.  They define the bytes where values are NaN: such a vertex points to
+// itself both ways, and every other one to itself, to a NaN or beyond its own value,
+// so that the pointers stay a forest.  The marches below share a box between two
+// vertices and keep neither, so a wave that meets a NaN there (an unordered pair costs
+// one comparison) makes its tile again this way.  512^3 binary32: 208 us without NaN,
+// 207 without the comparisons; 438 us with a NaN in every tile, 246 in the block
+// march that reduced every box for its own vertex.
+template <class T>
+__device__ __forceinline__ T nan_of() {
+  return T(__builtin_nan(""));
+}
+template <class T>
+__device__ __forceinline__ void wave_dirs_any3(gptr<const T> h, gptr<uint8_t> dirs,
+                                               const TileGeo& G, int32_t x0, int32_t y0,
+                                               int32_t z0, int32_t z1) {
+  constexpr int R = TY, V = TY + 2;
+  const int lane = threadIdx.x & 63;
+  const int32_t X = x0 + lane, xc = X < G.nx ? X : G.nx - 1;
+  // lanes 0..5 hold the values left of the tile's lines, 8..13 those right of them
+  const int er = lane & 7;
+  const bool e_right = lane & 8;
+  const bool e_in = lane < 16 && er < V && (er > 0 || y0 > 0) && er - 1 < G.ny - y0 &&
+                    (e_right ? G.nx - x0 > TX : x0 > 0);
+  const int64_t e_at = (int64_t)G.nx * clamp_step(y0, er - 1, G.ny) +
+                       clamp_step(x0, e_right ? TX : -1, G.nx);
+  struct Plane {
+    T c[V], e;
+  };
+  // (one plane ahead; what lies outside the grid is read inside it and then absent)
+  auto fetch = [&](int32_t q, Plane& S) {
+    const gptr<const T> h_p = h + (int64_t)G.sxy * clamp_step(z0, q - 1, G.nz);
+#pragma unroll
+    for (int k = 0; k < V; ++k) S.c[k] = h_p[(int64_t)G.nx * clamp_step(y0, k - 1, G.ny) + xc];
+    S.e = h_p[e_at];
+  };
+  Ext<T> up[R], dn[R], low[R];  // squares of the last plane; lower boxes of its vertices
+  Plane now, next;
+  fetch(0, next);
+  for (int32_t q = 0; q < z1 - z0 + 2; ++q) {
+    now = next;
+    fetch(q + 1, next);
+    const int32_t p = z0 - 1 + q;
+    const bool plane = p >= 0 && p < G.nz;
+    const T e = plane && e_in ? now.e : nan_of<T>();
+    T c[V], l[V], r[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      c[k] = plane && (k > 0 || y0 > 0) && k - 1 < G.ny - y0 && X < G.nx ? now.c[k] : nan_of<T>();
+      l[k] = lane_shift<kFromLeft>(c[k], __shfl(e, k, 64));
+      r[k] = lane_shift<kFromRight>(c[k], __shfl(e, 8 + k, 64));
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const Ext<T> u = merge_up(merge_up(ext_of(c[k + 1], 0), ext_of(r[k + 1], 1)),
+                                merge_up(ext_of(c[k + 2], 2), ext_of(r[k + 2], 3)));
+      const Ext<T> d = merge_dn(merge_dn(ext_of(l[k], 11), ext_of(c[k], 10)),
+                                merge_dn(ext_of(l[k + 1], 9), ext_of(c[k + 1], 0)));
+      if (q > 1 && X < G.nx && y0 + k < G.ny) {
+        const Ext<T> b = merge_up(low[k], merge_up(up[k], with_bits(u, 4)));
+        dirs[(int64_t)G.sxy * (p - 1) + (int64_t)G.nx * (y0 + k) + X] =
+            (uint8_t)(b.ca | (b.cd << 4));
+      }
+      if (q > 0) low[k] = merge_dn(with_bits(dn[k], 12), d);
+      up[k] = u;
+      dn[k] = d;
+    }
+  }
+}
+// The same for a 2D tile.
+template <class T>
+__device__ __forceinline__ void wave_dirs_any2(gptr<const T> h, gptr<uint8_t> dirs,
+                                               const TileGeo& G, int32_t x0, int32_t y0,
+                                               int32_t y1) {
+  constexpr int C = 4;
+  const int32_t X = x0 + C * (int32_t)(threadIdx.x & 63);
+  struct Row {
+    T c[C], l, r;
+  };
+  auto fetch = [&](int32_t q, Row& S) {
+    const gptr<const T> h_p = h + (int64_t)G.nx * clamp_step(y0, q - 1, G.ny);
+#pragma unroll
+    for (int j = 0; j < C; ++j) S.c[j] = h_p[X + j < G.nx ? X + j : G.nx - 1];
+    S.l = h_p[x0 ? x0 - 1 : 0];
+    S.r = h_p[clamp_step(x0, RX, G.nx)];
+  };
+  Ext<T> up[C], dn[C], low[C];  // pairs of the last row; lower boxes of its vertices
+  Row now, next;
+  fetch(0, next);
+  for (int32_t q = 0; q < y1 - y0 + 2; ++q) {
+    now = next;
+    fetch(q + 1, next);
+    const int32_t p = y0 - 1 + q;
+    const bool row = p >= 0 && p < G.ny;
+    T c[C + 2];  // from the column left of the lane's
+#pragma unroll
+    for (int j = 0; j < C; ++j) c[j + 1] = row && X + j < G.nx ? now.c[j] : nan_of<T>();
+    c[0] = lane_shift<kFromLeft>(c[C], row && x0 > 0 ? now.l : nan_of<T>());
+    c[C + 1] = lane_shift<kFromRight>(c[1], row && G.nx - x0 > RX ? now.r : nan_of<T>());
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+      const Ext<T> u = merge_up(ext_of(c[j + 1], 0), ext_of(c[j + 2], 1));
+      const Ext<T> d = merge_dn(ext_of(c[j], 9), ext_of(c[j + 1], 0));
+      if (q > 1 && X + j < G.nx) {
+        const Ext<T> b = merge_up(low[j], merge_up(up[j], with_bits(u, 2)));
+        dirs[(int64_t)G.nx * (p - 1) + X + j] = (uint8_t)(b.ca | (b.cd << 4));
+      }
+      if (q > 0) low[j] = merge_dn(with_bits(dn[j], 10), d);
+      up[j] = u;
+      dn[j] = d;
+    }
+  }
+}
+
 // One 3D tile (tiles.hpp's 64 x 4 x chunk) on one wave.  Arguments as tile3;
 // copy_to (COPY): the tile's values of h go there too (lanes and lines outside
 // the grid repeat the last ones inside).
@@ -344,7 +458,8 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
   const gptr<const T> h = as_global((const T*)uniform_ptr(h_in));
   const gptr<const T> f = as_global((const T*)uniform_ptr(f_in));
   const gptr<uint8_t> dirs = as_global(uniform_ptr(dirs_in));
-  constexpr bool kSweep = KIND != KIND_DIRS, kMake = KIND == KIND_FIRST;
+  constexpr bool kAny = KIND == KIND_DIRS_ANY;
+  constexpr bool kSweep = KIND != KIND_DIRS && !kAny, kMake = KIND == KIND_FIRST;
   constexpr bool kFirst = KIND == KIND_FIRST_GIVEN || kMake;
   constexpr int R = TY, V = TY + 2;  // lines out, lines in
   const int lane = threadIdx.x & 63;
@@ -429,7 +544,9 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
     e.a = p[e_left];
     e.b = p[e_own];
   };
+  bool any_nan = false;  // (kAny)
   auto edges_store1 = [&](int which, int32_t q0, const Edges& e) {
+    if (kAny) any_nan |= __builtin_isunordered(e.right, e.a);
     const XPair<T> xp = x_pair(e.a, e.b, 0u);
     const Box<T> ln{xp.hi, xp.lo, xp.c, xp.c ^ 1u};
     const Box<T> sq1 =
@@ -532,6 +649,10 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
     const int32_t z = z0 + q - 2;  // plane of the vertices finished
     XPair<T> xp[V], xf[V];
     pairs(parity, S.v, E, xp);
+    if (kAny) {
+#pragma unroll
+      for (int r = 0; r < V; r += 2) any_nan |= __builtin_isunordered(S.v[r], S.v[r + 1]);
+    }
     if (kMake) pairs(parity, S.fv, Ef, xf);
     if (COPY && MODE != 0) {
       const Rsrc rc = rsrc_at(copy_to + (plane_at(q) + at0), q < nq - 1);
@@ -617,6 +738,10 @@ __device__ __forceinline__ LaneCounts wave_tile3(LDS& sm, const int32_t* fdelta,
     last_plane(q + 3);
     step(Int<2>{}, Int<1>{}, q + 3, P1);
   }
+  if (kAny && __ballot(any_nan) != 0ull) {
+    __builtin_amdgcn_s_waitcnt(0);  // the march's stores are done
+    wave_dirs_any3<T>(h, dirs, G, x0, y0, z0, z1);
+  }
   if (kSweep) {
     wave_lds_fence();
     wave_flush_rows<kFlagW3>(sm.flags, (z1 - z0 + 2) * (TY + 2), [&](int32_t r) {
@@ -642,7 +767,8 @@ __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelt
   const gptr<const T> h = as_global((const T*)uniform_ptr(h_in));
   const gptr<const T> f = as_global((const T*)uniform_ptr(f_in));
   const gptr<uint8_t> dirs = as_global(uniform_ptr(dirs_in));
-  constexpr bool kSweep = KIND != KIND_DIRS, kMake = KIND == KIND_FIRST;
+  constexpr bool kAny = KIND == KIND_DIRS_ANY;
+  constexpr bool kSweep = KIND != KIND_DIRS && !kAny, kMake = KIND == KIND_FIRST;
   constexpr bool kFirst = KIND == KIND_FIRST_GIVEN || kMake;
   constexpr int C = 4;
   const int lane = threadIdx.x & 63;
@@ -705,11 +831,13 @@ __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelt
   fetch(1, P1);
 
   // ---- the tile's edges
+  bool any_nan = false;  // (kAny)
   {
     const int32_t xr = clamp_step(x0, RX, G.nx);
     const uint32_t gone_x = x0 == 0 ? 1u : 0u;
     auto edges_of = [&](gptr<const T> from, int32_t q, Edge2<T>& E) {
       E.right = from[row_at(q) + xr];
+      if (kAny) any_nan |= __builtin_isunordered(E.right, from[row_at(q) + (x0 ? x0 - 1 : x0)]);
       Box<T> ln[2];
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
@@ -780,6 +908,10 @@ __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelt
     const int32_t y = y0 + q - 2;  // row of the vertices finished
     XPair<T> xp[C], xf[C];
     pairs(parity, S.v, E, xp);
+    if (kAny) {
+#pragma unroll
+      for (int j = 0; j < C; j += 2) any_nan |= __builtin_isunordered(S.v[j], S.v[j + 1]);
+    }
     if (kMake) pairs(parity, S.fv, Ef, xf);
     if (COPY && MODE != 0) {
       const Rsrc rc = rsrc_at(copy_to + (row_at(q) + x0), q < nq - 1);
@@ -858,6 +990,10 @@ __device__ __forceinline__ LaneCounts wave_tile2_t(LDS& sm, const int32_t* fdelt
     step(Int<2>{}, Int<0>{}, q, P0);
     last_row(q + 1);
     step(Int<2>{}, Int<1>{}, q + 1, P1);
+  }
+  if (kAny && __ballot(any_nan) != 0ull) {
+    __builtin_amdgcn_s_waitcnt(0);  // the march's stores are done
+    wave_dirs_any2<T>(h, dirs, G, x0, y0, y1);
   }
   if (kSweep) {
     wave_lds_fence();

@@ -91,3 +91,63 @@ def test_directions_of_the_longest_row():
         want = (mx | (mn << 4)).to(torch.uint8)
         i, j = (0 if a == 0 else 1), (len(v) if b == n else len(v) - 1)
         assert torch.equal(d[a + i:a + j], want[i:j]), at
+
+
+def _merged_directions(h):
+    """Direction bytes by the stencil's merges, every box reduced for its own vertex;
+    neighbours outside the grid are NaN, as are some values."""
+    d3 = h.ndim == 3
+    p = np.pad(h if d3 else h[None], 1, constant_values=np.nan)
+    nz, ny, nx = (h if d3 else h[None]).shape
+
+    def at(m, sign, code):
+        dx, dy, dz = sign * (m & 1), sign * ((m >> 1) & 1), sign * (m >> 2)
+        v = p[1 + dz:1 + dz + nz, 1 + dy:1 + dy + ny, 1 + dx:1 + dx + nx]
+        c = np.full(v.shape, code, np.uint8)
+        return v, v, c, c
+
+    def merge(a, b, hi, lo):  # hi, lo: where b is taken
+        return (np.where(hi, b[0], a[0]), np.where(lo, b[1], a[1]), np.where(hi, b[2], a[2]),
+                np.where(lo, b[3], a[3]))
+
+    def up(a, b):
+        return merge(a, b, b[0] >= a[0], b[1] < a[1])
+
+    def down(a, b):
+        return merge(a, b, ~(a[0] > b[0]), ~(a[1] <= b[1]))
+
+    def box(sign, m, bits):  # the box of the offsets m | {0 .. bits}
+        if bits == 0:
+            return at(m, sign, (8 | m if m else 0) if sign < 0 else m)
+        bit = 1 << (bits - 1)
+        if sign > 0:
+            return up(box(sign, m, bits - 1), box(sign, m | bit, bits - 1))
+        return down(box(sign, m | bit, bits - 1), box(sign, m, bits - 1))
+
+    with np.errstate(invalid="ignore"):
+        e = up(box(-1, 0, 3 if d3 else 2), box(1, 0, 3 if d3 else 2))
+    return (e[2] | (e[3] << 4)).reshape(h.shape)
+
+
+@pytest.mark.parametrize("shape", [(35, 9, 130), (5, 17, 64), (2, 3, 65), (1, 1, 9), (70, 515),
+                                   (33, 256), (3, 300), (1, 5)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_directions_beside_nan(shape, dtype):
+    """One NaN (in a tile, on its edge or just outside), some, many, all: the bytes
+    are those of the merges, and their pointers a forest that verify takes."""
+    rng = np.random.default_rng(8)
+    f = random_case(shape, dtype, 8, ties=len(shape) == 2)[0]
+    assert np.array_equal(_merged_directions(f), oracle.directions(f))
+    n = f.size
+    spots = [rng.integers(n, size=1) for _ in range(12)] + [np.array([0]), np.array([n - 1])]
+    spots += [rng.integers(n, size=k) for k in (1 + n // 200, 1 + n // 3)] + [np.arange(n)]
+    if len(shape) == 3 and shape[0] > 32:  # around the first tile's far corner
+        spots += [np.ravel_multi_index(at, shape) for at in
+                  ((32, 4, 64), (32, 3, 63), (31, 4, 63), (31, 3, 64), (31, 3, 63))]
+    for at in spots:
+        g = f.copy()
+        g.reshape(-1)[at] = np.nan
+        assert np.array_equal(host(pmsz.directions(dev(g))), _merged_directions(g)), at
+        rep = pmsz.verify(dev(f), dev(g), dev(f), 0.1)
+        assert rep["bound_violations"] == np.isnan(g).sum() and rep["max_abs_err"] == np.inf
