@@ -340,12 +340,11 @@ inline int plain_rounds_of(int64_t segs) { return segs >= 2048 ? kPlainRounds : 
 // Sweep kernels of those rounds: in all of them for more than kSweepFields
 // fields, else in the first two; a round that needs tiles later waits for a
 // read-back (a field of kSplitVoxels or more) or is the engine's.  A sweep with
-// nothing to do costs about 3 us, a read-back with its idle launches 85 us.  Two
+// nothing to do costs 3 to 6 us, a read-back with its idle launches 85 us.  Two
 // sweeps against one, us: white noise that stays dense, 208^3 binary64 1480 -> 1228,
 // eight fields of 128^3 1619 -> 1561; fields that are sparse after round 1 within 2
-// us.  Sweeps in every round against two: sixteen sparse fields of 2000 x 2400 774
-// -> 799, sixteen dense ones of 144^3 3102 -> 2341; against one: 24 of the first 1031 ->
-// 1109, 24 of the second 4595 -> 3001.
+// us.  Sweeps in every round against one: sparse fields of 2000 x 2400, sixteen 774 ->
+// 799, 24 1031 -> 1109; dense ones of 144^3, sixteen 3102 -> 2341, 24 4595 -> 3001.
 constexpr int32_t kSweepFields = 16;
 
 // Events around a call's launches and the figures of the last run.
