@@ -311,7 +311,8 @@ int pmsz_decode_edits(const pmsz_grid* grid, const uint8_t* in, size_t n_bytes, 
  * nx*ny*nz, written with the index of the maximum (resp. minimum) reached by
  * following n_max (resp. n_min); either may be NULL.  ws: device workspace of
  * pmsz_workspace_size(grid, PMSZ_WS_LABELS) bytes, 256-byte aligned.  The
- * labels are found tile by tile on the device; paths too long for that are
+ * labels are found tile by tile on the device (in thin grids, which fill little
+ * of their tiles, from every vertex's neighbour); paths too long for that are
  * finished by pointer jumping, passes queued in batches with one read-back per
  * batch.  Bytes holding a code that does
  * not name a neighbour inside the grid, or pointers that do not form a
@@ -325,7 +326,7 @@ int pmsz_labels(const pmsz_grid* grid, const uint8_t* dirs, int32_t* max_label,
  * runs it twice; the record is the second run's).  Host struct. */
 typedef struct {
   int64_t vertices;    /* vertices labelled                                   */
-  int64_t passes_max;  /* passes of the max labels: the tile pass, then the
+  int64_t passes_max;  /* passes of the max labels: the first one, then the
                           pointer-jumping passes that had labels to finish (0
                           when not requested)                                 */
   int64_t passes_min;  /* the same for the min labels                         */

@@ -340,7 +340,7 @@ static LabelTiles label_tiles(const Geo& G) {
 // grid, so grids that fill less than a quarter of their tiles start from
 // k_labels_init.  Both ways, us, white noise / smooth: 4096 vertices per tile
 // (2048 x 2048 x 4) 294 / 319 by tiles, 261 / 441 from k_labels_init; 2048
-// (2048 x 2048 x 2) 274 / 324 and 136 / 272; 1024 (8 M x 4 in 2D) 1114 / 1177 and 250 /
+// (2048 x 2048 x 2) 274 / 324 and 136 / 272; 1024 (4 x 4 M in 2D) 1114 / 1177 and 250 /
 // 383; 64 (2 x 2 x 2 M) 6909 / 7166 and 142 / 188.  8192 and more: tiles (1024 x
 // 2048 x 8: 187 / 207 and 256 / 431).  A grid within one tile is one launch by
 // tiles and five the other way (3 x 3 x 3: 55 and 64).
