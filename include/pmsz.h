@@ -428,9 +428,10 @@ typedef struct {
   double dirs_ms;    /* directions of f, computed before the correction (0 when
                         the caller gave them, and for large batches, whose
                         first sweep makes them)                                 */
-  double sweep_ms;   /* the sweep kernels: by events around the first of those
-                        queued together, by their rounds' records (which hold
-                        the round's sparse examinations too) for the others     */
+  double sweep_ms;   /* the sweep kernels: by events around the first round's and
+                        the first after a read-back, by their rounds' records
+                        (which hold the launch gaps and the round's sparse
+                        examinations too) for the others                        */
   int32_t tail_rounds; /* rounds run by the tail kernel: the sparse rounds
                         after a round with few edits, on the blocks of one
                         XCD (Sec. IV-A's loop, unchanged)                       */

@@ -340,18 +340,19 @@ inline int plain_rounds_of(int64_t segs) { return segs >= 2048 ? kPlainRounds : 
 // Sweep kernels of those rounds: in all of them for more than kSweepFields
 // fields, else in the first two; a round that needs tiles later waits for a
 // read-back (a field of kSplitVoxels or more) or is the engine's.  A sweep with
-// nothing to do costs 3 to 6 us, a read-back with its idle launches 85 us.  Two
+// nothing to do costs 4 to 8 us, a read-back with its idle launches 85 us.  Two
 // sweeps against one, us: white noise that stays dense, 208^3 binary64 1480 -> 1228,
-// eight fields of 128^3 1619 -> 1561; fields that are sparse after round 1 within 2
-// us.  Sweeps in every round against one: sparse fields of 2000 x 2400, sixteen 774 ->
-// 799, 24 1031 -> 1109; dense ones of 144^3, sixteen 3102 -> 2341, 24 4595 -> 3001.
+// eight fields of 128^3 1619 -> 1561; Perlin noise of 208^3, eps 1e-3 711 -> 598, eps
+// 1e-4 (sparse after round 1) 414 -> 422.  Sweeps in every round against one: sparse
+// fields of 2000 x 2400, sixteen 774 -> 799, 24 1031 -> 1109; dense ones of 144^3, sixteen
+// 3102 -> 2341, 24 4595 -> 3001.
 constexpr int32_t kSweepFields = 16;
 
 // Events around a call's launches and the figures of the last run.
 struct Timing {
-  // start, after the directions, after the first sweep (split); start and end of
-  // a later group of launches (kGroup, kGroup + 1); around the first sweep of a
-  // group (kSweep, kSweep + 1)
+  // before the directions, after them, after the first sweep (split); start and end
+  // of a later group of launches (kGroup, kGroup + 1); around its first sweep
+  // (kSweep, kSweep + 1)
   static constexpr int kGroup = 3, kSweep = 5;
   hipEvent_t ev[kSweep + 2] = {};
   uint64_t gen = 0;
@@ -478,16 +479,18 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
   // keep the whole loop in one launch (the extra launches would cost more than they
   // save).
   constexpr int kGroup = Timing::kGroup, kSweep = Timing::kSweep;
-  if (timed) HIP_TRY(hipEventRecord(tm.ev[0], s));
   // (the first sweep of a large batch makes the directions on the way: both read f)
   const int first_kind = split && all_dirs ? KIND_FIRST : KIND_FIRST_GIVEN;
-  if (need_dirs && first_kind != KIND_FIRST)
-    HIP_TRY(engine_dirs(dtype, dims, a.fd, n, P.total_tiles, s));
+  const bool dirs_first = need_dirs && first_kind != KIND_FIRST;
+  // (an event costs about 5 us)
+  if (timed && dirs_first) HIP_TRY(hipEventRecord(tm.ev[0], s));
+  if (dirs_first) HIP_TRY(engine_dirs(dtype, dims, a.fd, n, P.total_tiles, s));
   if (timed) HIP_TRY(hipEventRecord(tm.ev[1], s));
+  int64_t group = 0;  // groups of launches read back
   auto sweep = [&](int i) -> int {  // of a round's marked tiles
-    // (two events cost about 11 us: the later sweeps of a group are timed by their
-    // rounds' records)
-    const bool events = timed && i == 0;
+    // (sweeps are timed by their rounds' records, but for the first after a read-back,
+    // whose record starts before that)
+    const bool events = timed && group > 0 && i == 0;
     if (events) HIP_TRY(hipEventRecord(tm.ev[kSweep], s));
     HIP_TRY(engine_sweep(dtype, KIND_NEXT, P.edit_mode != 0, dims, a, s));
     if (events) HIP_TRY(hipEventRecord(tm.ev[kSweep + 1], s));
@@ -531,7 +534,7 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
   int32_t sweeps = split ? 1 : 0, tail_rounds = 0, handbacks = 0;
   int group_sweeps = split ? n_sweeps : 0;  // of the group of launches just read back
   unsigned long long group_round = split ? 1 : 0;  // the round of the first of them
-  for (int64_t group = 0;; ++group) {
+  for (;;) {
     // the staging buffer is reused for the results: the upload above is
     // stream-ordered before this copy, so it has been consumed
     HIP_TRY(hipMemcpyAsync(stage, ctl, kCtlHostBytes, hipMemcpyDeviceToHost, s));
@@ -559,7 +562,7 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
         if (E >= hc->epoch || E >= (unsigned long long)kTraceRounds ||
             tr[kTraceSlots * E + 3] == tr[kTraceSlots * E + 6])
           continue;
-        if (i == 0)
+        if (group > 0 && i == 0)
           HIP_TRY(hipEventElapsedTime(&ms, tm.ev[kSweep], tm.ev[kSweep + 1]));
         else
           ms = (float)((double)(tr[kTraceSlots * E + 1] - tr[kTraceSlots * E]) * 1e-5);
@@ -579,6 +582,7 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
     // the launches ended before a round with tile sweeps: a large one (split
     // batches), or one after the tail (k_tail handed the loop back)
     if (!split && hc->handoff != kHandToEngine) break;
+    ++group;
     a.has_fresh = 0;
     group_round = hc->epoch;
     group_sweeps = split ? n_sweeps : 1;
@@ -604,7 +608,7 @@ int run_batch(int dtype, BatchPlan& P, const uint8_t* const* dirs_given, void* w
     return PMSZ_OK;
   }
   float dirs_ms = 0.f;
-  if (need_dirs && first_kind != KIND_FIRST)  // (else the sweep's, or the caller's)
+  if (dirs_first)  // (else the sweep's, or the caller's)
     HIP_TRY(hipEventElapsedTime(&dirs_ms, tm.ev[0], tm.ev[1]));
   memset(&tm.last, 0, sizeof(tm.last));
   tm.last.dirs_ms = dirs_ms;
