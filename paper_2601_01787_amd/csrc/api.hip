@@ -846,7 +846,7 @@ int labels_impl(const Geo& G, const uint8_t* dirs, int32_t* lmax, int32_t* lmin,
     return PMSZ_OK;
   };
   if (labels_by_tiles(G)) {
-    // (the tile pass counts invalid bytes when both labels are asked for)
+    // the tile pass checks the codes of the labels asked for
     if (!lmax || !lmin) HIP_TRY(launch_check_dirs(dirs, G, bad, s));
     if (lmax || lmin) HIP_TRY(launch_labels_tile(dirs, G, lmax, lmin, flags, bad, s));
   } else {
@@ -857,9 +857,17 @@ int labels_impl(const Geo& G, const uint8_t* dirs, int32_t* lmax, int32_t* lmin,
     HIP_TRY(hipEventRecord(tm.ev[1], s));
     HIP_TRY(hipMemcpyAsync(stage, ws, kLabelsWsBytes, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    if (*nbad)
+    if (*nbad) {
+      // (codes, some of them counted twice, and cycles: the bytes, if any, are
+      // counted for the message)
+      const unsigned long long cycles = *nbad;
+      HIP_TRY(engine_zero(bad, 8, s));
+      HIP_TRY(launch_check_dirs(dirs, G, bad, s));
+      HIP_TRY(hipMemcpyAsync(stage, bad, 8, hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipStreamSynchronize(s));
       return fail(PMSZ_ERR_INVALID_ARG, "%llu direction bytes hold a code that is not a neighbour "
-                  "of their vertex, or lie on a cycle of pointers", *nbad);
+                  "of their vertex, or lie on a cycle of pointers", *nbad ? *nbad : cycles);
+    }
     if (!open[2 * (pass - 1)] && !open[2 * (pass - 1) + 1]) break;
     if (pass + kLabelBatch > kLabelMaxPasses)
       return fail(PMSZ_ERR_INVALID_ARG,

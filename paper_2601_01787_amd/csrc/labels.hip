@@ -148,7 +148,6 @@ k_labels_tile(const uint8_t* __restrict__ dirs_in, Geo G, int32_t tiles_x, int32
                           (DIM == 2 ? kDownZ | kUpZ : 0u);
   const uint32_t tile_x = (lane == 0 ? kDownX : 0u) | (lane == 63 ? kUpX : 0u);
   unsigned nb = 0;
-  uint32_t wrongs = 0;  // bit k: this thread's vertex k has a code that is not valid
   const char* up = (const char*)s_up;
   auto id_at = [&](uint32_t o) { return (uint32_t)*(const uint16_t*)(up + o); };
   for (int which = 0; which < 2; ++which) {
@@ -172,7 +171,7 @@ k_labels_tile(const uint8_t* __restrict__ dirs_in, Geo G, int32_t tiles_x, int32
       const uint32_t wrong = (grid >> code) & 1u;
       const uint32_t out = ((tile & ~grid) >> code) & 1u;
       const uint32_t end = ((tile | grid | 1u) >> code) & 1u;
-      wrongs |= wrong << k;
+      nb += wrong;
       ends |= end << k;
       outs |= out << k;
       s_up[v >> 1] = (uint16_t)(end ? v : v + (uint32_t)s_step[code]);
@@ -258,8 +257,6 @@ k_labels_tile(const uint8_t* __restrict__ dirs_in, Geo G, int32_t tiles_x, int32
       if (x < nx && y0 + row_y(r) < ny && z0 + row_z(r) < nz) lab[s_row[r] + lane] = l;
     }
   }
-  // (with one label array alone, launch_check_dirs counts the bytes)
-  if (lmax && lmin) nb += __popc(wrongs);
   const unsigned long long all_bad = wave_sum(nb);
   if (lane == 0 && all_bad) atomicAdd(bad, all_bad);
 }
